@@ -116,6 +116,13 @@ DEVI int logical_wg(int total_wg, int reverse = 0) {
   return reverse ? total_wg - 1 - l : l;
 }
 
+// The same contiguous runs for a grid of any size n: work-groups i = x (mod 8) take run x, whose
+// length is their count.
+DEVI int xcd_chunk(int i, int n) {
+  const int x = i & 7, q = n >> 3, r = n & 7;
+  return x * q + min(x, r) + (i >> 3);
+}
+
 template <class T, class A>
 DEVI T pick_task(const A& args, int wg) {
   if (args.table == nullptr) return args.t0;

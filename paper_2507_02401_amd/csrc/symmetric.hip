@@ -24,6 +24,7 @@
 // Kernels (one work-group = one output tile, 256 threads):
 //   k_sym_down  a_out = A a_in: the tile's input window (2T + L - 2 per axis) is staged in LDS
 //               through per-axis tables of reflected indices, then filtered axis 2, 1, 0.
+//   k_sym_down_col  axis 0 of a 3-D analysis level whose slices went through the 2-D k_sym_down.
 //   k_sym_up    out = alpha * same + beta * S_a z: the window of z (U/2 + L/2 - 1 per axis,
 //               starting at half the tile origin) is staged with zeros outside [0, l), then
 //               filtered axis 2, 1, 0; the last pass writes the combination to global memory.
@@ -753,6 +754,77 @@ __global__ void __launch_bounds__(256) k_sym_shell(SymShell S, Filter f) {
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// Axis 0 of a split 3-D analysis level.  A level of a 3-D grid is the tensor product of its axes, so
+// it can run as the 2-D level (k_sym_down) over every slice of every instance followed by one pass
+// along axis 0 over a quarter of the level's samples.  Against the 3-D tile (whose window is 22 x 30 x
+// 46 samples for 512 outputs at 16 taps) this filters the halo of two axes only: ~130 instead of 433
+// FMA per output, at the price of writing and reading that quarter once.  The taps are summed in the
+// tile's order (axis 2, 1, 0): identical bits.
+//
+// The arrays are [instance][slice][`slice` floats], equal slices (a multiple of 4 floats) on both
+// sides.  A thread takes four adjacent floats of a slice and kColChunk outputs: every access is a
+// coalesced 16-byte one, all loads of the window are in flight before the first sum, and chunks of
+// the same column, which share most of their windows, run one after the other on one XCD.  Bound by
+// memory and, on small volumes, by launch latency: 2 x 96 x 112 x 160, 16 taps, 3 levels, a call
+// 148.7 -> 58.7 us, transposed 198.5 -> 96.6 us (finest tile alone: 80.5 us).
+struct SymCol {
+  const float* in;
+  float* out;
+  int64_t slice;         // floats per slice
+  int32_t ni, no;        // slices of one instance of in / out
+  int32_t nblk, nchunk;  // 256-thread blocks per slice, chunks per instance
+};
+
+constexpr int kColChunk = 4;
+
+template <int L, bool ZX>
+__global__ void __launch_bounds__(256) k_sym_down_col(SymCol S, Filter f) {
+  constexpr int C = kColChunk, W = 2 * C + L - 2;
+  const int wg = xcd_chunk(blockIdx.x, gridDim.x);
+  const int chunk = wg % S.nchunk, rest = wg / S.nchunk;
+  const int blk = rest % S.nblk, inst = rest / S.nblk;
+  const int64_t i4 = ((int64_t)blk * 256 + threadIdx.x) * 4;
+  if (i4 >= S.slice) return;
+  const float* in = S.in + (int64_t)inst * S.ni * S.slice + i4;
+  float* out = S.out + (int64_t)inst * S.no * S.slice + i4;
+  const int o = C * chunk, j0 = 2 * o - (L - 2), need = 2 * min(C, S.no - o) + L - 2;
+  float4 w[W];
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    const int j = j0 + i;
+    const bool ok = i < need && (!ZX || (j >= 0 && j < S.ni));
+    w[i] = ok ? gld4(in + (int64_t)(ZX ? j : sym_ix(j, S.ni)) * S.slice) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    if (o + k < S.no) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int t = 0; t < L; ++t) {
+        const float4 x = w[2 * k + t];
+        a.x = fmaf(f.h[t], x.x, a.x); a.y = fmaf(f.h[t], x.y, a.y);
+        a.z = fmaf(f.h[t], x.z, a.z); a.w = fmaf(f.h[t], x.w, a.w);
+      }
+      gst4(out + (int64_t)(o + k) * S.slice, a);
+    }
+  }
+}
+
+hipError_t launch_sym_col(int L, bool zx, const SymCol& S, unsigned grid, const Filter& f, hipStream_t s) {
+  switch (L) {
+#define ES_COL_CASE(LL)                                                                             \
+  case LL:                                                                                          \
+    if (zx) hipLaunchKernelGGL((k_sym_down_col<LL, true>), dim3(grid), dim3(256), 0, s, S, f);      \
+    else hipLaunchKernelGGL((k_sym_down_col<LL, false>), dim3(grid), dim3(256), 0, s, S, f);        \
+    break;
+    ES_COL_CASE(6) ES_COL_CASE(8) ES_COL_CASE(10) ES_COL_CASE(12) ES_COL_CASE(14) ES_COL_CASE(16)
+#undef ES_COL_CASE
+    default: return hipErrorInvalidValue;  // shorter filters keep the 3-D tile
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_sym_shell(int L, const SymShell& S, bool prep, unsigned grid, const Filter& f, hipStream_t s) {
   const bool two = S.D == 2;
   switch (L) {
@@ -889,11 +961,14 @@ bool sym_filter(int L, Filter* f) {
 }
 
 struct SymLaunch {
-  int kind;  // 0 analysis level, 1 synthesis level, 2 fold, 3 boundary shell (transposed operator)
+  int kind;  // 0 analysis level, 1 synthesis level, 2 fold, 3 boundary shell (transposed operator),
+             // 4 axis-0 pass of a split analysis level
   bool zx;   // analysis with zero extension (S_a^T)
+  int D;     // dimensionality of the level kernel (2 on the slices of a split 3-D level)
   SymTask t;
   SymFold fold;
   SymShell shell;
+  SymCol col;
   int64_t grid;
 };
 
@@ -956,6 +1031,21 @@ SymShell sym_shell(const SymGeo& g, int j, int64_t batch, const float* u, float*
   }
   S.batch = (int32_t)std::min<int64_t>(batch, 0x7fffffff);
   return S;
+}
+
+// Floats between the slices' 2-D pass and the axis-0 pass of a split 3-D analysis level i.
+int64_t sym_mid_floats(const SymGeo& g, int i, int64_t batch) {
+  return batch * g.dims[i - 1][0] * (g.stored(i) / g.dims[i][0]);
+}
+
+// 3-D analysis levels that run split (k_sym_down_col).  Measured per level on 32^3 .. 256^3, every
+// filter length: the second launch costs 2-3 us, the halo it saves grows with the taps and the
+// samples.  14 and 16 taps win from 32^3 on (16 taps: 27.6 -> 18.5 us a call at 32^3, 303 -> 108 us at
+// 256^3), 12 taps from ~2^19 samples (96^3: 23.3 -> 18.6 us), 10 from ~2^20, 8 from ~2^21 (128^3 even,
+// 200 x 180 x 190: 47.9 -> 41.6 us), 6 from ~2^22; 2 and 4 taps never do (256^3, 2 taps: 38.8 -> 46.4).
+bool sym_split(const SymGeo& g, int i, int64_t batch) {
+  if (g.D != 3 || g.L < 6) return false;
+  return g.L >= 14 || batch * g.size(i - 1) >= (int64_t)1 << (25 - g.L / 2);
 }
 
 // Scratch floats of the shell of level j (0 where the level has no shell pass).
@@ -1027,9 +1117,45 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
   // weights: w[i] of detail level i (1..m), w[m] = 1 = approximation weight
   std::vector<double> w(g.m + 1, 1.0);
   for (int i = 1; i <= g.m; ++i) w[i] = std::exp2(-2.0 * g.s * (double)(g.m - i));
+  // scratch of a split level: the extended level's array, which is written later, or (forward) y,
+  // which the last launch writes
+  float* mid = transpose ? vext : y;
+  const int64_t mid_cap = g.D < 3 || g.m < 2 ? 0 : transpose ? batch * ext_dims(g, 1).stored() : batch * g.size(0);
   for (int i = 1; i < g.m; ++i) {
+    if (sym_split(g, i, batch) && sym_mid_floats(g, i, batch) <= mid_cap) {
+      SymLaunch l{};
+      l.kind = 0;
+      l.D = 2;
+      l.zx = transpose;
+      l.t.in = lev[i - 1];
+      l.t.out = mid;
+      for (int a = 0; a < 3; ++a) {
+        l.t.ni[a] = a == 0 ? 1 : g.dims[i - 1][a];
+        l.t.no[a] = a == 0 ? 1 : g.dims[i][a];
+      }
+      l.t.si[1] = g.pitch(i - 1);
+      l.t.so[1] = g.pitch(i);
+      l.t.bs_in = (int64_t)l.t.ni[1] * l.t.si[1];
+      l.t.bs_out = (int64_t)l.t.no[1] * l.t.so[1];
+      l.grid = sym_tiling(l.t, sym_tiles(2, g.L).t, batch * g.dims[i - 1][0]);
+      out->push_back(l);
+      SymLaunch c{};
+      c.kind = 4;
+      c.zx = transpose;
+      c.col.in = mid;
+      c.col.out = lev[i];
+      c.col.slice = l.t.bs_out;
+      c.col.ni = g.dims[i - 1][0];
+      c.col.no = g.dims[i][0];
+      c.col.nblk = (int32_t)((c.col.slice / 4 + 255) / 256);
+      c.col.nchunk = (c.col.no + kColChunk - 1) / kColChunk;
+      c.grid = (int64_t)c.col.nblk * c.col.nchunk * batch;
+      out->push_back(c);
+      continue;
+    }
     SymLaunch l{};
     l.kind = 0;
+    l.D = g.D;
     l.zx = transpose;
     l.t.in = lev[i - 1];
     l.t.out = lev[i];
@@ -1053,6 +1179,7 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
       // z_{j-1} = c_{j-1} a_{j-1} + S_a z_j  (y = w_1 x + S_a z_1); z_{m-1} = c_{m-1} a_{m-1}
       SymLaunch l{};
       l.kind = 1;
+      l.D = g.D;
       l.t.in = lev[j];
       l.t.same = lev[j - 1];
       l.t.out = dst;
@@ -1076,6 +1203,7 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
       // [0, n)), then the boundary shell adds beta times the extension images
       SymLaunch l{};
       l.kind = 1;
+      l.D = g.D;
       l.t.in = lev[j];
       l.t.same = lev[j - 1];
       l.t.out = dst;
@@ -1104,6 +1232,7 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
     const ExtDims E = ext_dims(g, j);
     SymLaunch l{};
     l.kind = 1;
+    l.D = g.D;
     l.t.in = lev[j];
     l.t.same = nullptr;
     l.t.out = vext;
@@ -1243,8 +1372,10 @@ es_status sym_run(int ndim, const int64_t* shape, int64_t batch, int order, int 
           he = launch_sym_shell(g.L, S, pass == 0, grid, f, hs);
         }
       }
+    } else if (l.kind == 4) {
+      he = launch_sym_col(g.L, l.zx, l.col, (unsigned)l.grid, f, hs);
     } else {
-      he = launch_sym(g.D, g.L, l.kind == 1, l.zx, l.t, l.grid, f, hs);
+      he = launch_sym(l.D, g.L, l.kind == 1, l.zx, l.t, l.grid, f, hs);
     }
     if (he != hipSuccess) return report_error(ES_EDEVICE, hipGetErrorString(he));
   }
