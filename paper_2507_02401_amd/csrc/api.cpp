@@ -1016,11 +1016,28 @@ es_status run_split(int op, const Geo& g, int64_t batch, int S, const float* in,
   return ES_OK;
 }
 
-es_status run_op(int op, int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s,
-                 const float* in, float* out, void* ws, size_t ws_bytes, void* stream) {
+// One operator call, checked and scheduled: everything of a call but the launches.
+struct CallPlan {
   Geo g;
-  es_status st = make_geo(ndim, shape, order, levels, s, &g);
+  int op = 0;
+  int64_t batch = 0;
+  const float* in = nullptr;
+  float* out = nullptr;
+  float* ws = nullptr;
+  int streams = 1;  // > 1: sub-batch streams (run_split schedules its sub-batches itself)
+  Schedule sc;
+};
+
+es_status plan_call(int op, int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s,
+                    const float* in, float* out, void* ws, size_t ws_bytes, CallPlan* c) {
+  es_status st = make_geo(ndim, shape, order, levels, s, &c->g);
   if (st != ES_OK) return st;
+  const Geo& g = c->g;
+  c->op = op;
+  c->batch = batch;
+  c->in = in;
+  c->out = out;
+  c->ws = (float*)ws;
   const size_t need = (size_t)(batch > 0 ? batch : 0) * (size_t)ws_floats_per_instance(g) * sizeof(float);
   const bool identity = (op >= ES_OP_COV) ? levels <= 1 : levels == 0;
   st = check_io(in, out, batch, g.N(), ws, ws_bytes, identity ? 0 : need);
@@ -1029,16 +1046,26 @@ es_status run_op(int op, int ndim, const int64_t* shape, int64_t batch, int orde
   if (batch > 0x7fffffffll) return fail(ES_EINVAL, "batch too large");
   st = check_device();
   if (st != ES_OK) return st;
-  const int S = identity ? 1 : stream_count(g, batch);
-  if (S > 1) return run_split(op, g, batch, S, in, out, (float*)ws, (hipStream_t)stream);
-  Schedule sc;
-  st = build_schedule(op, g, batch, in, out, (float*)ws, &sc);
+  c->streams = identity ? 1 : stream_count(g, batch);
+  if (c->streams > 1) return ES_OK;
+  st = build_schedule(op, g, batch, in, out, c->ws, &c->sc);
   if (st != ES_OK) return st;
   Region reg[3];
   const int nreg = call_regions(in, out, batch * g.N() * (int64_t)sizeof(float), ws, need, reg);
-  st = check_schedule(sc, reg, nreg);
-  if (st != ES_OK) return st;
-  return run_schedule(sc, g, batch, in, out, (hipStream_t)stream);
+  return check_schedule(c->sc, reg, nreg);
+}
+
+es_status run_call(const CallPlan& c, hipStream_t stream) {
+  if (c.batch == 0) return ES_OK;
+  if (c.streams > 1) return run_split(c.op, c.g, c.batch, c.streams, c.in, c.out, c.ws, stream);
+  return run_schedule(c.sc, c.g, c.batch, c.in, c.out, stream);
+}
+
+es_status run_op(int op, int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s,
+                 const float* in, float* out, void* ws, size_t ws_bytes, void* stream) {
+  CallPlan c;
+  es_status st = plan_call(op, ndim, shape, batch, order, levels, s, in, out, ws, ws_bytes, &c);
+  return st == ES_OK ? run_call(c, (hipStream_t)stream) : st;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2095,6 +2122,20 @@ es_status cov_apply_masked_dot(int ndim, const int64_t* shape, int64_t batch, in
   *per = tpi;
   return ES_OK;
 }
+
+struct CovApply::Impl : CallPlan {};
+
+CovApply::~CovApply() { delete p_; }
+
+es_status CovApply::prepare(int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s, const float* x,
+                            float* y, void* ws, size_t ws_bytes) {
+  delete p_;
+  p_ = new (std::nothrow) Impl();
+  if (!p_) return fail(ES_ENOMEM, "operator schedule allocation failed");
+  return plan_call(ES_OP_COV, ndim, shape, batch, order, levels, s, x, y, ws, ws_bytes, p_);
+}
+
+es_status CovApply::run(hipStream_t stream) const { return run_call(*p_, stream); }
 
 es_status report_error(es_status st, const char* msg) {
   g_last_error = msg;

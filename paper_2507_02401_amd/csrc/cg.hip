@@ -30,7 +30,13 @@ namespace es {
 namespace {
 
 constexpr int kCgThreads = 256;
-constexpr int kCgChunk = 4096;  // elements of one instance per work-group of the element-wise kernels
+// Elements of one instance per work-group of the element-wise kernels.  Instances of up to 2^19
+// elements take one 16-byte access per thread: a single 512^2 image then fills the 256 CUs (64
+// work-groups of 4096 left three quarters idle).  Larger ones fill the chip with either and keep
+// fewer partial sums.  The rule looks at the instance only, so an instance's sums do not depend on
+// the batch.
+constexpr int kCgChunkSmall = 1024, kCgChunkLarge = 4096;
+inline __host__ __device__ int cg_chunk(int64_t n) { return n <= (int64_t)1 << 19 ? kCgChunkSmall : kCgChunkLarge; }
 
 // Per-instance CG scalars (device).
 struct CgScal {
@@ -83,8 +89,8 @@ struct Span {
 DEVI Span span_of(int64_t n, int per) {
   Span sp;
   sp.inst = blockIdx.x / per;
-  sp.lo = (int64_t)(blockIdx.x % per) * kCgChunk;
-  sp.hi = min(n, sp.lo + kCgChunk);
+  sp.lo = (int64_t)(blockIdx.x % per) * cg_chunk(n);
+  sp.hi = min(n, sp.lo + cg_chunk(n));
   return sp;
 }
 
@@ -299,14 +305,17 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_lin3(int64_t n, int per, floa
   }
 }
 
-// Over this work-group's chunk, for j < nv: part[j * nblk + blk] = <v_j, w> and
-// part[(nv + j) * nblk + blk] = <v_j, u> (u = v_{nv-1}, the newest basis vector: the new column of
-// the basis's Gram matrix).  The chunks of w and u are read once, into registers (16-byte loads
-// when the instance size is a multiple of 4); each product is summed within the wave per basis
-// vector and across the four waves, in a fixed order, once at the end.
-constexpr int kGmPer = kCgChunk / kCgThreads;  // elements of a chunk per thread
+// w += alpha v_{nv-1} (the operator's shift: w holds E_s^*(mask^2 v) on entry), then over this
+// work-group's chunk, for j < nv: part[j * nblk + blk] = <v_j, w> and part[(nv + j) * nblk + blk] =
+// <v_j, u> (u = v_{nv-1}, the newest basis vector: the new column of the basis's Gram matrix).  The
+// chunks of w and u are read once, into registers (PER elements per thread, 16-byte loads when the
+// instance size is a multiple of 4), and the next basis vector is in flight while one is summed; each
+// product is summed within the wave per basis vector and across the four waves, in a fixed order,
+// once at the end.  Memory-bound on large instances (the shift in a kernel of its own read and wrote
+// w once more and read v), latency-bound on small ones.
+template <int PER>
 __global__ void __launch_bounds__(kCgThreads) k_gm_dots(int64_t n, int per, int nv, const float* __restrict__ V,
-                                                        int64_t vs, const float* __restrict__ w,
+                                                        int64_t vs, float alpha, float* __restrict__ w,
                                                         float* __restrict__ part) {
   __shared__ float2 wp[kCgThreads / 64][kGmMaxBasis + 1];
   const Span sp = span_of(n, per);
@@ -323,23 +332,31 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_dots(int64_t n, int per, int 
     if (lane == 0) wp[wave][j] = make_float2(x, y);
   };
   if ((n & 3) == 0) {
-    constexpr int G = kGmPer / 4;  // float4 groups per thread
-    float4 wv[G], uv[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const int64_t i = sp.lo + 4 * threadIdx.x + (int64_t)g * 4 * kCgThreads;
-      const bool in = i < sp.hi;
-      wv[g] = in ? gld4(w + base + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-      uv[g] = in ? gld4(u + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    for (int j = 0; j < nv; ++j) {
-      const float* v = V + j * vs + base;
-      float4 xv[G];
+    constexpr int G = PER / 4;  // float4 groups per thread
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int64_t i0 = sp.lo + 4 * threadIdx.x;
+    auto load = [&](const float* v, float4* x) {
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const int64_t i = sp.lo + 4 * threadIdx.x + (int64_t)g * 4 * kCgThreads;
-        xv[g] = i < sp.hi ? gld4(v + i) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const int64_t i = i0 + (int64_t)g * 4 * kCgThreads;
+        x[g] = i < sp.hi ? gld4(v + i) : zero;
       }
+    };
+    float4 wv[G], uv[G], xv[G], nx[G];
+    load(w + base, wv);
+    load(u, uv);
+    load(V + base, nx);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      wv[g] = make_float4(fmaf(alpha, uv[g].x, wv[g].x), fmaf(alpha, uv[g].y, wv[g].y), fmaf(alpha, uv[g].z, wv[g].z),
+                          fmaf(alpha, uv[g].w, wv[g].w));
+      const int64_t i = i0 + (int64_t)g * 4 * kCgThreads;
+      if (i < sp.hi) gst4(w + base + i, wv[g]);
+    }
+    for (int j = 0; j < nv; ++j) {
+#pragma unroll
+      for (int g = 0; g < G; ++g) xv[g] = nx[g];
+      if (j + 1 < nv) load(V + (int64_t)(j + 1) * vs + base, nx);
       KSum aw, au;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -355,18 +372,19 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_dots(int64_t n, int per, int 
       wave_store(j, aw, au);
     }
   } else {
-    float wv[kGmPer], uv[kGmPer];
+    float wv[PER], uv[PER];
 #pragma unroll
-    for (int k = 0; k < kGmPer; ++k) {
+    for (int k = 0; k < PER; ++k) {
       const int64_t i = sp.lo + threadIdx.x + (int64_t)k * kCgThreads;
-      wv[k] = i < sp.hi ? gld(w + base + i) : 0.f;
       uv[k] = i < sp.hi ? gld(u + i) : 0.f;
+      wv[k] = i < sp.hi ? fmaf(alpha, uv[k], gld(w + base + i)) : 0.f;
+      if (i < sp.hi) gst(w + base + i, wv[k]);
     }
     for (int j = 0; j < nv; ++j) {
       const float* v = V + j * vs + base;
       KSum aw, au;
 #pragma unroll
-      for (int k = 0; k < kGmPer; ++k) {
+      for (int k = 0; k < PER; ++k) {
         const int64_t i = sp.lo + threadIdx.x + (int64_t)k * kCgThreads;
         if (i < sp.hi) {
           const float x = gld(v + i);
@@ -388,40 +406,56 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_dots(int64_t n, int per, int 
   }
 }
 
-// Coefficients of step k (one work-group of 64 threads per instance): the new Gram column
-// G[j][k] = G[k][j] = <v_j, v_k> enters the instance's (m+1) x (m+1) Gram matrix, and
-// c = 2 h - G h (j, i <= k) with h = V^T w: the two classical Gram-Schmidt passes of CGS2, the
-// second written through the Gram matrix (exact when the first subtraction is).
-__global__ void __launch_bounds__(64) k_gm_coef(int k, const float* __restrict__ hg, int ldg, float* __restrict__ G,
-                                                int ldG, float* __restrict__ c, int ldc) {
-  const int inst = blockIdx.x, j = threadIdx.x;
-  const float* h = hg + inst * ldg;        // h[0..k], then the Gram column [k+1 .. 2k+1]
-  float* Gi = G + (int64_t)inst * ldG * ldG;
-  if (j <= k) {
-    const float gj = h[k + 1 + j];
-    Gi[j * ldG + k] = gj;
-    Gi[k * ldG + j] = gj;
-  }
-  __syncthreads();
-  if (j <= k) {
-    float acc = 0.f;
-    for (int i = 0; i <= k; ++i) acc = fmaf(Gi[j * ldG + i], h[i], acc);
-    c[inst * ldc + j] = 2.f * h[j] - acc;
-  }
-}
+// Partials are reduced by the kernel that needs the sums where an instance has at most this many
+// (every work-group of the instance repeats the short sum; a launch of its own costs ~4 us), by
+// k_gm_final otherwise.
+constexpr int kGmMaxParts = 256;
 
-// dst[inst * ld + j] = sum of instance inst's `per` partials of vector j, in a fixed order;
-// grid (batch, nv)
+// dst[j * batch + inst] = sum of instance inst's `per` partials of vector j, in a fixed order;
+// grid (batch, vectors)
 __global__ void __launch_bounds__(kCgThreads) k_gm_final(int per, int nblk, const float* __restrict__ part,
-                                                         float* __restrict__ dst, int ld) {
+                                                         float* __restrict__ dst) {
   const int inst = blockIdx.x, j = blockIdx.y;
   KSum acc;
   for (int k = threadIdx.x; k < per; k += kCgThreads) acc.add(part[(int64_t)j * nblk + (int64_t)inst * per + k]);
   const float sum = wg_sum(acc.value());
-  if (threadIdx.x == 0) dst[inst * ld + j] = sum;
+  if (threadIdx.x == 0) dst[(int64_t)j * gridDim.x + inst] = sum;
 }
 
-// w -= sum_j h[inst * ld + j] v_j (j < nv); partial ||w||^2 when part is given
+// Coefficients of step k (one work-group per instance): the sums of the 2 (k + 1) inner products (one
+// wave per vector), the new Gram column G[j][k] = G[k][j] = <v_j, v_k> into the instance's
+// (m+1) x (m+1) Gram matrix, and c = 2 h - G h (j, i <= k) with h = V^T w: the two classical
+// Gram-Schmidt passes of CGS2, the second written through the Gram matrix (exact when the first
+// subtraction is).
+constexpr int kGmCoefThreads = 1024;
+__global__ void __launch_bounds__(kGmCoefThreads) k_gm_coef(int k, int per, int nblk, const float* __restrict__ part,
+                                                            float* __restrict__ G, int ldG, float* __restrict__ c, int ldc) {
+  __shared__ float h[2 * (kGmMaxBasis + 1)];  // h[0..k], then the Gram column [k+1 .. 2k+1]
+  const int inst = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int v = wave; v < 2 * (k + 1); v += kGmCoefThreads / 64) {
+    const float* p = part + (int64_t)v * nblk + (int64_t)inst * per;
+    KSum acc;
+    for (int i = lane; i < per; i += 64) acc.add(p[i]);
+    float x = acc.value();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_down(x, o, 64);
+    if (lane == 0) h[v] = x;
+  }
+  __syncthreads();
+  float* Gi = G + (int64_t)inst * ldG * ldG;
+  const int j = threadIdx.x;
+  if (j <= k) {
+    const float gj = h[k + 1 + j];
+    Gi[j * ldG + k] = gj;
+    Gi[k * ldG + j] = gj;
+    float acc = 0.f;
+    for (int i = 0; i < k; ++i) acc = fmaf(j == k ? h[k + 1 + i] : Gi[j * ldG + i], h[i], acc);
+    acc = fmaf(gj, h[k], acc);
+    c[(int64_t)inst * ldc + j] = 2.f * h[j] - acc;
+  }
+}
+
+// w -= sum_j h[inst * ld + j] v_j (j < nv); partial ||w||^2
 __global__ void __launch_bounds__(kCgThreads) k_gm_sub(int64_t n, int per, int nv, const float* __restrict__ V,
                                                        int64_t vs, const float* __restrict__ h, int ld,
                                                        float* __restrict__ w, float* __restrict__ part) {
@@ -434,8 +468,21 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_sub(int64_t n, int per, int n
   if ((n & 3) == 0) {
     for (int64_t i = sp.lo + 4 * threadIdx.x; i < sp.hi; i += 4 * kCgThreads) {
       float4 o = gld4(w + base + i);
-      for (int j = 0; j < nv; ++j) {
-        const float4 x = gld4(V + j * vs + base + i);
+      const float* v = V + base + i;
+      int j = 0;
+      constexpr int U = 4;  // basis vectors in flight
+      for (; j + U <= nv; j += U) {
+        float4 x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = gld4(v + (j + u) * vs);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float hj = -hs[j + u];
+          o = make_float4(fmaf(hj, x[u].x, o.x), fmaf(hj, x[u].y, o.y), fmaf(hj, x[u].z, o.z), fmaf(hj, x[u].w, o.w));
+        }
+      }
+      for (; j < nv; ++j) {
+        const float4 x = gld4(v + j * vs);
         const float hj = -hs[j];
         o = make_float4(fmaf(hj, x.x, o.x), fmaf(hj, x.y, o.y), fmaf(hj, x.z, o.z), fmaf(hj, x.w, o.w));
       }
@@ -453,36 +500,62 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_sub(int64_t n, int per, int n
       acc.add(o * o);
     }
   }
-  if (part) {
-    const float t = wg_sum(acc.value());
-    if (threadIdx.x == 0) gst(part + blockIdx.x, t);
-  }
+  const float t = wg_sum(acc.value());
+  if (threadIdx.x == 0) gst(part + blockIdx.x, t);
 }
 
-// v = w / sqrt(nrm2[inst]), or 0 when the norm is 0 (an exhausted or zero instance); with a mask,
-// also t = mask^2 v (the next operator application's input)
-__global__ void __launch_bounds__(kCgThreads) k_gm_scale(int64_t n, int per, const float* __restrict__ nrm2,
-                                                         const float* __restrict__ w, float* __restrict__ v,
-                                                         const float* __restrict__ mask, float* __restrict__ t) {
+// x = 0; partial ||b||^2
+__global__ void __launch_bounds__(kCgThreads) k_gm_begin(int64_t n, int per, const float* __restrict__ b,
+                                                         float* __restrict__ x, float* __restrict__ part) {
   const Span sp = span_of(n, per);
-  const float q = nrm2[sp.inst];
+  KSum acc;
+  for_chunk(sp, n, [&](int64_t i, int wdt) {
+    if (wdt == 4) {
+      const float4 v = gld4(b + i);
+      gst4(x + i, make_float4(0.f, 0.f, 0.f, 0.f));
+      acc.add(v.x * v.x);
+      acc.add(v.y * v.y);
+      acc.add(v.z * v.z);
+      acc.add(v.w * v.w);
+    } else {
+      const float v = gld(b + i);
+      gst(x + i, 0.f);
+      acc.add(v * v);
+    }
+  });
+  const float t = wg_sum(acc.value());
+  if (threadIdx.x == 0) gst(part + blockIdx.x, t);
+}
+
+// v = w / ||w||, or 0 when the norm is 0 (an exhausted or zero instance), ||w||^2 the sum of the
+// instance's `nparts` partials, kept in nrm[inst * ld]; and t = mask^2 v (the next operator
+// application's input)
+__global__ void __launch_bounds__(kCgThreads) k_gm_scale(int64_t n, int per, int nparts, const float* __restrict__ part,
+                                                         float* __restrict__ nrm, int ld, const float* __restrict__ w,
+                                                         float* __restrict__ v, const float* __restrict__ mask,
+                                                         float* __restrict__ t) {
+  __shared__ float total;
+  const Span sp = span_of(n, per);
+  KSum acc;
+  for (int k = threadIdx.x; k < nparts; k += kCgThreads) acc.add(part[sp.inst * nparts + k]);
+  const float sum = wg_sum(acc.value());
+  if (threadIdx.x == 0) {
+    total = sum;
+    if (sp.lo == 0) nrm[sp.inst * ld] = sum;
+  }
+  __syncthreads();
+  const float q = total;
   const float sc = q > 0.f ? 1.f / sqrtf(q) : 0.f;
   for_chunk(sp, n, [&](int64_t i, int wdt) {
     if (wdt == 4) {
-      const float4 x = gld4(w + i);
+      const float4 x = gld4(w + i), m = gld4(mask + i);
       const float4 o = make_float4(sc * x.x, sc * x.y, sc * x.z, sc * x.w);
       gst4(v + i, o);
-      if (mask) {
-        const float4 m = gld4(mask + i);
-        gst4(t + i, make_float4(m.x * m.x * o.x, m.y * m.y * o.y, m.z * m.z * o.z, m.w * m.w * o.w));
-      }
+      gst4(t + i, make_float4(m.x * m.x * o.x, m.y * m.y * o.y, m.z * m.z * o.z, m.w * m.w * o.w));
     } else {
-      const float o = sc * gld(w + i);
+      const float o = sc * gld(w + i), m = gld(mask + i);
       gst(v + i, o);
-      if (mask) {
-        const float m = gld(mask + i);
-        gst(t + i, m * m * o);
-      }
+      gst(t + i, m * m * o);
     }
   });
 }
@@ -514,11 +587,11 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_combine(int64_t n, int per, i
   }
 }
 
-int64_t cg_parts(int64_t n) { return (n + kCgChunk - 1) / kCgChunk; }
+int64_t cg_parts(int64_t n) { return (n + cg_chunk(n) - 1) / cg_chunk(n); }
 size_t a256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct GmLayout {
-  size_t V, b, w, t, part, hg, c, G, nrm, y, cov, total;
+  size_t V, b, w, t, part, hg, c, G, y, cov, total;
   int64_t vs;  // floats between basis vectors
 };
 
@@ -533,9 +606,8 @@ GmLayout gm_layout(int64_t n, int64_t batch, int m, size_t cov_bytes, int64_t pe
   L.part = L.t + vec;
   L.hg = L.part + a256((size_t)(2 * (m + 1) * per * batch) * sizeof(float));
   L.c = L.hg + a256((size_t)(batch * 2 * (m + 1)) * sizeof(float));
-  L.G = L.c + a256((size_t)(batch * (m + 1)) * sizeof(float));
-  L.nrm = L.G + a256((size_t)(batch * (m + 1) * (m + 1)) * sizeof(float));
-  L.y = L.nrm + a256((size_t)batch * sizeof(float));
+  L.G = L.c + a256((size_t)((m + 1) * batch * (m + 1)) * sizeof(float));
+  L.y = L.G + a256((size_t)(batch * (m + 1) * (m + 1)) * sizeof(float));
   L.cov = L.y + a256((size_t)(batch * (m + 1)) * sizeof(float));
   L.total = L.cov + cov_bytes;
   return L;
@@ -776,13 +848,15 @@ es_status es_tikhonov_gmres(int ndim, const int64_t* shape, int64_t batch, int o
   float* t = (float*)(wsc + L.t);
   float* part = (float*)(wsc + L.part);
   float* hg = (float*)(wsc + L.hg);
+  // row 0: the cycle's start norm; row k + 1: the column of Arnoldi step k.  A row holds ld = m + 1
+  // floats per instance: the coefficients c_0 .. c_k, and ||w||^2 last
   float* cd = (float*)(wsc + L.c);
   float* Gd = (float*)(wsc + L.G);
-  float* nrm = (float*)(wsc + L.nrm);
   float* yd = (float*)(wsc + L.y);
   void* cws = cov ? (void*)(wsc + L.cov) : nullptr;
   const int64_t vs = L.vs;
   const int ld = m + 1;
+  const int64_t row = batch * ld;
   const hipStream_t hs = (hipStream_t)stream;
   const dim3 grid((unsigned)(per * batch)), blk(kCgThreads);
   const int nblk = (int)(per * batch);
@@ -799,43 +873,55 @@ es_status es_tikhonov_gmres(int ndim, const int64_t* shape, int64_t batch, int o
     snprintf(msg, sizeof msg, "GMRES coefficient read: %s", hipGetErrorString(e));
     return report_error(ES_EDEVICE, msg);
   };
-  // per-instance sums of `nv` partial arrays into dst[inst * ldd + j]
-  auto final_ = [&](int nv, float* dst, int ldd) -> es_status {
-    hipLaunchKernelGGL(k_gm_final, dim3((unsigned)batch, (unsigned)nv), blk, 0, hs, (int)per, nblk, part, dst, ldd);
+  // the partial sums of `nv` vectors, as the next kernel takes them: as they are, or reduced to one
+  struct Parts {
+    const float* p;
+    int per, nblk;
+  };
+  auto reduced = [&](int nv, Parts* out) -> es_status {
+    *out = Parts{part, (int)per, nblk};
+    if (per <= kGmMaxParts) return ES_OK;
+    hipLaunchKernelGGL(k_gm_final, dim3((unsigned)batch, (unsigned)nv), blk, 0, hs, (int)per, nblk, part, hg);
+    *out = Parts{hg, 1, (int)batch};
     return ok("GMRES reduction launch");
   };
-  // out = A v = E_s^*(mask^2 v) + alpha v, or out = b - A v (residual); premasked: t already holds
-  // mask^2 v (written with the basis vector)
-  auto apply_a = [&](const float* v, float* out, bool residual, float* nparts, bool premasked) -> es_status {
-    if (!premasked) hipLaunchKernelGGL(k_gm_mask, grid, blk, 0, hs, n, (int)per, 1, mask, v, t);
-    es_status r = ok("GMRES mask launch");
-    if (r == ES_OK) r = matern_cov_apply(ndim, shape, batch, order, levels, s, t, out, cws, cov, stream);
+  auto normalise = [&](const float* src, float* v, float* norm_row) -> es_status {
+    Parts q;
+    es_status r = reduced(1, &q);
     if (r != ES_OK) return r;
-    if (residual)
-      hipLaunchKernelGGL(k_gm_lin3, grid, blk, 0, hs, n, (int)per, 1.f, (const float*)bv, -1.f, (const float*)out,
-                         (float)-alpha, v, out, nparts);
-    else
-      hipLaunchKernelGGL(k_gm_lin3, grid, blk, 0, hs, n, (int)per, 1.f, (const float*)out, (float)alpha, v,
-                         0.f, (const float*)nullptr, out, nparts);
+    hipLaunchKernelGGL(k_gm_scale, grid, blk, 0, hs, n, (int)per, q.per, q.p, norm_row + m, ld, src, v, mask, t);
+    return ok("GMRES scale launch");
+  };
+  // the operator with its two pairs of arrays, scheduled once
+  CovApply op_b, op_w;
+  if ((st = op_b.prepare(ndim, shape, batch, order, levels, s, t, bv, cws, cov)) != ES_OK) return st;
+  if ((st = op_w.prepare(ndim, shape, batch, order, levels, s, t, w, cws, cov)) != ES_OK) return st;
+  // w = b - A x and its norm's partials
+  auto residual = [&]() -> es_status {
+    hipLaunchKernelGGL(k_gm_mask, grid, blk, 0, hs, n, (int)per, 1, mask, x, t);
+    es_status r = ok("GMRES mask launch");
+    if (r == ES_OK) r = op_w.run(hs);
+    if (r != ES_OK) return r;
+    hipLaunchKernelGGL(k_gm_lin3, grid, blk, 0, hs, n, (int)per, 1.f, (const float*)bv, -1.f, (const float*)w,
+                       (float)-alpha, x, w, part);
     return ok("GMRES update launch");
   };
-  // host copies of the coefficients and the FP64 least-squares state per instance: R (upper
-  // triangle of the rotated Hessenberg matrix, column-major m x m), rotations, right side g,
-  // ||b||, the current residual norm, whether the instance still takes steps, its steps this cycle
-  std::vector<float> hb, hn, yh;
-  std::vector<double> R, cs, sn, g, bn, beta;
+  // host copies of the rows and the FP64 least-squares state per instance: R (upper triangle of the
+  // rotated Hessenberg matrix, column-major m x m), rotations, right side g, ||b||, whether the
+  // instance still takes steps, its steps this cycle
+  std::vector<float> hb, yh, hn;
+  std::vector<double> R, cs, sn, g, bn;
   std::vector<char> active;
   std::vector<int> kk;
   try {
-    hb.resize((size_t)batch * ld);
+    hb.resize((size_t)(row * ld));
+    yh.assign((size_t)row, 0.f);
     hn.resize((size_t)batch);
-    yh.assign((size_t)batch * ld, 0.f);
     R.resize((size_t)batch * m * m);
     cs.resize((size_t)batch * m);
     sn.resize((size_t)batch * m);
-    g.resize((size_t)batch * ld);
-    bn.resize((size_t)batch);
-    beta.resize((size_t)batch);
+    g.resize((size_t)row);
+    bn.assign((size_t)batch, 0.0);
     active.resize((size_t)batch);
     kk.resize((size_t)batch);
   } catch (const std::bad_alloc&) {
@@ -844,80 +930,113 @@ es_status es_tikhonov_gmres(int ndim, const int64_t* shape, int64_t batch, int o
 
   // b = E_s^*(mask p), x = 0, v_0 = b / ||b||
   hipLaunchKernelGGL(k_gm_mask, grid, blk, 0, hs, n, (int)per, 0, mask, p, t);
-  if ((st = ok("GMRES mask launch")) != ES_OK) return st;
-  if ((st = matern_cov_apply(ndim, shape, batch, order, levels, s, t, bv, cws, cov, stream)) != ES_OK) return st;
-  hipLaunchKernelGGL(k_gm_lin3, grid, blk, 0, hs, n, (int)per, 0.f, (const float*)nullptr, 0.f,
-                     (const float*)nullptr, 0.f, (const float*)nullptr, x, (float*)nullptr);
-  hipLaunchKernelGGL(k_gm_lin3, grid, blk, 0, hs, n, (int)per, 1.f, (const float*)bv, 0.f, (const float*)nullptr,
-                     0.f, (const float*)nullptr, w, part);
-  if ((st = ok("GMRES init launch")) != ES_OK || (st = final_(1, nrm, 1)) != ES_OK) return st;
-  hipLaunchKernelGGL(k_gm_scale, grid, blk, 0, hs, n, (int)per, nrm, w, V, mask, t);
-  if ((st = ok("GMRES scale launch")) != ES_OK || (st = to_host(hn.data(), nrm, hn.size() * sizeof(float))) != ES_OK)
-    return st;
+  if ((st = ok("GMRES mask launch")) != ES_OK || (st = op_b.run(hs)) != ES_OK) return st;
+  hipLaunchKernelGGL(k_gm_begin, grid, blk, 0, hs, n, (int)per, (const float*)bv, x, part);
+  if ((st = ok("GMRES init launch")) != ES_OK || (st = normalise(bv, V, cd)) != ES_OK) return st;
 
-  for (int64_t b = 0; b < batch; ++b) {
-    bn[b] = beta[b] = std::sqrt((double)hn[b]);
-    active[b] = bn[b] > 0 && 1.0 > rtol;
-  }
   int it = 0;
   auto any_active = [&]() {
     for (char a : active)
       if (a) return true;
     return false;
   };
-  while (any_active() && it < max_iter) {
+  bool have_bn = false;
+  auto start_norms = [&]() {  // row 0 of hb: the cycle's start norms (the first cycle's: ||b||)
     for (int64_t b = 0; b < batch; ++b) {
+      const double beta = std::sqrt((double)hb[b * ld + m]);
+      if (!have_bn) {
+        bn[b] = beta;
+        active[b] = beta > 0 && 1.0 > rtol;
+      } else if (active[b] && !(beta / bn[b] > rtol)) {
+        active[b] = 0;
+      }
       std::fill(g.begin() + b * ld, g.begin() + (b + 1) * ld, 0.0);
-      g[b * ld] = beta[b];
+      g[b * ld] = beta;
       kk[b] = 0;
     }
-    int K = 0;  // Arnoldi steps of this cycle
-    while (K < m && it < max_iter && any_active()) {
-      const int k = K;
-      const float* vk = V + k * vs;
-      if ((st = apply_a(vk, w, false, nullptr, true)) != ES_OK) return st;
+    have_bn = true;
+  };
+  // Column k of the Hessenberg matrix of every active instance: rotations, residual estimate.
+  auto take_column = [&](int k) {
+    for (int64_t b = 0; b < batch; ++b) {
+      if (!active[b]) continue;
+      const float* hc = hb.data() + (size_t)(k + 1) * row + b * ld;
+      double col[kGmMaxBasis + 1];
+      for (int j = 0; j <= k; ++j) col[j] = (double)hc[j];
+      col[k + 1] = std::sqrt((double)hc[m]);
+      double* c = cs.data() + b * m;
+      double* sv = sn.data() + b * m;
+      for (int i = 0; i < k; ++i) {  // earlier rotations
+        const double u = col[i], v = col[i + 1];
+        col[i] = c[i] * u + sv[i] * v;
+        col[i + 1] = -sv[i] * u + c[i] * v;
+      }
+      const double r = std::hypot(col[k], col[k + 1]);
+      c[k] = r > 0 ? col[k] / r : 1.0;
+      sv[k] = r > 0 ? col[k + 1] / r : 0.0;
+      col[k] = r;
+      double* gb = g.data() + b * ld;
+      gb[k + 1] = -sv[k] * gb[k];
+      gb[k] = c[k] * gb[k];
+      for (int j = 0; j <= k; ++j) R[(size_t)b * m * m + (size_t)k * m + j] = col[j];
+      kk[b] = k + 1;
+      if (!(std::fabs(gb[k + 1]) / bn[b] > rtol) || r == 0) active[b] = 0;
+    }
+  };
+  // Steps are enqueued without waiting; the host reads the columns where the residual may have
+  // reached rtol.  Small problems (a step of ~50 us, a wait of ~25 us): after two steps, then where
+  // the rate of the steps seen so far would reach 80 % of the way; a step past the end changes
+  // nothing but the time.  Problems whose step outweighs the wait: after every step.
+  const bool lag = n * batch <= (int64_t)1 << 22;
+  while (1.0 > rtol && it < max_iter) {
+    const int steps = std::min(m, max_iter - it);
+    int K = 0, read = 0, next = lag ? (rtol > 0 ? std::min(2, steps) : steps) : 1;
+    double seen = 1.0;
+    bool stop = false;
+    for (int k = 0; k < steps && !stop; ++k) {
+      if ((st = op_w.run(hs)) != ES_OK) return st;
       // Gram-Schmidt against v_0 .. v_k: one pass of inner products (with w and with v_k), the
       // CGS2 coefficients from the Gram matrix, one update pass
-      hipLaunchKernelGGL(k_gm_dots, grid, blk, 0, hs, n, (int)per, k + 1, (const float*)V, vs, (const float*)w, part);
-      if ((st = ok("GMRES inner-product launch")) != ES_OK || (st = final_(2 * (k + 1), hg, 2 * ld)) != ES_OK) return st;
-      hipLaunchKernelGGL(k_gm_coef, dim3((unsigned)batch), dim3(64), 0, hs, k, (const float*)hg, 2 * ld, Gd, ld, cd,
-                         ld);
+      if (cg_chunk(n) == kCgChunkSmall)
+        hipLaunchKernelGGL((k_gm_dots<kCgChunkSmall / kCgThreads>), grid, blk, 0, hs, n, (int)per, k + 1, (const float*)V, vs,
+                           (float)alpha, w, part);
+      else
+        hipLaunchKernelGGL((k_gm_dots<kCgChunkLarge / kCgThreads>), grid, blk, 0, hs, n, (int)per, k + 1, (const float*)V, vs,
+                           (float)alpha, w, part);
+      Parts q;
+      if ((st = ok("GMRES inner-product launch")) != ES_OK || (st = reduced(2 * (k + 1), &q)) != ES_OK) return st;
+      float* col = cd + (int64_t)(k + 1) * row;
+      hipLaunchKernelGGL(k_gm_coef, dim3((unsigned)batch), dim3(kGmCoefThreads), 0, hs, k, q.per, q.nblk, q.p, Gd, ld, col, ld);
       if ((st = ok("GMRES coefficient launch")) != ES_OK) return st;
-      hipLaunchKernelGGL(k_gm_sub, grid, blk, 0, hs, n, (int)per, k + 1, (const float*)V, vs, (const float*)cd, ld, w,
-                         part);
-      if ((st = ok("GMRES update launch")) != ES_OK || (st = final_(1, nrm, 1)) != ES_OK) return st;
-      hipLaunchKernelGGL(k_gm_scale, grid, blk, 0, hs, n, (int)per, (const float*)nrm, (const float*)w,
-                         V + (k + 1) * vs, mask, t);
-      if ((st = ok("GMRES scale launch")) != ES_OK) return st;
-      if ((st = to_host(hb.data(), cd, hb.size() * sizeof(float))) != ES_OK ||
-          (st = to_host(hn.data(), nrm, hn.size() * sizeof(float))) != ES_OK)
+      hipLaunchKernelGGL(k_gm_sub, grid, blk, 0, hs, n, (int)per, k + 1, (const float*)V, vs, (const float*)col, ld, w, part);
+      if ((st = ok("GMRES update launch")) != ES_OK || (st = normalise(w, V + (int64_t)(k + 1) * vs, col)) != ES_OK) return st;
+      if (k + 1 < next && k + 1 < steps) continue;
+      // rows not read yet (row 0 with the first ones)
+      const int r0 = read == 0 ? 0 : read + 1;
+      if ((st = to_host(hb.data() + (size_t)r0 * row, cd + (size_t)r0 * row,
+                        (size_t)(k + 2 - r0) * row * sizeof(float))) != ES_OK)
         return st;
-      ++it;
-      ++K;
-      for (int64_t b = 0; b < batch; ++b) {
-        if (!active[b]) continue;
-        double col[kGmMaxBasis + 1];
-        for (int j = 0; j <= k; ++j) col[j] = (double)hb[b * ld + j];
-        col[k + 1] = std::sqrt((double)hn[b]);
-        double* c = cs.data() + b * m;
-        double* sv = sn.data() + b * m;
-        for (int i = 0; i < k; ++i) {  // earlier rotations
-          const double u = col[i], v = col[i + 1];
-          col[i] = c[i] * u + sv[i] * v;
-          col[i + 1] = -sv[i] * u + c[i] * v;
-        }
-        const double r = std::hypot(col[k], col[k + 1]);
-        c[k] = r > 0 ? col[k] / r : 1.0;
-        sv[k] = r > 0 ? col[k + 1] / r : 0.0;
-        col[k] = r;
-        double* gb = g.data() + b * ld;
-        gb[k + 1] = -sv[k] * gb[k];
-        gb[k] = c[k] * gb[k];
-        for (int j = 0; j <= k; ++j) R[(size_t)b * m * m + (size_t)k * m + j] = col[j];
-        kk[b] = k + 1;
-        if (!(std::fabs(gb[k + 1]) / bn[b] > rtol) || r == 0) active[b] = 0;
+      if (read == 0) start_norms();
+      const int from = read;
+      for (; read <= k && any_active(); ++read) {
+        take_column(read);
+        ++it;
+        ++K;
+      }
+      stop = !any_active();
+      if (lag && !stop && rtol > 0) {
+        double rel = 0;
+        for (int64_t b = 0; b < batch; ++b)
+          if (active[b]) rel = std::max(rel, std::fabs(g[b * ld + read]) / bn[b]);
+        const double rate = std::log(rel / seen) / (read - from);  // per step, negative
+        const double need = rate < 0 ? 0.8 * std::log(rtol / rel) / rate : 1;
+        next = k + 1 + (int)std::max(1.0, std::min(need, (double)m));
+        seen = rel;
+      } else {
+        next = lag ? steps : k + 2;
       }
     }
+    if (K == 0) break;
     // x += V y, y = R^{-1} g over each instance's steps of this cycle
     for (int64_t b = 0; b < batch; ++b) {
       const int nk = kk[b];
@@ -940,18 +1059,17 @@ es_status es_tikhonov_gmres(int ndim, const int64_t* shape, int64_t batch, int o
     if ((st = ok("GMRES combine launch")) != ES_OK) return st;
     if (!any_active() || it >= max_iter) break;
     // restart from the true residual r = b - A x: v_0 = r / ||r||
-    if ((st = apply_a(x, w, true, part, false)) != ES_OK || (st = final_(1, nrm, 1)) != ES_OK) return st;
-    hipLaunchKernelGGL(k_gm_scale, grid, blk, 0, hs, n, (int)per, (const float*)nrm, (const float*)w, V, mask, t);
-    if ((st = ok("GMRES scale launch")) != ES_OK || (st = to_host(hn.data(), nrm, hn.size() * sizeof(float))) != ES_OK)
-      return st;
-    for (int64_t b = 0; b < batch; ++b) {
-      beta[b] = std::sqrt((double)hn[b]);
-      if (active[b] && !(beta[b] / bn[b] > rtol)) active[b] = 0;
-    }
+    if ((st = residual()) != ES_OK || (st = normalise(w, V, cd)) != ES_OK) return st;
+  }
+  if (!have_bn) {  // no step taken
+    if ((st = to_host(hb.data(), cd, (size_t)row * sizeof(float))) != ES_OK) return st;
+    start_norms();
   }
   // true relative residual of the final iterate
-  if ((st = apply_a(x, w, true, part, false)) != ES_OK || (st = final_(1, nrm, 1)) != ES_OK) return st;
-  if ((st = to_host(hn.data(), nrm, hn.size() * sizeof(float))) != ES_OK) return st;
+  if ((st = residual()) != ES_OK) return st;
+  hipLaunchKernelGGL(k_gm_final, dim3((unsigned)batch, 1), blk, 0, hs, (int)per, nblk, part, hg);
+  if ((st = ok("GMRES reduction launch")) != ES_OK || (st = to_host(hn.data(), hg, hn.size() * sizeof(float))) != ES_OK)
+    return st;
   for (int64_t b = 0; b < batch; ++b)
     rel_residual[b] = bn[b] > 0 ? (float)(std::sqrt((double)hn[b]) / bn[b]) : 0.f;
   if (iterations) *iterations = it;

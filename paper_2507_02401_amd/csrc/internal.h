@@ -241,6 +241,23 @@ hipError_t launch_sumsq(const float* x, int64_t n, int64_t batch, float* out, hi
 hipError_t launch_lp_up_cge(int taps, int variant, const TaskArgs& args, int grid, const Filter& f,
                             hipStream_t stream);
 
+// matern_cov_apply of one pair of arrays, validated and scheduled once and run any number of times
+// (the solvers apply the operator to the same arrays in every iteration).
+class CovApply {
+ public:
+  CovApply() = default;
+  CovApply(const CovApply&) = delete;
+  CovApply& operator=(const CovApply&) = delete;
+  ~CovApply();
+  es_status prepare(int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s, const float* x,
+                    float* y, void* ws, size_t ws_bytes);
+  es_status run(hipStream_t stream) const;
+
+ private:
+  struct Impl;
+  Impl* p_ = nullptr;
+};
+
 // matern_cov_apply whose last launch is the 2-D vector-path synthesis with the solver epilogue:
 //   y = (scale * w_1 + gamma * mask) x + scale * A^T z_1,
 // and partials[b * per + k] = the k-th work-group's sum of x * y over instance b (per = the
