@@ -38,16 +38,27 @@ constexpr int kCgThreads = 256;
 constexpr int kCgChunkSmall = 1024, kCgChunkLarge = 4096;
 inline __host__ __device__ int cg_chunk(int64_t n) { return n <= (int64_t)1 << 19 ? kCgChunkSmall : kCgChunkLarge; }
 
-// Per-instance CG scalars (device).
+// Per-instance CG scalars (device).  Two copies: an iteration reads one and writes the next
+// iteration's, so that every work-group of a launch may read them.
 struct CgScal {
   float bn;      // ||b||
   float rz;      // r . z
   float a;       // step length of this iteration (0 once converged)
-  float beta;    // direction update of this iteration (0 once converged)
   float rel;     // ||r|| / ||b||
   float active;  // 1 while rel > rtol at the start of the iteration
-  float pad_[2];
+  float pad_[3];
 };
+
+// Partials of a sum over an instance, `n` of them from p[inst * n] on.
+struct Partials {
+  const float* p;
+  int32_t n;
+};
+
+// Partials are summed by the kernel that needs the sum where an instance has at most this many
+// (every work-group of the instance repeats the short sum, four loads a thread; a launch of its own
+// costs ~4 us), by k_cg_reduce first otherwise.
+constexpr int kCgMaxParts = 1024;
 
 // Sum of one value per thread over the work-group, pairwise (fixed order); thread 0 gets it.
 DEVI float wg_sum(float v) {
@@ -174,12 +185,46 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_apply(int64_t n, int per, flo
   if (threadIdx.x == 0) gst(part + blockIdx.x, t);
 }
 
-// r -= a ad; partial r . r  (x += a d waits for the direction pass, which reads d anyway)
-__global__ void __launch_bounds__(kCgThreads) k_cg_step(int64_t n, int per, const CgScal* __restrict__ sc,
+DEVI KSum thread_sum(const Partials& q, int64_t inst) {
+  KSum acc;
+  for (int k = threadIdx.x; k < q.n; k += kCgThreads) acc.add(q.p[inst * q.n + k]);
+  return acc;
+}
+
+// dst[inst] = sum of the instance's partials, in a fixed order
+__global__ void __launch_bounds__(kCgThreads) k_cg_reduce(Partials q, float* __restrict__ dst) {
+  const float sum = wg_sum(thread_sum(q, blockIdx.x).value());
+  if (threadIdx.x == 0) dst[blockIdx.x] = sum;
+}
+
+// First scalars of every instance: rr = ||b||^2, rz = r . z
+__global__ void __launch_bounds__(kCgThreads) k_cg_start(Partials rr, Partials rz, CgScal* __restrict__ sc, float rtol) {
+  const int64_t inst = blockIdx.x;
+  const float2 sum = wg_sum2(thread_sum(rr, inst).value(), thread_sum(rz, inst).value());
+  if (threadIdx.x != 0) return;
+  CgScal c{};
+  c.bn = sqrtf(sum.x);
+  c.rz = sum.y;
+  c.rel = c.bn > 0.f ? 1.f : 0.f;
+  c.active = c.rel > rtol ? 1.f : 0.f;
+  sc[inst] = c;
+}
+
+// a = r.z / d.ad (dad: the partials of d . ad; kept in sc for the direction pass); r -= a ad; partial
+// r . r  (x += a d waits for the direction pass, which reads d anyway)
+__global__ void __launch_bounds__(kCgThreads) k_cg_step(int64_t n, int per, Partials dad, CgScal* __restrict__ sc,
                                                         float* __restrict__ r, const float* __restrict__ ad,
                                                         float* __restrict__ part) {
+  __shared__ float step;
   const Span sp = span_of(n, per);
-  const float a = sc[sp.inst].a;
+  const float sum = wg_sum(thread_sum(dad, sp.inst).value());
+  if (threadIdx.x == 0) {
+    const float rz = sc[sp.inst].rz, act = sc[sp.inst].active;
+    step = (act != 0.f && sum > 0.f) ? rz / sum : 0.f;
+    if (sp.lo == 0) sc[sp.inst].a = step;
+  }
+  __syncthreads();
+  const float a = step;
   KSum acc;
   for_chunk(sp, n, [&](int64_t i, int w) {
     if (w == 4) {
@@ -200,12 +245,27 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_step(int64_t n, int per, cons
   if (threadIdx.x == 0) gst(part + blockIdx.x, t);
 }
 
-// x += a d (this iteration's step), then d = beta d + z
-__global__ void __launch_bounds__(kCgThreads) k_cg_dir(int64_t n, int per, const CgScal* __restrict__ sc,
+// beta = r.z / (r.z of the iteration's start); x += a d (this iteration's step), then d = beta d + z;
+// and the next iteration's scalars (rr, rz: the partials of r . r and r . z of the new residual)
+__global__ void __launch_bounds__(kCgThreads) k_cg_dir(int64_t n, int per, Partials rr, Partials rz,
+                                                       const CgScal* __restrict__ sc, CgScal* __restrict__ next, float rtol,
                                                        float* __restrict__ x, float* __restrict__ d,
                                                        const float* __restrict__ z) {
+  __shared__ float2 ab;
   const Span sp = span_of(n, per);
-  const float a = sc[sp.inst].a, beta = sc[sp.inst].beta;
+  const float2 sum = wg_sum2(thread_sum(rr, sp.inst).value(), thread_sum(rz, sp.inst).value());
+  if (threadIdx.x == 0) {
+    CgScal c = sc[sp.inst];
+    ab = make_float2(c.a, (c.active != 0.f && c.rz > 0.f) ? sum.y / c.rz : 0.f);
+    if (sp.lo == 0) {
+      c.rel = c.bn > 0.f ? sqrtf(sum.x) / c.bn : 0.f;
+      c.rz = sum.y;
+      c.active = c.rel > rtol ? c.active : 0.f;  // converged instances stay frozen
+      next[sp.inst] = c;
+    }
+  }
+  __syncthreads();
+  const float a = ab.x, beta = ab.y;
   for_chunk(sp, n, [&](int64_t i, int w) {
     if (w == 4) {
       const float4 xv = gld4(x + i), dv = gld4(d + i), zv = gld4(z + i);
@@ -218,37 +278,6 @@ __global__ void __launch_bounds__(kCgThreads) k_cg_dir(int64_t n, int per, const
       gst(d + i, fmaf(beta, dv, gld(z + i)));
     }
   });
-}
-
-enum CgFinal { F_INIT = 0, F_RZ0 = 1, F_A = 2, F_RR = 3, F_BETA = 4 };
-
-// One work-group per instance: the sum of its `per` partials, in a fixed order, and the scalar
-// update of step `kind`.
-__global__ void __launch_bounds__(kCgThreads) k_cg_final(int kind, int per, const float* __restrict__ part,
-                                                         CgScal* __restrict__ sc, float rtol) {
-  const int64_t inst = blockIdx.x;
-  KSum acc;
-  for (int k = threadIdx.x; k < per; k += kCgThreads) acc.add(part[inst * per + k]);
-  const float sum = wg_sum(acc.value());
-  if (threadIdx.x != 0) return;
-  CgScal c = sc[inst];
-  switch (kind) {
-    case F_INIT:
-      c.bn = sqrtf(sum);
-      c.rel = c.bn > 0.f ? 1.f : 0.f;
-      c.active = c.rel > rtol ? 1.f : 0.f;
-      c.a = c.beta = 0.f;
-      break;
-    case F_RZ0: c.rz = sum; break;
-    case F_A: c.a = (c.active != 0.f && sum > 0.f) ? c.rz / sum : 0.f; break;
-    case F_RR: c.rel = c.bn > 0.f ? sqrtf(sum) / c.bn : 0.f; break;
-    default:  // F_BETA: sum = r . z of the new residual
-      c.beta = (c.active != 0.f && c.rz > 0.f) ? sum / c.rz : 0.f;
-      c.rz = sum;
-      c.active = c.rel > rtol ? c.active : 0.f;  // converged instances stay frozen
-      break;
-  }
-  sc[inst] = c;
 }
 
 // ---- GMRES on (E_s^* K^* K + alpha I) x = E_s^* K^* p (K = diag(mask)) ----------------------
@@ -615,7 +644,7 @@ GmLayout gm_layout(int64_t n, int64_t batch, int m, size_t cov_bytes, int64_t pe
 
 
 struct CgLayout {
-  size_t r, z, d, ad, part, scal, cov, total;
+  size_t r, z, d, ad, part, prr, scal, cov, total;
 };
 
 CgLayout cg_layout(int64_t n, int64_t batch, size_t cov_bytes, int64_t parts) {
@@ -626,8 +655,9 @@ CgLayout cg_layout(int64_t n, int64_t batch, size_t cov_bytes, int64_t parts) {
   L.d = L.z + vec;
   L.ad = L.d + vec;
   L.part = L.ad + vec;
-  L.scal = L.part + a256((size_t)(parts * batch) * sizeof(float));
-  L.cov = L.scal + a256((size_t)batch * sizeof(CgScal));
+  L.prr = L.part + a256((size_t)((parts + 1) * batch) * sizeof(float));
+  L.scal = L.prr + a256((size_t)((cg_parts(n) + 1) * batch) * sizeof(float));
+  L.cov = L.scal + a256((size_t)batch * 2 * sizeof(CgScal));
   L.total = L.cov + cov_bytes;
   return L;
 }
@@ -696,7 +726,8 @@ es_status es_tikhonov_pcg(int ndim, const int64_t* shape, int64_t batch, int ord
   float* z = (float*)(w + L.z);
   float* d = (float*)(w + L.d);
   float* ad = (float*)(w + L.ad);
-  float* part = (float*)(w + L.part);
+  float* part = (float*)(w + L.part);  // d . ad and r . z, then one reduced value per instance
+  float* prr = (float*)(w + L.prr);    // r . r, likewise
   CgScal* sc = (CgScal*)(w + L.scal);
   void* cws = cov ? (void*)(w + L.cov) : nullptr;
   const hipStream_t hs = (hipStream_t)stream;
@@ -708,9 +739,14 @@ es_status es_tikhonov_pcg(int ndim, const int64_t* shape, int64_t batch, int ord
     snprintf(msg, sizeof msg, "%s: %s", what, hipGetErrorString(e));
     return report_error(ES_EDEVICE, msg);
   };
-  auto final_ = [&](int kind, int64_t nparts) -> es_status {
-    hipLaunchKernelGGL(k_cg_final, dim3((unsigned)batch), blk, 0, hs, kind, (int)nparts, part, sc, frtol);
-    return ok("CG scalar update launch");
+  // partials as the next kernel takes them: as they are, or reduced to one per instance behind them
+  auto reduced = [&](float* p, int64_t nparts, int64_t cap, Partials* q) -> es_status {
+    *q = Partials{p, (int32_t)nparts};
+    if (nparts <= kCgMaxParts) return ES_OK;
+    float* one = p + cap * batch;
+    hipLaunchKernelGGL(k_cg_reduce, dim3((unsigned)batch), blk, 0, hs, *q, one);
+    *q = Partials{one, 1};
+    return ok("CG reduction launch");
   };
   // Fused operator steps (2-D grids whose operator ends in the vector-path synthesis): the last
   // kernel of the operator also forms the mask term and the per-tile inner products, so the
@@ -718,72 +754,73 @@ es_status es_tikhonov_pcg(int ndim, const int64_t* shape, int64_t batch, int ord
   // separate kernels when the schedule does not allow it.
   const char* fz = getenv("ESWAVE_CG_FUSED");  // 0: always the separate kernels (comparison)
   bool fused = cov_dot_partials_max(ndim, shape) > 0 && !(fz && *fz == '0');
-  // out = scale * op(in) + gamma * mask * in, and part = per-tile sums of in * out
-  auto cov_dot = [&](const float* in, float* out, double sm, const float* msk, float scale, int64_t* np) -> es_status {
-    const es_status r = cov_apply_masked_dot(ndim, shape, batch, order, levels, sm, in, out, cws, cov, msk, 1.f, scale,
-                                             part, parts * batch, np, hs);
-    if (r == ES_EUNSUPPORTED) fused = false;
-    return r;
-  };
-  auto cov_apply = [&](const float* in, float* out, double sm) -> es_status {
-    return matern_cov_apply(ndim, shape, batch, order, levels, sm, in, out, cws, cov, stream);
-  };
+  // the operators with their pairs of arrays, scheduled once: z = P r; ad = alpha Gamma^2 d + M d and
+  // z = P r with the inner products
+  CovApply op_z, op_ad, op_zdot;
+  if ((st = op_z.prepare(ndim, shape, batch, order, levels, s, r, z, cws, cov)) != ES_OK) return st;
+  if (fused) {
+    st = op_ad.prepare_dot(ndim, shape, batch, order, levels, -s, d, ad, cws, cov, mask, 1.f, (float)alpha, part,
+                           parts * batch);
+    if (st == ES_OK)
+      st = op_zdot.prepare_dot(ndim, shape, batch, order, levels, s, r, z, cws, cov, nullptr, 1.f, 1.f, part, parts * batch);
+    if (st == ES_EUNSUPPORTED) fused = false;
+    else if (st != ES_OK) return st;
+  }
+  if (!fused && (st = op_ad.prepare(ndim, shape, batch, order, levels, -s, d, ad, cws, cov)) != ES_OK) return st;
 
   // r = b = M p, x = 0, ||b||; z = P r, d = z, rz = r . z
-  hipLaunchKernelGGL(k_cg_init, grid, blk, 0, hs, n, (int)per, p, mask, x, r, part);
-  if ((st = ok("CG init launch")) != ES_OK || (st = final_(F_INIT, per)) != ES_OK) return st;
-  if ((st = cov_apply(r, z, s)) != ES_OK) return st;
+  Partials rr, rz, dad;
+  hipLaunchKernelGGL(k_cg_init, grid, blk, 0, hs, n, (int)per, p, mask, x, r, prr);
+  if ((st = ok("CG init launch")) != ES_OK || (st = reduced(prr, per, per, &rr)) != ES_OK) return st;
+  if ((st = op_z.run(hs)) != ES_OK) return st;
   hipLaunchKernelGGL(k_cg_dot, grid, blk, 0, hs, n, (int)per, r, z, d, part);
-  if ((st = ok("CG dot launch")) != ES_OK || (st = final_(F_RZ0, per)) != ES_OK) return st;
+  if ((st = ok("CG dot launch")) != ES_OK || (st = reduced(part, per, parts, &rz)) != ES_OK) return st;
+  hipLaunchKernelGGL(k_cg_start, dim3((unsigned)batch), blk, 0, hs, rr, rz, sc, frtol);
+  if ((st = ok("CG start launch")) != ES_OK) return st;
 
   std::vector<CgScal> host((size_t)batch);
+  auto read_scalars = [&](int it) -> es_status {
+    hipError_t e = hipMemcpyAsync(host.data(), sc + (it & 1) * batch, host.size() * sizeof(CgScal), hipMemcpyDeviceToHost, hs);
+    if (e == hipSuccess) e = hipStreamSynchronize(hs);
+    if (e == hipSuccess) return ES_OK;
+    snprintf(msg, sizeof msg, "CG residual read: %s", hipGetErrorString(e));
+    return report_error(ES_EDEVICE, msg);
+  };
   int it = 0;
-  bool done = false;
+  bool done = false, read = false;  // read: host holds the scalars of iteration `it`
   while (it < max_iter && !done) {
-    // ad = alpha Gamma^2 d + M d, a = rz / (d . ad)
-    int64_t np = per;
-    st = fused ? cov_dot(d, ad, -s, mask, (float)alpha, &np) : ES_EUNSUPPORTED;
-    if (st == ES_EUNSUPPORTED) {
-      np = per;
-      if ((st = cov_apply(d, ad, -s)) != ES_OK) return st;
+    CgScal* cur = sc + (it & 1) * batch;
+    CgScal* next = sc + ((it + 1) & 1) * batch;
+    // ad = alpha Gamma^2 d + M d, d . ad
+    if ((st = op_ad.run(hs)) != ES_OK) return st;
+    if (!fused) {
       hipLaunchKernelGGL(k_cg_apply, grid, blk, 0, hs, n, (int)per, (float)alpha, mask, d, ad, part);
-      st = ok("CG operator update launch");
+      if ((st = ok("CG operator update launch")) != ES_OK) return st;
     }
-    if (st != ES_OK || (st = final_(F_A, np)) != ES_OK) return st;
-    // r -= a ad, rel = ||r|| / ||b||
-    hipLaunchKernelGGL(k_cg_step, grid, blk, 0, hs, n, (int)per, sc, r, ad, part);
-    if ((st = ok("CG step launch")) != ES_OK || (st = final_(F_RR, per)) != ES_OK) return st;
-    // z = P r, beta = (r . z) / rz, d = z + beta d
-    np = per;
-    st = fused ? cov_dot(r, z, s, nullptr, 1.f, &np) : ES_EUNSUPPORTED;
-    if (st == ES_EUNSUPPORTED) {
-      np = per;
-      if ((st = cov_apply(r, z, s)) != ES_OK) return st;
+    if ((st = reduced(part, fused ? op_ad.parts() : per, parts, &dad)) != ES_OK) return st;
+    // a = rz / (d . ad), r -= a ad, ||r||
+    hipLaunchKernelGGL(k_cg_step, grid, blk, 0, hs, n, (int)per, dad, cur, r, (const float*)ad, prr);
+    if ((st = ok("CG step launch")) != ES_OK || (st = reduced(prr, per, per, &rr)) != ES_OK) return st;
+    // z = P r, r . z
+    if ((st = (fused ? op_zdot : op_z).run(hs)) != ES_OK) return st;
+    if (!fused) {
       hipLaunchKernelGGL(k_cg_dot, grid, blk, 0, hs, n, (int)per, r, z, (float*)nullptr, part);
-      st = ok("CG dot launch");
+      if ((st = ok("CG dot launch")) != ES_OK) return st;
     }
-    if (st != ES_OK || (st = final_(F_BETA, np)) != ES_OK) return st;
-    // x += a d, d = z + beta d
-    hipLaunchKernelGGL(k_cg_dir, grid, blk, 0, hs, n, (int)per, sc, x, d, z);
+    if ((st = reduced(part, fused ? op_zdot.parts() : per, parts, &rz)) != ES_OK) return st;
+    // rel = ||r|| / ||b||, beta = (r . z) / rz, x += a d, d = z + beta d
+    hipLaunchKernelGGL(k_cg_dir, grid, blk, 0, hs, n, (int)per, rr, rz, (const CgScal*)cur, next, frtol, x, d,
+                       (const float*)z);
     if ((st = ok("CG direction launch")) != ES_OK) return st;
     ++it;
-    if (it % check_every == 0 || it == max_iter) {
-      hipError_t e = hipMemcpyAsync(host.data(), sc, host.size() * sizeof(CgScal), hipMemcpyDeviceToHost, hs);
-      if (e == hipSuccess) e = hipStreamSynchronize(hs);
-      if (e != hipSuccess) {
-        snprintf(msg, sizeof msg, "CG residual read: %s", hipGetErrorString(e));
-        return report_error(ES_EDEVICE, msg);
-      }
+    read = it % check_every == 0 || it == max_iter;
+    if (read) {
+      if ((st = read_scalars(it)) != ES_OK) return st;
       done = true;
       for (const CgScal& c : host) done = done && !(c.rel > frtol);
     }
   }
-  hipError_t e = hipMemcpyAsync(host.data(), sc, host.size() * sizeof(CgScal), hipMemcpyDeviceToHost, hs);
-  if (e == hipSuccess) e = hipStreamSynchronize(hs);
-  if (e != hipSuccess) {
-    snprintf(msg, sizeof msg, "CG residual read: %s", hipGetErrorString(e));
-    return report_error(ES_EDEVICE, msg);
-  }
+  if (!read && (st = read_scalars(it)) != ES_OK) return st;
   for (int64_t b = 0; b < batch; ++b) rel_residual[b] = host[(size_t)b].rel;
   if (iterations) *iterations = it;
   return ES_OK;

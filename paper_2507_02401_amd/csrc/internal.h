@@ -251,6 +251,15 @@ class CovApply {
   ~CovApply();
   es_status prepare(int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s, const float* x,
                     float* y, void* ws, size_t ws_bytes);
+  // The operator whose last launch is the 2-D vector-path synthesis with the solver epilogue:
+  //   y = (scale * w_1 + gamma * mask) x + scale * A^T z_1,
+  // and partials[b * parts() + k] = the k-th work-group's sum of x * y over instance b.  Returns
+  // ES_EUNSUPPORTED when the geometry's schedule does not end in such a launch (then run the steps
+  // separately).
+  es_status prepare_dot(int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s, const float* x,
+                        float* y, void* ws, size_t ws_bytes, const float* mask, float gamma, float scale,
+                        float* partials, int64_t partials_cap);
+  int64_t parts() const;
   es_status run(hipStream_t stream) const;
 
  private:
@@ -258,15 +267,7 @@ class CovApply {
   Impl* p_ = nullptr;
 };
 
-// matern_cov_apply whose last launch is the 2-D vector-path synthesis with the solver epilogue:
-//   y = (scale * w_1 + gamma * mask) x + scale * A^T z_1,
-// and partials[b * per + k] = the k-th work-group's sum of x * y over instance b (per = the
-// launch's tiles per instance, written to *per).  Returns ES_EUNSUPPORTED, enqueueing nothing,
-// when the geometry's schedule does not end in such a launch (then run the steps separately).
-es_status cov_apply_masked_dot(int ndim, const int64_t* shape, int64_t batch, int order, int levels, double s,
-                               const float* x, float* y, void* ws, size_t ws_bytes, const float* mask, float gamma,
-                               float scale, float* partials, int64_t partials_cap, int64_t* per, hipStream_t stream);
-// Largest `per` cov_apply_masked_dot can produce for this grid (0 when it never applies).
+// Largest parts() a prepare_dot of this grid can produce (0 when it never applies).
 int64_t cov_dot_partials_max(int ndim, const int64_t* shape);
 
 // Host filter derivation (filters.cpp).
