@@ -168,6 +168,15 @@ bool get_filter(int L, Filter* f) {
 // Detail weight of level i (1..m), FP64.
 double wdet(const Geo& g, double tau, int i) { return std::exp2(-tau * g.s * (double)(g.m - i)); }
 
+// First coarse level of a 2-D block whose remaining levels run as matrix products (lp_coarse_block): the
+// first of at most 32 x 32 samples with a level below it; -1: none.
+int dense_from(int D, const int b[3], int nlev) {
+  if (D != 2) return -1;
+  for (int j = 0; j < nlev; ++j)
+    if ((b[1] >> j) <= kDenseSide && (b[2] >> j) <= kDenseSide) return j;
+  return -1;
+}
+
 int64_t align64(int64_t v) { return (v + 63) & ~(int64_t)63; }
 
 // Schedule mode of persistent plans (set around their schedule builds): every level launch uses
@@ -555,14 +564,17 @@ es_status build_schedule_raw(int op, const Geo& g, int64_t batch, const float* i
       t.batch = (int32_t)batch;
       t.coef[0] = (float)(T == 0 ? w[1] : c[T]);
       for (int j = 1; j <= K; ++j) t.coef[j] = (float)c[T + j];
+      t.dense = dense_from(D, t.b, K);
       l.lds = tail_lds_bytes(3, D, t.b, K);  // selects the kernel's LDS size class
-      // the kernel's LDS layout: pyramid A_0 .. A_K, then the temporaries (2-D: B/2; 3-D: B/2 + B/2)
+      // the kernel's LDS layout: pyramid A_0 .. A_K, then the temporaries (2-D: B/2; 3-D: B/2 + B/2) or, where
+      // larger, the matrix products' two arrays, and those products' matrices and tables
       {
         const int64_t B = g.level_size(T);
         int64_t need = 0;
         for (int j = 0; j <= K; ++j) need += B >> (D * j);
-        need += D == 2 ? B / 2 : (D == 3 ? B : 0);
-        const int64_t cap = B <= kCoarseMaxBlock ? kCoarseMaxBlock / 4 * 9 : kCoarseMaxBlockBig / 4 * 9;
+        const int64_t tmp = D == 2 ? B / 2 : (D == 3 ? B : 0);
+        need += t.dense >= 0 ? dense_extra_floats((int)tmp) : tmp;
+        const int64_t cap = coarse_lds_floats(B <= kCoarseMaxBlock ? kCoarseMaxBlock : kCoarseMaxBlockBig);
         if (B > kCoarseMaxBlockBig || need > cap)
           return fail(ES_EUNSUPPORTED, "coarse block of %lld floats needs %lld floats of LDS", (long long)B, (long long)need);
       }

@@ -84,7 +84,8 @@ struct TailTask {
   //       approximation weight.
   float coef[32];
   int32_t tile_begin;
-  int32_t pad2_;
+  int32_t dense;     // 2-D LP: coarse level from which the block (at most 32 x 32 samples) goes through
+                     // matrix products; -1: none
 };
 
 struct TailArgs {

@@ -427,15 +427,48 @@ DEVI void lp_up_tile(const Task& t, int wg, const Filter& f, LpUpSmem<D, L, U0, 
 // Axes at least L long wrap with one compare; shorter ones use the modulo (periodic folding).
 
 
-template <int L, bool SHORT>
+// Block of B <= CMAX contiguous floats into LDS and back, in 16-byte accesses where the address and
+// the length allow, every load of a thread in flight before its first LDS store; `meanwhile` runs while
+// they are.
+template <int NT, int CMAX, class F>
+DEVI void block_to_lds(const float* in, float* sm, int B, F meanwhile) {
+  if ((((uintptr_t)in & 15) | (B & 3)) == 0) {
+    constexpr int U = (CMAX / 4 + NT - 1) / NT;
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * NT;
+      v[u] = e < B / 4 ? gld4(in + 4 * e) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    meanwhile();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = threadIdx.x + u * NT;
+      if (e < B / 4) reinterpret_cast<float4*>(sm)[e] = v[u];
+    }
+  } else {
+    meanwhile();
+    gather_to_lds<NT, CMAX / NT>(
+        B, [&](int e) { return gld(in + e); }, [&](int e, float v) { sm[e] = v; });
+  }
+}
+template <int NT>
+DEVI void block_from_lds(const float* sm, float* out, int B) {
+  if ((((uintptr_t)out & 15) | (B & 3)) == 0)
+    for (int e = threadIdx.x; e < B / 4; e += NT) gst4(out + 4 * e, reinterpret_cast<const float4*>(sm)[e]);
+  else
+    for (int e = threadIdx.x; e < B; e += NT) gst(out + e, sm[e]);
+}
+
+template <int L, bool SHORT, int NT>
 DEVI void coarse_analysis_w(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f) {
   // sm[src] holds an (n0, n1, n2) block; writes the low half along ax, (.., n_ax/2, ..), to sm[dst]
   const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2);
   const int o0 = ax == 0 ? n0 >> 1 : n0, o1 = ax == 1 ? n1 >> 1 : n1, o2 = ax == 2 ? n2 >> 1 : n2;
+  const int total = o0 * o1 * o2;
   const int l1 = ilog2_or_neg(o1), l2 = ilog2_or_neg(o2);
   const int step = ax == 0 ? n1 * n2 : (ax == 1 ? n2 : 1);
-  const int total = o0 * o1 * o2;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
+  for (int e = threadIdx.x; e < total; e += NT) {
     int c0, c1, c2;
     split3(e, o1, o2, l1, l2, c0, c1, c2);
     const int k = ax == 0 ? c0 : (ax == 1 ? c1 : c2);
@@ -455,18 +488,18 @@ DEVI void coarse_analysis_w(float* sm, int src, int dst, int n0, int n1, int n2,
   }
 }
 
-template <int L, bool SHORT>
+template <int L, bool SHORT, int NT>
 DEVI void coarse_synthesis_w(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f, bool combine,
                              float alpha) {
   // sm[src] holds the low half along ax of an (n0, n1, n2) block; writes the full block to
   // sm[dst] (dst = alpha*dst + value when combine)
   const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), half = n >> 1;
   const int h0 = ax == 0 ? half : n0, h1 = ax == 1 ? half : n1, h2 = ax == 2 ? half : n2;
-  const int step = ax == 0 ? h1 * h2 : (ax == 1 ? h2 : 1);
   const int total = n0 * n1 * n2;
+  const int step = ax == 0 ? h1 * h2 : (ax == 1 ? h2 : 1);
   const int l1 = ilog2_or_neg(n1), l2 = ilog2_or_neg(n2);
   (void)h0;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
+  for (int e = threadIdx.x; e < total; e += NT) {
     int c0, c1, c2;
     split3(e, n1, n2, l1, l2, c0, c1, c2);
     const int p = ax == 0 ? c0 : (ax == 1 ? c1 : c2);
@@ -488,120 +521,363 @@ DEVI void coarse_synthesis_w(float* sm, int src, int dst, int n0, int n1, int n2
   }
 }
 
-// Register-window versions: a thread computes PO consecutive outputs along the filtered axis
-// from one window of inputs (each input read once per window, its wrap resolved once), with
-// the per-output arithmetic of the versions above.  Along the contiguous axis the window is
-// read as 16-byte vectors (start and length multiples of 4, so a vector never straddles the
-// wrap); along the strided axes lanes run along the contiguous axis (conflict-free LDS).
-// Preconditions (checked by the dispatchers): the axis is at least L long (analysis) or its
-// half at least L/2 (synthesis), the outputs per line are a multiple of PO, and for the
-// contiguous axis the block offset is a multiple of 4.
-template <int L>
-DEVI void coarse_analysis_v(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f) {
-  constexpr int PO = 4, WN = 2 * PO + L - 2, W4 = (WN + 3) / 4;
-  const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2);
-  const int o0 = ax == 0 ? n0 >> 1 : n0, o1 = ax == 1 ? n1 >> 1 : n1, o2 = ax == 2 ? n2 >> 1 : n2;
-  // item space: the filtered axis counted in chunks of PO outputs
-  const int p0 = ax == 0 ? o0 / PO : o0, p1 = ax == 1 ? o1 / PO : o1, p2 = ax == 2 ? o2 / PO : o2;
-  const int l1 = ilog2_or_neg(p1), l2 = ilog2_or_neg(p2);
-  const int step = ax == 0 ? n1 * n2 : (ax == 1 ? n2 : 1);
-  const int ostep = ax == 0 ? o1 * o2 : (ax == 1 ? o2 : 1);
-  const int total = p0 * p1 * p2;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    int c0, c1, c2;
-    split3(e, p1, p2, l1, l2, c0, c1, c2);
-    const int k0 = PO * (ax == 0 ? c0 : (ax == 1 ? c1 : c2));
-    const int base = src + (ax == 0 ? 0 : c0 * n1 * n2) + (ax == 1 ? 0 : c1 * n2) + (ax == 2 ? 0 : c2);
+// The passes of a coarse level are bound by issued instructions: a pass of a small level takes as long
+// as one wave's chain of them, a pass of a large level as the ~200 instructions that a task took while its
+// indices were split by shifts or divisions, multiplied by strides and wrapped element by element
+// (1100-4000 cycles a pass, a quarter of them sums).  So items are laid out on powers of two (idle
+// lanes where a count is none), a thread keeps its place along the contiguous direction and steps along
+// the other one, and window offsets are formed once per thread; windows are 16-byte vectors along the
+// contiguous axis and four columns per lane along the strided ones, and the last pass stores to global
+// memory.  Per output the taps are summed in the order of the _w versions.  Together with the matrix
+// products below, between the first and the last instruction of one work-group: 128^2, 8 taps, 5 levels
+// 34800 -> 23200 cycles; 64^2, 16 taps, 4 levels 22600 -> 13900.  As a launch: one 128^2 db4 image 16.2 -> 11.7
+// us, the 64 blocks of 128^2 of a 64 x 1024^2 db8 batch 19.5 -> 17.0, one 128^2 db6 block 15.4 -> 13.0.
+
+DEVI int ceil_log2(int v) { return v <= 1 ? 0 : 32 - __builtin_clz(v - 1); }
+
+// (lines, n) -> (lines, n / 2); n / 2 and the offsets multiples of 4
+template <int L, int NT>
+DEVI void coarse_rows_down(float* sm, int src, int dst, int lines, int n, const Filter& f) {
+  constexpr int PO = 4, W4 = (2 * PO + L - 2 + 3) / 4;
+  const int o = n >> 1, nch = o / PO, lg = ceil_log2(nch);
+  const int ch = threadIdx.x & ((1 << lg) - 1), l0 = threadIdx.x >> lg;
+  if (ch >= nch || l0 >= lines) return;
+  int off[W4];
+#pragma unroll
+  for (int v = 0; v < W4; ++v) {
+    const int i = 2 * PO * ch + 4 * v;
+    off[v] = i >= n ? i - n : i;
+  }
+  const float* in = sm + src + l0 * n;
+  float* out = sm + dst + l0 * o + PO * ch;
+  const int ls = NT >> lg;
+  for (int l = l0; l < lines; l += ls, in += ls * n, out += ls * o) {
     float win[4 * W4];
-    if (ax == 2) {
 #pragma unroll
-      for (int v = 0; v < W4; ++v) {
-        int i = 2 * k0 + 4 * v;
-        i = i >= n ? i - n : i;
-        const float4 x = *reinterpret_cast<const float4*>(sm + base + i);
-        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
-      }
-    } else {
-      const int a0 = base + 2 * k0 * step, a0w = a0 - n * step, wrap = n - 2 * k0;
-#pragma unroll
-      for (int j = 0; j < WN; ++j) win[j] = sm[(j >= wrap ? a0w : a0) + j * step];
+    for (int v = 0; v < W4; ++v) {
+      const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
+      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
     }
-    const int ob = dst + (ax == 0 ? k0 : c0) * o1 * o2 + (ax == 1 ? k0 : c1) * o2 + (ax == 2 ? k0 : c2);
+    float r[PO];
 #pragma unroll
     for (int q = 0; q < PO; ++q) {
-      float acc = 0.f;
+      r[q] = 0.f;
 #pragma unroll
-      for (int t = 0; t < L; ++t) acc = fmaf(f.h[t], win[2 * q + t], acc);
-      sm[ob + q * ostep] = acc;
+      for (int t = 0; t < L; ++t) r[q] = fmaf(f.h[t], win[2 * q + t], r[q]);
+    }
+    *reinterpret_cast<float4*>(out) = make_float4(r[0], r[1], r[2], r[3]);
+  }
+}
+
+// Items of a strided pass: (position along the axis, four columns), the columns padded to a power of two;
+// a thread keeps its columns and steps over positions, then over the outer index.
+struct ColItems {
+  int c, p, ps;  // first column, first position (outer * count + k) and its step
+};
+template <int NT>
+DEVI ColItems col_items(int inner) {
+  const int lc = ceil_log2(inner >> 2);
+  const int c = 4 * (threadIdx.x & ((1 << lc) - 1));
+  return ColItems{c < inner ? c : -1, (int)(threadIdx.x >> lc), NT >> lc};
+}
+DEVI float4 axpy4(float a, const float4& x, const float4& y) {
+  return make_float4(fmaf(a, x.x, y.x), fmaf(a, x.y, y.y), fmaf(a, x.z, y.z), fmaf(a, x.w, y.w));
+}
+
+// (outer, n, inner) -> (outer, n / 2, inner); inner and the offsets multiples of 4
+template <int L, int NT>
+DEVI void coarse_cols_down(float* sm, int src, int dst, int outer, int n, int inner, const Filter& f) {
+  const int o = n >> 1;
+  const ColItems it = col_items<NT>(inner);
+  if (it.c < 0) return;
+  for (int p = it.p; p < outer * o; p += it.ps) {
+    const int q = outer == 1 ? 0 : p / o, k = p - q * o, wrap = n - 2 * k;
+    const float* in = sm + src + (q * n + 2 * k) * inner + it.c;
+    float4 win[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) win[j] = *reinterpret_cast<const float4*>(in + (j >= wrap ? j - n : j) * inner);
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < L; ++j) r = axpy4(f.h[j], win[j], r);
+    *reinterpret_cast<float4*>(sm + dst + p * inner + it.c) = r;
+  }
+}
+
+// (lines, n / 2) -> (lines, n): four half-resolution positions per item; n / 2 and the offsets multiples of
+// 4; combine: dst = alpha dst + value
+template <int L, int NT>
+DEVI void coarse_rows_up(float* sm, int src, int dst, int lines, int n, const Filter& f, bool combine, float alpha) {
+  constexpr int H = L / 2, PO = 4, A = (H - 1 + 3) & ~3, NW = (A + PO) / 4;
+  const int half = n >> 1, nch = half / PO, lg = ceil_log2(nch);
+  const int ch = threadIdx.x & ((1 << lg) - 1), l0 = threadIdx.x >> lg;
+  if (ch >= nch || l0 >= lines) return;
+  int off[NW];
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
+    const int k = PO * ch - A + 4 * v;
+    off[v] = k < 0 ? k + half : k;
+  }
+  const float* in = sm + src + l0 * half;
+  float* out = sm + dst + l0 * n + 2 * PO * ch;
+  const int ls = NT >> lg;
+  for (int l = l0; l < lines; l += ls, in += ls * half, out += ls * n) {
+    float win[A + PO];
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+      const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
+      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
+    }
+    float v[2 * PO];
+#pragma unroll
+    for (int r = 0; r < 2 * PO; ++r) {
+      v[r] = 0.f;
+#pragma unroll
+      for (int j = 0; j < H; ++j) v[r] = fmaf(f.h[2 * j + (r & 1)], win[A + (r >> 1) - j], v[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 2 * PO; r += 4) {
+      float4 s = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+      float4* o = reinterpret_cast<float4*>(out + r);
+      if (combine) s = axpy4(alpha, *o, s);
+      *o = s;
     }
   }
 }
 
-template <int L>
-DEVI void coarse_synthesis_v(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f, bool combine,
-                             float alpha) {
-  // PO = 8 full-res outputs (4 half-res positions q0 .. q0+3) per thread; the window holds the
-  // half-res samples q0 - A .. q0 + 3 with A = L/2 - 1 rounded up to a multiple of 4
-  constexpr int H = L / 2, PO = 8, A = (H - 1 + 3) & ~3, WN = A + 4, W4 = WN / 4;
-  const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), half = n >> 1;
-  const int h1 = ax == 1 ? half : n1, h2 = ax == 2 ? half : n2;
-  const int p0 = ax == 0 ? n0 / PO : n0, p1 = ax == 1 ? n1 / PO : n1, p2 = ax == 2 ? n2 / PO : n2;
-  const int l1 = ilog2_or_neg(p1), l2 = ilog2_or_neg(p2);
-  const int step = ax == 0 ? h1 * h2 : (ax == 1 ? h2 : 1);
-  const int ostep = ax == 0 ? n1 * n2 : (ax == 1 ? n2 : 1);
-  const int total = p0 * p1 * p2;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    int c0, c1, c2;
-    split3(e, p1, p2, l1, l2, c0, c1, c2);
-    const int q0 = (PO / 2) * (ax == 0 ? c0 : (ax == 1 ? c1 : c2));
-    const int base = src + (ax == 0 ? 0 : c0 * h1 * h2) + (ax == 1 ? 0 : c1 * h2) + (ax == 2 ? 0 : c2);
-    float win[WN];
-    if (ax == 2) {
+// (outer, n / 2, inner) -> (outer, n, inner), both outputs of a half-resolution position per item; inner and
+// the offsets multiples of 4; combine as above.  gout (16-byte aligned): the result goes there instead of
+// to dst.
+template <int L, int NT>
+DEVI void coarse_cols_up(float* sm, int src, int dst, int outer, int n, int inner, const Filter& f, bool combine,
+                         float alpha, float* gout) {
+  constexpr int H = L / 2;
+  const int half = n >> 1;
+  const ColItems it = col_items<NT>(inner);
+  if (it.c < 0) return;
+  for (int p = it.p; p < outer * half; p += it.ps) {
+    const int q = outer == 1 ? 0 : p / half, k = p - q * half;
+    const float* in = sm + src + p * inner + it.c;
+    float4 win[H];
 #pragma unroll
-      for (int v = 0; v < W4; ++v) {
-        int k = q0 - A + 4 * v;
-        k = k < 0 ? k + half : k;
-        const float4 x = *reinterpret_cast<const float4*>(sm + base + k);
-        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
-      }
+    for (int j = 0; j < H; ++j) win[j] = *reinterpret_cast<const float4*>(in - (j > k ? j - half : j) * inner);
+    float4 e0 = make_float4(0.f, 0.f, 0.f, 0.f), e1 = e0;
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      e0 = axpy4(f.h[2 * j], win[j], e0);
+      e1 = axpy4(f.h[2 * j + 1], win[j], e1);
+    }
+    const int o = 2 * p * inner + it.c;
+    if (combine) {
+      e0 = axpy4(alpha, *reinterpret_cast<const float4*>(sm + dst + o), e0);
+      e1 = axpy4(alpha, *reinterpret_cast<const float4*>(sm + dst + o + inner), e1);
+    }
+    if (gout) {
+      gst4(gout + o, e0);
+      gst4(gout + o + inner, e1);
     } else {
-      const int a0 = base + (q0 - A) * step, a0w = a0 + half * step;
-#pragma unroll
-      for (int j = 0; j < WN; ++j) win[j] = sm[(q0 - A + j < 0 ? a0w : a0) + j * step];
-    }
-    const int p00 = 2 * q0;
-    const int ob = dst + (ax == 0 ? p00 : c0) * n1 * n2 + (ax == 1 ? p00 : c1) * n2 + (ax == 2 ? p00 : c2);
-#pragma unroll
-    for (int r = 0; r < PO; ++r) {
-      const int par = r & 1, qq = r >> 1;  // output 2 (q0 + qq) + par
-      float acc = 0.f;
-#pragma unroll
-      for (int j = 0; j < H; ++j) acc = fmaf(f.h[2 * j + par], win[A + qq - j], acc);
-      const int o = ob + r * ostep;
-      sm[o] = combine ? fmaf(alpha, sm[o], acc) : acc;
+      *reinterpret_cast<float4*>(sm + dst + o) = e0;
+      *reinterpret_cast<float4*>(sm + dst + o + inner) = e1;
     }
   }
 }
 
-// Uniform dispatch: register-window version where its preconditions hold, else one output per
-// thread with single-wrap or modulo (axis shorter than the filter: periodic folding) indexing.
-template <int L>
+// Uniform dispatch over an (n0, n1, n2) block.  Axes shorter than the filter (halves shorter than L / 2
+// for the synthesis) fold periodically: the _w versions, as where a count or an offset does not divide.
+// One instantiation serves every level: variants of its own for the largest and the smallest levels were
+// up to 20 % faster per pass in a loop of the same launch, but between other launches each variant's
+// first pass waits for its code (~100 cycles per 64 bytes), which cost more than it gave.
+template <int L, int NT>
 DEVI void coarse_analysis(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f) {
-  const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2);
-  if (n >= L && (n >> 1) % 4 == 0 && (ax != 2 || src % 4 == 0)) coarse_analysis_v<L>(sm, src, dst, n0, n1, n2, ax, f);
-  else if (n >= L) coarse_analysis_w<L, false>(sm, src, dst, n0, n1, n2, ax, f);
-  else coarse_analysis_w<L, true>(sm, src, dst, n0, n1, n2, ax, f);
+  const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), o = n >> 1;
+  const int inner = ax == 0 ? n1 * n2 : (ax == 1 ? n2 : 1), outer = ax == 0 ? 1 : (ax == 1 ? n0 : n0 * n1);
+  const bool v4 = ((src | dst) & 3) == 0;
+  if (n < L) return coarse_analysis_w<L, true, NT>(sm, src, dst, n0, n1, n2, ax, f);
+  if (ax == 2) {
+    if (v4 && o % 4 == 0 && o <= 4 * NT) return coarse_rows_down<L, NT>(sm, src, dst, outer, n, f);
+  } else if (v4 && inner % 4 == 0 && ceil_log2(inner / 4) <= ceil_log2(NT)) {
+    return coarse_cols_down<L, NT>(sm, src, dst, outer, n, inner, f);
+  }
+  coarse_analysis_w<L, false, NT>(sm, src, dst, n0, n1, n2, ax, f);
 }
-template <int L>
+// gout: the block's final place in global memory, taken only where *direct says so
+template <int L, int NT>
 DEVI void coarse_synthesis(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f, bool combine,
-                           float alpha) {
-  const int half = (ax == 0 ? n0 : (ax == 1 ? n1 : n2)) >> 1;
-  if (half >= L / 2 && half % 4 == 0 && (ax != 2 || src % 4 == 0))
-    coarse_synthesis_v<L>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
-  else if (half >= L / 2) coarse_synthesis_w<L, false>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
-  else coarse_synthesis_w<L, true>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
+                           float alpha, float* gout = nullptr, bool* direct = nullptr) {
+  const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), half = n >> 1;
+  const int inner = ax == 0 ? n1 * n2 : (ax == 1 ? n2 : 1), outer = ax == 0 ? 1 : (ax == 1 ? n0 : n0 * n1);
+  const bool v4 = ((src | dst) & 3) == 0;
+  if (half < L / 2) return coarse_synthesis_w<L, true, NT>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
+  if (ax == 2) {
+    if (v4 && half % 4 == 0 && half <= 4 * NT) return coarse_rows_up<L, NT>(sm, src, dst, outer, n, f, combine, alpha);
+  } else if (v4 && inner % 4 == 0 && ceil_log2(inner / 4) <= ceil_log2(NT)) {
+    if (direct) *direct = true;
+    return coarse_cols_up<L, NT>(sm, src, dst, outer, n, inner, f, combine, alpha, gout);
+  }
+  coarse_synthesis_w<L, false, NT>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
 }
 
+// ---------------------------------------------------------------------------------------
+// The coarsest levels as matrix products.  A pass of a level of at most 32 x 32 samples is latency
+// (~900 cycles for a handful of sums), and such a block has up to ten of them; but its whole remaining
+// operator is a sum of separable projections,
+//   z = c_0 a + sum_i c_i (U_i U_i^T) a (V_i V_i^T),
+// with U_i^T, V_i^T the i-level low-pass analysis of the two axes (rows: the i-fold composite filter,
+// folded to the axis length, shifted by 2^i).  With the rows of every level stacked into T1 (s1 x n1)
+// and T2 (s2 x n2), s = sum_i n / 2^i < n <= 32, that is four products of at most 32 x 32 x 32 on the matrix
+// cores, one 16 x 16 tile per wave:
+//   P = T1 a,  M = (P T2^T) on the blocks of equal level, times c_i,  Q = M T2,  z = c_0 a + T1^T Q.
+// FP32 products and sums throughout.  A block with an infinity or a NaN goes through the passes
+// instead, so that such values reach exactly the outputs that depend on them.
+// Scratch of the dense levels: P (then Q) and M over the passes' temporaries, then T1, T2 and tables.  Rows
+// of kDenseRow floats: the 16 rows x 4 columns that a wave reads of a left factor hit distinct banks.
+struct DenseLds {
+  int P, M, T1, T2, lev1, lev2, coef, bad;
+};
+DEVI DenseLds dense_lds(int tmp, int tmp_floats, int n1, int n2) {
+  DenseLds d;
+  d.P = tmp;
+  d.M = tmp + kDenseBuf;
+  d.T1 = tmp + max(tmp_floats, 2 * kDenseBuf);
+  d.T2 = n1 == n2 ? d.T1 : d.T1 + kDenseBuf;
+  d.lev1 = d.T1 + 2 * kDenseBuf;
+  d.lev2 = n1 == n2 ? d.lev1 : d.lev1 + kDenseSide;
+  d.coef = d.lev1 + 2 * kDenseSide;
+  d.bad = d.coef + kDenseLevels + 1;
+  return d;
+}
+
+// T1, T2 (one array for a square block; zero outside s x n), the rows' levels (0: no row) and the
+// coefficients c_0 .. c_K of the K levels below the (n1, n2) block; no barrier.  Row r of an axis of length n:
+// its distance u = n - r from the end lies in (n / 2^i, n / 2^(i-1)] for level i, where it is row
+// k = n / 2^(i-1) - u.
+template <int L, int NT>
+DEVI void dense_tables(float* sm, const DenseLds& d, const TailTask* tp, int j0, int n1, int n2, int K) {
+  constexpr int N = kDenseSide * kDenseSide;
+  const int axes = n1 == n2 ? 1 : 2;
+  for (int e = threadIdx.x; e < axes * N; e += NT) {
+    const int ax = e / N, r = e / kDenseSide % kDenseSide, j = e % kDenseSide;
+    const int n = ax ? n2 : n1, u = n - r;
+    int lev = 1;
+#pragma unroll
+    for (int q = 1; q < kDenseLevels; ++q) lev += u <= (n >> q);
+    const bool row = u > 0 && lev <= K;
+    const int i = j - (((n >> (lev - 1)) - u) << lev);
+    const int at = row && j < n ? (n / 2 * kDenseLevels + lev - 1) * kDenseSide + (i < 0 ? i + n : i) : 0;
+    const float v = gld(&kComposite<L>.c[0][0][0] + at);
+    sm[(ax ? d.T2 : d.T1) + r * kDenseRow + j] = row && j < n ? v : 0.f;
+    if (j == 0) reinterpret_cast<int*>(sm)[(ax ? d.lev2 : d.lev1) + r] = row ? lev : 0;
+  }
+  if (threadIdx.x <= (unsigned)K) sm[d.coef + threadIdx.x] = tp->coef[j0 + threadIdx.x];
+  if (threadIdx.x == 0) reinterpret_cast<int*>(sm)[d.bad] = 0;
+}
+
+// Operands and product of a wave's 16 x 16 tile: lane l supplies A(l % 16, 4 s + l / 16) and B(4 s + l / 16,
+// l % 16) of step s, and gets rows 4 (l / 16) + 0 .. 3 of column l % 16.  The inner index runs to `len`
+// rounded up to 16; two chains of products, since one waits for its own sums.
+typedef float mfma_f4 __attribute__((ext_vector_type(4)));
+constexpr int kDenseSteps = kDenseSide / 4;
+struct DenseOp {
+  float x[kDenseSteps];
+};
+DEVI DenseOp dense_get(const float* p, int step) {  // p: the lane's element of step 0
+  DenseOp r;
+#pragma unroll
+  for (int s = 0; s < kDenseSteps; ++s) r.x[s] = p[s * step];
+  return r;
+}
+DEVI mfma_f4 dense_mul(const DenseOp& a, const DenseOp& b, int len) {
+  mfma_f4 u = {0.f, 0.f, 0.f, 0.f}, v = u;
+#pragma unroll
+  for (int s = 0; s < kDenseSteps / 2; s += 2) {
+    u = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[s], b.x[s], u, 0, 0, 0);
+    v = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[s + 1], b.x[s + 1], v, 0, 0, 0);
+  }
+  if (len > 16) {
+#pragma unroll
+    for (int s = kDenseSteps / 2; s < kDenseSteps; s += 2) {
+      u = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[s], b.x[s], u, 0, 0, 0);
+      v = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x[s + 1], b.x[s + 1], v, 0, 0, 0);
+    }
+  }
+  return u + v;
+}
+
+// z over a in place for the (n1, n2) block at sm[ao], K levels below it.  Returns false, with a unchanged,
+// where a holds a value that is not finite.  Ends with a barrier.  T1 and T2 are zero past s x n, a is
+// masked, and P, M and Q are written as whole tiles up to the inner lengths.  What a product takes from
+// the tables and from a is read before the barrier that its other factor waits for.
+template <int NT>
+DEVI bool coarse_dense(float* sm, const DenseLds& d, int ao, int n1, int n2, int K) {
+  constexpr int S = kDenseRow;
+  const int s1 = n1 - (n1 >> K), s2 = n2 - (n2 >> K);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int lo = lane & 15, hi = lane >> 4;
+  const int r0 = 16 * (wave >> 1), c0 = 16 * (wave & 1);  // tile of waves 0 .. 3
+  int* words = reinterpret_cast<int*>(sm);
+  static_assert(NT >= 256, "a tile per wave");
+  const bool mine = wave < 4;
+  const bool tP = mine && r0 < s1 && c0 < n2, tM = mine && r0 < s1 && c0 < s2, tZ = mine && r0 < n1 && c0 < n2;
+  const int col = c0 + lo, row = r0 + 4 * hi;  // this lane's column, its four rows of a product
+  float* const tile = sm + row * S + col;      // and its place in an array of kDenseRow floats a row
+  DenseOp t;                                   // the next product's table factor
+  int lr[4], lc = 0;
+  float w = 0.f, x[4];
+  // P = T1 a (reads past the block stay inside the LDS array, which holds more than 32 rows behind it)
+  if (tP) {
+    DenseOp av = dense_get(sm + ao + hi * n2 + col, 4 * n2);
+    const int rows = (col < n2 ? n1 : 0) - hi;
+    float zero = 0.f;  // NaN once a value is not finite
+#pragma unroll
+    for (int s = 0; s < kDenseSteps; ++s) {
+      av.x[s] = 4 * s < rows ? av.x[s] : 0.f;
+      zero = fmaf(av.x[s], 0.f, zero);
+    }
+    const mfma_f4 v = dense_mul(dense_get(sm + d.T1 + (r0 + lo) * S + hi, 4), av, n1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tile[d.P + q * S] = v[q];
+    if (__any(zero != 0.f) && lane == 0) words[d.bad] = 1;
+  }
+  if (tM) {
+    t = dense_get(sm + d.T2 + col * S + hi, 4);
+    lc = words[d.lev2 + col];
+    w = sm[d.coef + lc];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) lr[q] = words[d.lev1 + row + q];
+  }
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(words[d.bad])) return false;
+  // M = P T2^T on the blocks of equal level, weighted
+  if (tM) {
+    const mfma_f4 v = dense_mul(dense_get(sm + d.P + (r0 + lo) * S + hi, 4), t, n2);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tile[d.M + q * S] = lr[q] == lc && lc > 0 ? w * v[q] : 0.f;
+  }
+  if (tP) t = dense_get(sm + d.T2 + hi * S + col, 4 * S);
+  __syncthreads();
+  // Q = M T2 (over P)
+  if (tP) {
+    const mfma_f4 v = dense_mul(dense_get(sm + d.M + (r0 + lo) * S + hi, 4), t, s2);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tile[d.P + q * S] = v[q];
+  }
+  float* const z = sm + ao + row * n2 + col;
+  if (tZ) {
+    t = dense_get(sm + d.T1 + hi * S + r0 + lo, 4 * S);
+    w = sm[d.coef];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = z[q * n2];
+  }
+  __syncthreads();
+  // z = c_0 a + T1^T Q
+  if (tZ) {
+    const mfma_f4 v = dense_mul(t, dense_get(sm + d.P + hi * S + col, 4 * S), s1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (row + q < n1 && col < n2) z[q * n2] = fmaf(w, x[q], v[q]);
+  }
+  __syncthreads();
+  return true;
+}
 
 // Every coarse level of instance `inst` of tail task `tp` in one work-group of NT threads; `sm`
 // holds coarse_lds_floats(CMAX) floats of LDS (16-byte aligned).
@@ -616,57 +892,71 @@ DEVI void lp_coarse_block(const TailTask* tp, int inst, const Filter& f, float* 
   int tmpA = 0;
   for (int j = 0; j <= K; ++j) tmpA += B >> (D * j);
   const int tmpB = tmpA + (B >> 1);
-  gather_to_lds<NT, CMAX / NT>(
-      B, [&](int e) { return gld(in + e); }, [&](int e, float v) { sm[e] = v; });
+  // levels from Kd on (2-D, at most 32 x 32 samples) as matrix products
+  int Kd = D == 2 && tp->dense >= 0 ? tp->dense : K;
+  const DenseLds dl = dense_lds(tmpA, B >> 1, m1 >> Kd, m2 >> Kd);
+  block_to_lds<NT, CMAX>(in, sm, B, [&] {
+    if (D == 2 && Kd < K) dense_tables<L, NT>(sm, dl, tp, Kd, m1 >> Kd, m2 >> Kd, K - Kd);
+  });
   __syncthreads();
   int off = 0;
-  for (int j = 0; j < K; ++j) {
+  for (int j = 0;; ++j) {
+    if (D == 2 && j == Kd && Kd < K) {
+      if (coarse_dense<NT>(sm, dl, off, m1 >> j, m2 >> j, K - j)) break;
+      Kd = K;
+    }
+    if (j == K) break;
     const int a0 = D >= 3 ? m0 >> j : 1, a1 = D >= 2 ? m1 >> j : 1, a2 = m2 >> j;
     const int nxt = off + a0 * a1 * a2;
     if (D == 1) {
-      coarse_analysis<L>(sm, off, nxt, a0, a1, a2, 2, f);
+      coarse_analysis<L, NT>(sm, off, nxt, a0, a1, a2, 2, f);
     } else if (D == 2) {
-      coarse_analysis<L>(sm, off, tmpA, a0, a1, a2, 2, f);
+      coarse_analysis<L, NT>(sm, off, tmpA, a0, a1, a2, 2, f);
       __syncthreads();
-      coarse_analysis<L>(sm, tmpA, nxt, a0, a1, a2 >> 1, 1, f);
+      coarse_analysis<L, NT>(sm, tmpA, nxt, a0, a1, a2 >> 1, 1, f);
     } else {
-      coarse_analysis<L>(sm, off, tmpA, a0, a1, a2, 2, f);
+      coarse_analysis<L, NT>(sm, off, tmpA, a0, a1, a2, 2, f);
       __syncthreads();
-      coarse_analysis<L>(sm, tmpA, tmpB, a0, a1, a2 >> 1, 1, f);
+      coarse_analysis<L, NT>(sm, tmpA, tmpB, a0, a1, a2 >> 1, 1, f);
       __syncthreads();
-      coarse_analysis<L>(sm, tmpB, nxt, a0, a1 >> 1, a2 >> 1, 0, f);
+      coarse_analysis<L, NT>(sm, tmpB, nxt, a0, a1 >> 1, a2 >> 1, 0, f);
     }
     __syncthreads();
     off = nxt;
   }
-  {
+  if (Kd == K) {
     const int sz = B >> (D * K);
     const float ck = tp->coef[K];
-    for (int e = threadIdx.x; e < sz; e += blockDim.x) sm[off + e] *= ck;
+    for (int e = threadIdx.x; e < sz; e += NT) sm[off + e] *= ck;
+    __syncthreads();
   }
-  __syncthreads();
-  for (int j = K - 1; j >= 0; --j) {
+  // the last synthesis pass (j = 0) writes the result to global memory itself where it can
+  bool stored = false;
+  float* const gout = (((uintptr_t)out) & 15) == 0 ? out : nullptr;
+  for (int j = Kd - 1; j >= 0; --j) {
+    float* const g = j == 0 ? gout : nullptr;
+    bool* const d = g ? &stored : nullptr;
     const int a0 = D >= 3 ? m0 >> j : 1, a1 = D >= 2 ? m1 >> j : 1, a2 = m2 >> j;  // output block
     const int cur = off - a0 * a1 * a2;  // A_j precedes A_{j+1}
     const float alpha = tp->coef[j];
     if (D == 1) {
-      coarse_synthesis<L>(sm, off, cur, a0, a1, a2, 2, f, true, alpha);
+      coarse_synthesis<L, NT>(sm, off, cur, a0, a1, a2, 2, f, true, alpha);
     } else if (D == 2) {
       // contiguous axis first: (a1/2, a2/2) -> (a1/2, a2) in tmpA, then rows -> A_j
-      coarse_synthesis<L>(sm, off, tmpA, a0, a1 >> 1, a2, 2, f, false, 0.f);
+      coarse_synthesis<L, NT>(sm, off, tmpA, a0, a1 >> 1, a2, 2, f, false, 0.f);
       __syncthreads();
-      coarse_synthesis<L>(sm, tmpA, cur, a0, a1, a2, 1, f, true, alpha);
+      coarse_synthesis<L, NT>(sm, tmpA, cur, a0, a1, a2, 1, f, true, alpha, g, d);
     } else {
-      coarse_synthesis<L>(sm, off, tmpA, a0 >> 1, a1 >> 1, a2, 2, f, false, 0.f);
+      coarse_synthesis<L, NT>(sm, off, tmpA, a0 >> 1, a1 >> 1, a2, 2, f, false, 0.f);
       __syncthreads();
-      coarse_synthesis<L>(sm, tmpA, tmpB, a0 >> 1, a1, a2, 1, f, false, 0.f);
+      coarse_synthesis<L, NT>(sm, tmpA, tmpB, a0 >> 1, a1, a2, 1, f, false, 0.f);
       __syncthreads();
-      coarse_synthesis<L>(sm, tmpB, cur, a0, a1, a2, 0, f, true, alpha);
+      coarse_synthesis<L, NT>(sm, tmpB, cur, a0, a1, a2, 0, f, true, alpha, g, d);
     }
     __syncthreads();
     off = cur;
   }
-  for (int e = threadIdx.x; e < B; e += blockDim.x) gst(out + e, sm[e]);
+  if (!stored) block_from_lds<NT>(sm, out, B);
 }
 
 }  // namespace es

@@ -2,6 +2,7 @@
 // instantiated for them) and the host planner (which tiles level blocks with them).
 #pragma once
 
+#include "composite.h"
 #include "internal.h"
 
 namespace es {
@@ -52,8 +53,16 @@ constexpr int kFbCoarseThreads = 1024;  // full-bank coarse kernels
 
 // LDS of a block of at most CMAX floats: the pyramid (< 2B in 1-D, < 4B/3 in 2-D, < 8B/7 in 3-D)
 // plus the temporaries (1-D: none; 2-D: B/2; 3-D: B/2 + B/2, the second synthesis pass writes a
-// half block) stay below 9B/4.
-constexpr int coarse_lds_floats(int cmax) { return cmax / 4 * 9; }
+// half block) stay below 9B/4.  2-D blocks whose coarsest levels run as matrix products (sides of at most
+// kDenseSide) hold two of their arrays over (or past) the temporaries, two more and tables behind.
+constexpr int kDenseRow = kDenseSide + 4;
+constexpr int kDenseBuf = kDenseSide * kDenseRow;
+constexpr int kDenseTables = 2 * kDenseSide + kDenseLevels + 2;
+constexpr int dense_extra_floats(int tmp) { return (tmp > 2 * kDenseBuf ? tmp : 2 * kDenseBuf) + 2 * kDenseBuf + kDenseTables; }
+constexpr int coarse_lds_floats(int cmax) {
+  const int passes = cmax / 4 * 9, dense = (cmax / 3 * 4 + 8 + dense_extra_floats(cmax / 2) + 3) & ~3;
+  return passes > dense ? passes : dense;
+}
 
 inline TileShape tile_shape(int kind, int ndim, int variant, int taps) {
   const Shape3 sh = shape_of(kind, ndim, variant, taps);
