@@ -276,20 +276,6 @@ void set_tiles(Task& t, int kind, const Geo& g, int level, int variant, int64_t 
   t.tile_begin = 0;
 }
 
-double tile_waste(int kind, const Geo& g, int level, int variant) {
-  int b[3];
-  g.level_dims(level - 1, b);
-  const TileShape ts = tile_shape(kind, g.D, variant, g.L);
-  const bool analysis = kind_is_analysis(kind);
-  double covered = 1, needed = 1;
-  for (int k = 3 - g.D; k < 3; ++k) {
-    const int extent = analysis ? b[k] / 2 : b[k];
-    covered *= (double)((extent + ts.t[k] - 1) / ts.t[k]) * ts.t[k];
-    needed *= extent;
-  }
-  return covered / needed;
-}
-
 // Work-group count the tile heuristic assumes; ragged plans set it to their instance count so
 // that a level shared by many instances is tiled for the whole launch, not for one instance.
 thread_local int64_t g_variant_batch = 0;
@@ -310,21 +296,45 @@ int64_t lp_tail_limit(const Geo&) {
   return kCoarseMaxBlockBig;
 }
 
+// Work-groups of a level launch with the given tile variant.
+int64_t level_wgs(int kind, const Geo& g, int level, int variant, int64_t batch) {
+  Task t{};
+  set_tiles(t, kind, g, level, variant, batch);
+  return (int64_t)t.tiles_per_inst * std::max(batch, g_variant_batch);
+}
+
+// Tile variant of a level (the kernel family is chosen by level_launch).  The rule follows what
+// es_autotune picked, launch by launch inside whole calls, on 28 geometries from 7 x 360 x 600 to 64 x
+// 1024^2 and 64^3 to 256^3, 4 to 16 taps (all tiles give the same bits): large tiles win as soon as they
+// make about half a work-group per CU, because the filter halo of a small one is most of its work; only
+// launches below that take the narrow tiles.  Calls with the earlier thresholds (wide or medium tiles
+// from 1024 work-groups on) against these: 16 x 512^2 db6 48.8 -> 42 us, 8 x 1024^2 db8 68 -> 57, 64 x 256^2
+// db2 34 -> 28, 2 x 128^3 db6 es_adjoint 71 -> 44.
 int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
   if (g_mode.persist) return kPVariant;
   const int fv = forced_variant();
   if (fv >= 0) return fv;
-  if (g_variant_batch > batch) batch = g_variant_batch;
-  const double w0 = tile_waste(kind, g, level, 0), w1 = tile_waste(kind, g, level, 1);
-  Task t{};
-  set_tiles(t, kind, g, level, 0, batch);
-  const int64_t wg0 = (int64_t)t.tiles_per_inst * batch;
-  // large levels: wide tiles for analysis, medium tiles for the synthesis kernels (measured
-  // fastest on 64 x 1024^2 db8); small levels: narrow tiles (more work-groups)
-  const int big = (kind == K_LP_UP || kind == K_FB_UP || kind == K_LP_UP_S) ? 2 : 0;
-  if (w0 <= 1.25 && wg0 >= 1024) return big;
-  if (w0 <= w1 && wg0 >= 2048) return big;
-  return 1;
+  auto wgs = [&](int v) { return level_wgs(kind, g, level, v, batch); };
+  if (g.D == 2) {
+    switch (kind) {
+      case K_FB_DOWN: return wgs(2) >= 1024 ? 2 : wgs(0) >= 128 ? 0 : 1;
+      case K_FB_UP: return wgs(0) >= 128 ? 0 : 1;
+      default: return wgs(2) >= 128 ? 2 : 1;  // LP_DOWN, LP_UP and the opt-in kinds
+    }
+  }
+  if (g.D == 3) {
+    switch (kind) {
+      case K_LP_DOWN: return g.L > 8 ? 1 : wgs(0) >= 256 ? 0 : wgs(2) >= 128 ? 2 : 1;
+      case K_LP_DOWN_S: return wgs(2) >= 512 ? 2 : 1;
+      case K_LP_UP: return wgs(0) >= 512 ? 0 : wgs(2) >= 256 ? 2 : 1;
+      case K_LP_UP_S: return wgs(0) >= 512 ? 0 : 1;
+      case K_FB_DOWN: return wgs(2) >= 64 ? 2 : 1;
+      case K_FB_DOWN_S: return 1;
+      case K_FB_UP: return wgs(0) >= 1024 ? 0 : 1;
+      default: return wgs(0) >= 256 ? 0 : 1;  // FB_UP_S
+    }
+  }
+  return wgs(0) >= 1024 ? (kind == K_LP_UP || kind == K_FB_UP ? 2 : 0) : 1;
 }
 
 // Row-alignment condition of the vector staging path for one launch.
@@ -348,8 +358,7 @@ void strides_of(const int dims[3], int32_t st[2]) {
 
 // 3-D levels (full-bank and low-pass) and 2-D low-pass analysis levels have two kernel families:
 // plain tiles, and tiles streamed along the slowest axis (no halo re-reads along it, but one
-// work-group walks its run in sequence).  Streaming wins when the level has enough tiles to fill
-// the chip.
+// work-group walks its run in sequence).
 bool has_family(int kind, int D) {
   return (D == 3 && (kind == K_FB_DOWN || kind == K_FB_UP || kind == K_FB_DOWN_S || kind == K_FB_UP_S ||
                      kind == K_LP_DOWN || kind == K_LP_DOWN_S || kind == K_LP_UP || kind == K_LP_UP_S)) ||
@@ -367,14 +376,24 @@ int tiled_kind(int kind) {
   return kind_is_analysis(kind) ? K_FB_DOWN : K_FB_UP;
 }
 
+// Whether a level with two families streams: 3-D levels that then still have a work-group or two per CU,
+// except the low-pass synthesis of up to 10 taps, whose wide plain tile is as fast (256^3 db4: 94 -> 82 us
+// a call); 2-D levels take the plain 16 x 64 tile at every size (64 x 1024^2 db8: 254 -> 241 us a call).
+bool streams(int kind, const Geo& g, int level, int64_t batch) {
+  if (g.D != 3) return false;
+  const int sk = streamed_kind(kind);
+  switch (sk) {
+    case K_LP_UP_S: return g.L >= 12 && level_wgs(sk, g, level, 0, batch) >= 512;
+    case K_FB_UP_S: return level_wgs(sk, g, level, 1, batch) >= (g.L >= 12 ? 128 : 256);
+    case K_LP_DOWN_S: return g.L <= 8 ? level_wgs(sk, g, level, 2, batch) >= 512 : level_wgs(sk, g, level, 1, batch) >= 256;
+    default: return level_wgs(sk, g, level, 1, batch) >= 256;  // FB_DOWN_S
+  }
+}
+
 Launch level_launch(int kind, const Geo& g, int level, int64_t batch) {
   const int mode = streamed_mode();
-  if (has_family(kind, g.D) && mode != 0 && !g_mode.persist) {
-    const int sk = streamed_kind(kind);
-    Task t{};
-    set_tiles(t, sk, g, level, pick_variant(sk, g, level, batch), batch);
-    if (mode == 2 || (int64_t)t.tiles_per_inst * std::max<int64_t>(batch, g_variant_batch) >= 1024) kind = sk;
-  }
+  if (has_family(kind, g.D) && mode != 0 && !g_mode.persist && (mode == 2 || streams(kind, g, level, batch)))
+    kind = streamed_kind(kind);
   Launch l{};
   l.is_tail = 0;
   l.kind = kind;
