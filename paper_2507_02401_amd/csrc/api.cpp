@@ -276,9 +276,10 @@ void set_tiles(Task& t, int kind, const Geo& g, int level, int variant, int64_t 
   t.tile_begin = 0;
 }
 
-// Work-group count the tile heuristic assumes; ragged plans set it to their instance count so
-// that a level shared by many instances is tiled for the whole launch, not for one instance.
-thread_local int64_t g_variant_batch = 0;
+// Instances the tile heuristic counts for one: ragged plans set it to the voxels of all instances that share
+// the launch over those of this instance, so that a level is tiled for the whole launch and every member
+// takes the same tiles.
+thread_local double g_variant_share = 0;
 
 // Largest block the low-pass coarse kernel takes: the large LDS class (an instance that fits it
 // as a whole runs entirely in one work-group, in one launch).  Measured against handing over at
@@ -300,7 +301,7 @@ int64_t lp_tail_limit(const Geo&) {
 int64_t level_wgs(int kind, const Geo& g, int level, int variant, int64_t batch) {
   Task t{};
   set_tiles(t, kind, g, level, variant, batch);
-  return (int64_t)t.tiles_per_inst * std::max(batch, g_variant_batch);
+  return (int64_t)((double)t.tiles_per_inst * std::max((double)batch, g_variant_share));
 }
 
 // Tile variant of a level (the kernel family is chosen by level_launch).  The rule follows what
@@ -1225,6 +1226,7 @@ struct es_plan {
   int op = 0;
   int device = 0;
   std::vector<Geo> geos;
+  std::map<std::pair<int, int>, int64_t> class_voxels;  // (D, L) -> voxels of its instances
   std::vector<int64_t> ws_off;
   std::vector<int64_t> ws_len;  // floats of each instance's workspace slice
   int64_t ws_total = 0;
@@ -1285,10 +1287,10 @@ constexpr uintptr_t kSentinelSpan = (uintptr_t)1 << 44;
 
 es_status instance_schedule_frozen(const es_plan* p, int k, Schedule* sc) {
   const Geo& g = p->geos[k];
-  g_variant_batch = (int64_t)p->geos.size();
+  g_variant_share = (double)p->class_voxels.at({g.D, g.L}) / (double)g.N();
   const es_status st = build_schedule(p->op, g, 1, (const float*)kSentinelIn, (float*)kSentinelOut,
                                       (float*)kSentinelWs + p->ws_off[k], sc);
-  g_variant_batch = 0;
+  g_variant_share = 0;
   return st;
 }
 
@@ -1402,10 +1404,12 @@ es_status plan_launch_all(es_plan* p, hipStream_t s) {
   return ES_OK;
 }
 
-// Graph capture with concurrent groups: the groups of one phase touch disjoint instances, so they
-// are forked onto `nside` side streams (joined back before the next phase); the captured graph
-// then holds them as parallel branches and the device overlaps their launches.  Events are
-// created here and destroyed by the caller after the capture ends.
+// Graph capture with concurrent chains: instances of one dimensionality and filter length share their
+// launches and no others, so the groups of such a class are a chain that no other chain waits for.  The
+// chains are dealt to the stream and `nside` side streams, longest first to the least loaded, forked once
+// at the start and joined once at the end.  Joining the branches after every phase instead cost more
+// than the overlap gained (see es_plan_execute).  Events are created here and destroyed by the caller
+// after the capture ends.
 es_status plan_launch_all_forked(es_plan* p, hipStream_t s, hipStream_t* side, int nside,
                                  std::vector<hipEvent_t>* events) {
   auto new_event = [&](hipEvent_t* e) -> es_status {
@@ -1413,37 +1417,41 @@ es_status plan_launch_all_forked(es_plan* p, hipStream_t s, hipStream_t* side, i
     events->push_back(*e);
     return ES_OK;
   };
-  const size_t n = p->groups.size();
-  for (size_t g = 0; g < n;) {
-    size_t e = g;
-    while (e < n && p->groups[e].phase == p->groups[g].phase) ++e;
-    const int width = (int)std::min<size_t>(e - g, (size_t)nside + 1);
-    if (width == 1) {
-      for (size_t q = g; q < e; ++q) {
-        es_status st = plan_launch_group(p, p->groups[q], s);
-        if (st != ES_OK) return st;
-      }
-      g = e;
-      continue;
-    }
-    hipEvent_t fork;
+  // cost of a chain in voxels: a launch that is too small to fill the chip takes as long as some 2^20 voxels
+  std::map<std::pair<int, int>, std::pair<int64_t, int>> chains;  // (D, L) -> (cost, branch)
+  for (const PlanGroup& gr : p->groups) chains[{gr.proto.D, gr.proto.L}].first += 1 << 20;
+  for (const Geo& g : p->geos) {
+    auto it = chains.find({g.D, g.L});
+    if (it != chains.end()) it->second.first += g.N();
+  }
+  std::vector<std::pair<int64_t, std::pair<int, int>>> order;
+  for (const auto& c : chains) order.push_back({-c.second.first, c.first});
+  std::sort(order.begin(), order.end());
+  const int width = (int)std::min<size_t>(order.size(), (size_t)nside + 1);
+  std::vector<int64_t> load(width, 0);
+  for (const auto& o : order) {
+    const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    load[k] -= o.first;
+    chains[o.second].second = k;
+  }
+  hipEvent_t fork;
+  if (width > 1) {
     es_status st = new_event(&fork);
     if (st != ES_OK) return st;
     ES_HIP(hipEventRecord(fork, s), "hipEventRecord");
     for (int k = 1; k < width; ++k) ES_HIP(hipStreamWaitEvent(side[k - 1], fork, 0), "hipStreamWaitEvent");
-    for (size_t q = g; q < e; ++q) {
-      const int k = (int)((q - g) % width);
-      st = plan_launch_group(p, p->groups[q], k == 0 ? s : side[k - 1]);
-      if (st != ES_OK) return st;
-    }
-    for (int k = 1; k < width; ++k) {
-      hipEvent_t join;
-      st = new_event(&join);
-      if (st != ES_OK) return st;
-      ES_HIP(hipEventRecord(join, side[k - 1]), "hipEventRecord");
-      ES_HIP(hipStreamWaitEvent(s, join, 0), "hipStreamWaitEvent");
-    }
-    g = e;
+  }
+  for (const PlanGroup& gr : p->groups) {
+    const int k = chains[{gr.proto.D, gr.proto.L}].second;
+    es_status st = plan_launch_group(p, gr, k == 0 ? s : side[k - 1]);
+    if (st != ES_OK) return st;
+  }
+  for (int k = 1; k < width; ++k) {
+    hipEvent_t join;
+    es_status st = new_event(&join);
+    if (st != ES_OK) return st;
+    ES_HIP(hipEventRecord(join, side[k - 1]), "hipEventRecord");
+    ES_HIP(hipStreamWaitEvent(s, join, 0), "hipStreamWaitEvent");
   }
   return ES_OK;
 }
@@ -1698,6 +1706,7 @@ es_status plan_build(const es_desc* descs, int32_t count, int op, es_plan** out,
     const es_desc& d = descs[k];
     st = make_geo(d.ndim, d.shape, d.order, d.levels, d.s, &p->geos[k]);
     if (st != ES_OK) { delete p; return fail(st, "desc %d: %s", k, g_last_error.c_str()); }
+    p->class_voxels[{p->geos[k].D, p->geos[k].L}] += p->geos[k].N();
   }
   plan_layout(p, persistent_wanted(op));
   // freeze every instance schedule: for persistent execution when every level launch can take
@@ -2449,9 +2458,12 @@ es_status es_plan_execute(es_plan* p, const float* const* in, float* const* out,
   if (!p->exec) {
     // kernels read everything through the device tables, so the captured graph stays valid
     // when the caller's pointers change (only the tables are refreshed, above)
-    // groups of a phase run as parallel branches, ESWAVE_PLAN_BRANCHES of them at most
-    // (default: 4, or 1 -- one chain -- for plans under 2^22 voxels, where the cross-queue
-    // synchronisation of the branches costs more than their overlap gains)
+    // the chains of the instance classes run as parallel branches, ESWAVE_PLAN_BRANCHES of them at most
+    // (default: 2, or 1 -- one chain -- for plans under 2^22 voxels).  48 instances of 23 M voxels, same /
+    // new buffers on each call, us: 1 branch 318 / 320, 2 branches 236-257 / 295-305, 3 261-277 / 290-300,
+    // 4 245-270 / 335-360; 36 instances of 13.6 M voxels: 251 / 253, 202 / 250, 210 / 255, 208 / 277.
+    // Submitting a branched graph costs the host 3.5 us a launch against 1.5 us for one chain.  Joining 4
+    // branches after every phase: 285-440, differing from process to process.
     constexpr int kSide = 15;
     constexpr int64_t kBranchMinVoxels = 1 << 22;
     hipStream_t cap = nullptr, side[kSide] = {};
@@ -2459,7 +2471,7 @@ es_status es_plan_execute(es_plan* p, const float* const* in, float* const* out,
     const char* br = getenv("ESWAVE_PLAN_BRANCHES");
     int64_t voxels = 0;
     for (const Geo& g : p->geos) voxels += g.N();
-    const int def_br = voxels < kBranchMinVoxels ? 1 : 4;
+    const int def_br = voxels < kBranchMinVoxels ? 1 : 2;
     int nside = std::max(0, std::min(kSide, (br && *br ? atoi(br) : def_br) - 1));
     if (p->persistent) nside = std::min(kSide, (int)p->pgroups.size() - 1);  // one branch per launch
     hipError_t e = hipSuccess;
