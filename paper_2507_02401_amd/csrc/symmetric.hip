@@ -235,8 +235,19 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
 // Output tile (U0, U1, U2) (even) of one synthesis level; z window J_k = U_k/2 + L/2 - 1 starting
 // at U_k c_k / 2: output i = U_k c_k + 2q + e reads z[U_k c_k/2 + q + L/2 - 1 - j] with tap
 // h[2j + e], j < L/2 (the index i + L - 2 - 2k of the left inverse).
-template <int D, int L, int U0, int U1, int U2, int NT>
+//
+// TR (1-D and 2-D grids, every axis of at least L - 1 samples): the transposed level's A^T z, the
+// synthesis on the extension folded onto [0, n).  Per axis an output j adds the synthesis at its images
+// -1 - j (j < L - 2) and 2n - 1 - j (j >= 2n - 2l) to that at j.  The last tile of an axis ends at n (its first
+// output moves down to a multiple of 4, axis 1: of 2, but not below L - 2; the tile before it keeps the
+// outputs up to there), so that the coefficients
+// which the images of an edge tile's outputs read, z[0 .. L/2 - 2] and z[n/2 .. l - 1], all lie in that
+// tile's window: the row pass adds the column images from the staged window, the column pass the row images
+// from the row pass's results.  As two launches after the forward level (the terms to scratch, then onto
+// the output) the images took 126 us of a transposed call on 64 x 1024^2, 16 taps; here they take 22.
+template <int D, int L, int U0, int U1, int U2, int NT, bool TR>
 __global__ void __launch_bounds__(NT) k_sym_up(SymTask t, Filter f) {
+  static_assert(!TR || D <= 2, "the 3-D transposed level is an extended synthesis and a fold");
   constexpr int H = L / 2;
   constexpr int J0 = D >= 3 ? U0 / 2 + H - 1 : 1;
   constexpr int J1 = D >= 2 ? U1 / 2 + H - 1 : 1;
@@ -265,24 +276,38 @@ __global__ void __launch_bounds__(NT) k_sym_up(SymTask t, Filter f) {
   float* out = t.out + inst * t.bs_out;
   const int l0 = t.ni[0], l1 = t.ni[1], l2 = t.ni[2];
   const int m0 = t.no[0], m1 = t.no[1], m2 = t.no[2];
-  const int o0 = U0 * c0, o1 = U1 * c1, o2 = U2 * c2;  // first output of the tile on each axis
+  // outputs [o, q) of the tile on each axis
+  const int o0 = U0 * c0;
+  int o1 = U1 * c1, o2 = U2 * c2, q1 = min(o1 + U1, m1), q2 = min(o2 + U2, m2);
+  if constexpr (TR) {
+    // past the outputs with an image before the start, which are the first tile's
+    const int last1 = m1 > U1 ? max((m1 - U1 + 1) & ~1, L - 2) : 0;
+    const int last2 = m2 > U2 ? max((m2 - U2 + 3) & ~3, L & ~3) : 0;
+    if constexpr (D == 2) {
+      o1 = min(o1, last1);
+      q1 = o1 == last1 ? m1 : min(q1, last1);
+    }
+    o2 = min(o2, last2);
+    q2 = o2 == last2 ? m2 : min(q2, last2);
+  }
   const int zs = t.zshift;
   const int r0 = o0 / 2 - zs, r1 = o1 / 2 - zs, r2 = o2 / 2 - zs;  // first z sample of the window
 
-  // 2-D tiles whose columns lie inside a row length divisible by 4: the last pass gives each lane
-  // four adjacent columns of one output row pair (16-byte LDS reads, loads and stores), and the
-  // lane's `same` values are loaded first so that their latency overlaps the staging of z
+  // 2-D arrays whose rows start at multiples of 4 floats: the last pass gives each lane four adjacent
+  // columns of one output row pair (16-byte LDS reads, loads and stores; a group that ends past the row
+  // takes the row's padding with it), and the lane's `same` values are loaded first so that their latency
+  // overlaps the staging of z
   constexpr int C4 = U2 / 4, NT2 = C4 * (U1 / 2);
   const int so0 = t.so[0], so1 = t.so[1];
-  const bool fast = D == 2 && ((so1 | t.bs_out | t.bs_same) & 3) == 0 && o2 + U2 <= m2;
+  const bool fast = D == 2 && ((so1 | t.bs_out | t.bs_same) & 3) == 0;
   float4 xs0 = make_float4(0.f, 0.f, 0.f, 0.f), xs1 = xs0;
   if constexpr (D == 2) {
     static_assert(NT2 <= NT, "one task per lane");
     if (fast && has_same && threadIdx.x < NT2) {
       const int c4 = threadIdx.x % C4, ch = threadIdx.x / C4;
       const int g1 = o1 + 2 * ch, g2 = o2 + 4 * c4;
-      if (g1 < m1) xs0 = gld4(same + g1 * so1 + g2);
-      if (g1 + 1 < m1) xs1 = gld4(same + (g1 + 1) * so1 + g2);
+      if (g1 < q1 && g2 < q2) xs0 = gld4(same + g1 * so1 + g2);
+      if (g1 + 1 < q1 && g2 < q2) xs1 = gld4(same + (g1 + 1) * so1 + g2);
     }
   }
 
@@ -314,11 +339,41 @@ __global__ void __launch_bounds__(NT) k_sym_up(SymTask t, Filter f) {
       });
   __syncthreads();
 
+  // Images of the output pair (j, j + 1), j even: both read z[k], k = kb + i, i < H, with taps
+  // h[L - 1 - 2i] and h[L - 2 - 2i], where kb = -1 - j/2 before the start and n - 1 - j/2 past the end;
+  // a k outside [0, l) adds nothing.
+  auto images = [&](int kb, int l, auto&& read, auto&& add) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int kk = kb + i;
+      if (kk >= 0 && kk < l) add(f.h[L - 1 - 2 * i], f.h[L - 2 - 2 * i], read(kk));
+    }
+  };
+  if constexpr (TR) {
+    auto columns = [&](int first, int pairs, int kb0) {  // output columns first, first + 2, ...
+      for (int q = threadIdx.x; q < J1 * pairs; q += NT) {
+        const int row = q / pairs, c = q - row * pairs;
+        float e0 = 0.f, e1 = 0.f;
+        images(kb0 - c, l2, [&](int kk) { return s_z[row * J2P + kk - r2]; },
+               [&](float ho, float he, float z) { e0 = fmaf(ho, z, e0); e1 = fmaf(he, z, e1); });
+        float* a = s_a + row * U2P + first - o2 + 2 * c;
+        a[0] += e0;
+        a[1] += e1;
+      }
+      __syncthreads();
+    };
+    if (H > 1 && o2 == 0) columns(0, min(H - 1, U2 / 2), -1);
+    if (q2 == m2) {
+      const int first = 2 * (m2 - l2);  // first even column with an image past the end
+      columns(first, (m2 - first + 1) / 2, l2 - 1);
+    }
+  }
+
   const float alpha = t.alpha, beta = t.beta;
   if constexpr (D == 1) {
     for (int p = threadIdx.x; p < U2; p += NT) {
       const int g2 = o2 + p;
-      if (g2 < m2) gst(out + g2, fmaf(alpha, has_same ? gld(same + g2) : 0.f, beta * s_a[p]));
+      if (g2 < q2) gst(out + g2, fmaf(alpha, has_same ? gld(same + g2) : 0.f, beta * s_a[p]));
     }
   } else if constexpr (D == 2) {
     if (fast) {
@@ -338,10 +393,24 @@ __global__ void __launch_bounds__(NT) k_sym_up(SymTask t, Filter f) {
           e0.w = fmaf(f.h[2 * j], v.w, e0.w); e1.w = fmaf(f.h[2 * j + 1], v.w, e1.w);
         }
         const int g1 = o1 + 2 * ch, g2 = o2 + 4 * c4;
-        if (g1 < m1)
+        if constexpr (TR) {
+          auto rows = [&](int kb) {
+            images(kb, l1, [&](int kk) { return *reinterpret_cast<const float4*>(s_a + (kk - r1) * U2P + 4 * c4); },
+                   [&](float ho, float he, float4 v) {
+                     e0.x = fmaf(ho, v.x, e0.x); e1.x = fmaf(he, v.x, e1.x);
+                     e0.y = fmaf(ho, v.y, e0.y); e1.y = fmaf(he, v.y, e1.y);
+                     e0.z = fmaf(ho, v.z, e0.z); e1.z = fmaf(he, v.z, e1.z);
+                     e0.w = fmaf(ho, v.w, e0.w); e1.w = fmaf(he, v.w, e1.w);
+                   });
+          };
+          if (o1 == 0 && g1 < L - 2) rows(-1 - g1 / 2);
+          if (q1 == m1 && g1 < m1 && m1 - 1 - g1 / 2 < l1) rows(m1 - 1 - g1 / 2);
+        }
+        if (g2 >= q2) return;
+        if (g1 < q1)
           gst4(out + g1 * so1 + g2, make_float4(fmaf(alpha, xs0.x, beta * e0.x), fmaf(alpha, xs0.y, beta * e0.y),
                                                fmaf(alpha, xs0.z, beta * e0.z), fmaf(alpha, xs0.w, beta * e0.w)));
-        if (g1 + 1 < m1)
+        if (g1 + 1 < q1)
           gst4(out + (g1 + 1) * so1 + g2, make_float4(fmaf(alpha, xs1.x, beta * e1.x), fmaf(alpha, xs1.y, beta * e1.y),
                                                      fmaf(alpha, xs1.z, beta * e1.z), fmaf(alpha, xs1.w, beta * e1.w)));
       }
@@ -355,12 +424,20 @@ __global__ void __launch_bounds__(NT) k_sym_up(SymTask t, Filter f) {
         },
         [&](int c, int p, float e0, float e1) {
           const int g1 = o1 + p, g2 = o2 + c;
-          if (g2 < m2) {
-            if (g1 < m1) {
+          if constexpr (TR) {
+            auto rows = [&](int kb) {
+              images(kb, l1, [&](int kk) { return s_a[(kk - r1) * U2P + c]; },
+                     [&](float ho, float he, float v) { e0 = fmaf(ho, v, e0); e1 = fmaf(he, v, e1); });
+            };
+            if (o1 == 0 && g1 < L - 2) rows(-1 - g1 / 2);
+            if (q1 == m1 && g1 < m1 && m1 - 1 - g1 / 2 < l1) rows(m1 - 1 - g1 / 2);
+          }
+          if (g2 < q2) {
+            if (g1 < q1) {
               const int o = g1 * so1 + g2;
               gst(out + o, fmaf(alpha, has_same ? gld(same + o) : 0.f, beta * e0));
             }
-            if (g1 + 1 < m1) {
+            if (g1 + 1 < q1) {
               const int o = (g1 + 1) * so1 + g2;
               gst(out + o, fmaf(alpha, has_same ? gld(same + o) : 0.f, beta * e1));
             }
@@ -618,7 +695,8 @@ __global__ void __launch_bounds__(256) k_sym_fold(SymFold F) {
     fold_edges(F, b - F.gmain, gridDim.x - F.gmain);
 }
 
-// Boundary shell of the transposed operator on 1-D and 2-D grids.  On [0, n) the extended
+// Boundary shell of the transposed operator on 1-D and 2-D grids with an axis of fewer than L - 1 samples
+// (longer ones: k_sym_up<TR>, whose edge tiles hold all their images).  On [0, n) the extended
 // synthesis equals the forward synthesis S, so per axis the folded synthesis is S + C, where C adds
 // at a position j the synthesis at every other image of j (nonzero only within L - 2 of an edge, or
 // everywhere on an axis shorter than L - 1: the shell).  On a 2-D grid (axis 1 = rows, axis 2 =
@@ -842,17 +920,18 @@ hipError_t launch_sym_shell(int L, const SymShell& S, bool prep, unsigned grid, 
   return hipGetLastError();
 }
 
+// ZX: an analysis level extended by zeros, or a synthesis level with its images folded in (TR).
 template <int D, int L, bool ZX>
 hipError_t launch_sym_level(bool up, const SymTask& t, int64_t grid, const Filter& f, hipStream_t s) {
   if constexpr (D == 1) {
-    if (up) hipLaunchKernelGGL((k_sym_up<1, L, 1, 1, 512, kSymThreads>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
+    if (up) hipLaunchKernelGGL((k_sym_up<1, L, 1, 1, 512, kSymThreads, ZX>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
     else hipLaunchKernelGGL((k_sym_down<1, L, 1, 1, 256, kSymThreads, ZX>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
   } else if constexpr (D == 2) {
-    if (up) hipLaunchKernelGGL((k_sym_up<2, L, 1, 32, 64, kSymThreads>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
+    if (up) hipLaunchKernelGGL((k_sym_up<2, L, 1, 32, 64, kSymThreads, ZX>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
     else hipLaunchKernelGGL((k_sym_down<2, L, 1, 16, 48, kSymThreads, ZX>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
   } else {
     if (up) {
-      hipLaunchKernelGGL((k_sym_up<3, L, 8, 8, 32, kSymThreads>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
+      hipLaunchKernelGGL((k_sym_up<3, L, 8, 8, 32, kSymThreads, false>), dim3((unsigned)grid), dim3(kSymThreads), 0, s, t, f);
     } else if constexpr (L <= 4) {
       hipLaunchKernelGGL((k_sym_down<3, L, 4, 8, 16, kSym3Threads, ZX>), dim3((unsigned)grid), dim3(kSym3Threads), 0, s, t, f);
     } else if constexpr (L <= 8) {
@@ -963,7 +1042,7 @@ bool sym_filter(int L, Filter* f) {
 struct SymLaunch {
   int kind;  // 0 analysis level, 1 synthesis level, 2 fold, 3 boundary shell (transposed operator),
              // 4 axis-0 pass of a split analysis level
-  bool zx;   // analysis with zero extension (S_a^T)
+  bool zx;   // analysis with zero extension (S_a^T); synthesis with its images folded in (A^T)
   int D;     // dimensionality of the level kernel (2 on the slices of a split 3-D level)
   SymTask t;
   SymFold fold;
@@ -1048,7 +1127,17 @@ bool sym_split(const SymGeo& g, int i, int64_t batch) {
   return g.L >= 14 || batch * g.size(i - 1) >= (int64_t)1 << (25 - g.L / 2);
 }
 
-// Scratch floats of the shell of level j (0 where the level has no shell pass).
+// Whether the transposed up-level j of a 1-D or 2-D grid folds its images in (k_sym_up<TR>): every axis
+// holds at least L - 1 samples, so that an output has at most one image past either end and the edge tiles
+// hold all of both.  Shorter axes take the forward level and the boundary shell.
+bool sym_fused_images(const SymGeo& g, int j) {
+  for (int a = 3 - g.D; a < 3; ++a)
+    if (g.dims[j - 1][a] < g.L - 1) return false;
+  return g.D <= 2;
+}
+
+// Scratch floats of the shell of level j, counted for every level of a 1-D or 2-D grid: the workspace size
+// is part of the interface.
 int64_t sym_shell_floats(const SymGeo& g, int j, int64_t batch) {
   const SymShell S = sym_shell(g, j, batch, nullptr, nullptr, 0.f, nullptr);
   return align64f(batch * S.bs_Y) + align64f(batch * S.bs_W);
@@ -1199,10 +1288,11 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
       continue;
     }
     if (g.D <= 2) {
-      // transposed, 1-D and 2-D: the forward up-level (u_{j-1} = c_{j-1} b_{j-1} + beta S u_j on
-      // [0, n)), then the boundary shell adds beta times the extension images
+      // transposed, 1-D and 2-D: u_{j-1} = c_{j-1} b_{j-1} + beta A^T u_j with the extension's images
+      // folded in, or the forward up-level on [0, n) and the boundary shell after it
       SymLaunch l{};
       l.kind = 1;
+      l.zx = sym_fused_images(g, j);
       l.D = g.D;
       l.t.in = lev[j];
       l.t.same = lev[j - 1];
@@ -1220,6 +1310,7 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
       strides(j - 1, l.t.so);
       l.grid = sym_tiling(l.t, tl.u, batch);
       out->push_back(l);
+      if (l.zx) continue;
       SymLaunch sl{};
       sl.kind = 3;
       sl.shell = sym_shell(g, j, batch, lev[j], dst, (float)beta, vext);
