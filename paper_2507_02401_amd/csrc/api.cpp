@@ -227,9 +227,8 @@ bool reverse_orders() {
   const char* e = getenv("ESWAVE_NO_REVERSE");
   return !(e && *e == '1');
 }
-// Kernel family of the levels that have a streamed variant (3-D full-bank levels, 2-D low-pass
-// analysis): ESWAVE_STREAMED=0 plain tiles only, 2 streamed tiles at every such level,
-// otherwise (default) streamed where the level fills the chip.
+// Kernel family of the levels that have more than one: ESWAVE_STREAMED=0 plain tiles only, 2 streamed
+// tiles at every level that has them, otherwise (default) the rules of streams() and lp_split().
 int streamed_mode() {
   const char* e = getenv("ESWAVE_STREAMED");
   if (e && (*e == '0' || *e == '2')) return *e - '0';
@@ -263,6 +262,24 @@ struct Schedule {
 void set_tiles(Task& t, int kind, const Geo& g, int level, int variant, int64_t batch) {
   int b[3];
   g.level_dims(level - 1, b);  // full-res block of the level
+  if (kind == K_LP_DOWN_P || kind == K_LP_DOWN_A1) {
+    const TileShape ts = tile_shape(kind, g.D, variant, g.L);
+    for (int k = 0; k < 3; ++k) t.b[k] = b[k];
+    auto tiles = [](int64_t n, int tile) { return (int32_t)((n + tile - 1) / tile); };
+    if (kind == K_LP_DOWN_P) {  // planes of axis 1; axes 0 and 2 tiled
+      t.ntile[0] = b[1];
+      t.ntile[1] = tiles(b[0] / 2, ts.t[1]);
+      t.ntile[2] = tiles(b[2] / 2, ts.t[2]);
+    } else {  // lines along axis 1 in 16-byte groups; axis 1 in chunks
+      t.ntile[0] = tiles((int64_t)(b[0] / 2) * ((b[2] / 2 + 3) / 4), ts.t[0]);
+      t.ntile[1] = tiles(b[1] / 2, ts.t[1]);
+      t.ntile[2] = 1;
+    }
+    t.tiles_per_inst = t.ntile[0] * t.ntile[1] * t.ntile[2];
+    t.batch = (int32_t)batch;
+    t.tile_begin = 0;
+    return;
+  }
   const TileShape ts = tile_shape(kind, g.D, variant, g.L);
   const bool analysis = kind_is_analysis(kind);
   for (int k = 0; k < 3; ++k) {
@@ -327,6 +344,12 @@ int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
     switch (kind) {
       case K_LP_DOWN: return g.L > 8 ? 1 : wgs(0) >= 256 ? 0 : wgs(2) >= 128 ? 2 : 1;
       case K_LP_DOWN_S: return wgs(2) >= 512 ? 2 : 1;
+      case K_LP_DOWN_P: {  // the widest tile that a plane's rows fill
+        int b[3];
+        g.level_dims(level - 1, b);
+        return b[2] >= 96 ? 0 : b[2] >= 48 ? 2 : 1;
+      }
+      case K_LP_DOWN_A1: return 0;
       case K_LP_UP: return wgs(0) >= 512 ? 0 : wgs(2) >= 256 ? 2 : 1;
       case K_LP_UP_S: return wgs(0) >= 512 ? 0 : 1;
       case K_FB_DOWN: return wgs(2) >= 64 ? 2 : 1;
@@ -342,6 +365,8 @@ int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
 bool vec_ok(const Task& t, int kind, const Geo& g) {
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   auto m4 = [](int64_t v) { return (v & 3) == 0; };
+  if (kind == K_LP_DOWN_A1)
+    return m4(t.b[2] / 2) && a16(t.in0) && a16(t.out0) && m4(t.bs_in0) && m4(t.bs_out0);
   const bool analysis = kind_is_analysis(kind);
   const int row = analysis ? t.b[2] : (kind == K_LP_UP2 ? t.b[2] / 4 : t.b[2] / 2);  // staged input rows
   if (!m4(row)) return false;
@@ -391,6 +416,21 @@ bool streams(int kind, const Geo& g, int level, int64_t batch) {
   }
 }
 
+// Whether a 3-D low-pass analysis level runs as planes and an axis-1 pass (K_LP_DOWN_P, K_LP_DOWN_A1): the
+// second launch costs 3-4 us of a small call, the halo saved grows with the taps and the samples.  Calls
+// with the finest level in one launch / split, us: 12 to 16 taps win from ~2^19.5 samples (16 taps: 96^3
+// 42.5 / 37.6, 4 x 128^3 86.7 / 73.7, 256^3 125 / 105; 64^3 28.2 / 28.6), also at the second level (4 x 128^3
+// 73.7 / 68.0), 10 taps from ~2^20.5 (128^3 35.7 / 32.1, 96^3 31.1 / 30.8), 8 taps from ~2^22.5 (4 x 128^3
+// 51.8 / 49.8, 128^3 29.1 / 31.1), 2 to 6 taps nowhere (256^3, 6 taps: 69.0 / 71.5).
+bool lp_split(const Geo& g, int level, int64_t batch) {
+  if (g.D != 3 || g.L < 8 || streamed_mode() != 1 || g_mode.persist || forced_variant() >= 0) return false;
+  int b[3];
+  g.level_dims(level - 1, b);
+  if (b[2] & 3) return false;  // the plane kernel has the 16-byte path only
+  const double samples = (double)g.level_size(level - 1) * std::max((double)batch, g_variant_share);
+  return samples >= (double)((int64_t)3 << (g.L >= 12 ? 18 : g.L == 10 ? 19 : 21));
+}
+
 Launch level_launch(int kind, const Geo& g, int level, int64_t batch) {
   const int mode = streamed_mode();
   if (has_family(kind, g.D) && mode != 0 && !g_mode.persist && (mode == 2 || streams(kind, g, level, batch)))
@@ -416,7 +456,9 @@ void apply_variant(Launch& l, const Geo& g, int v, int64_t batch) {
 
 // Tunable choices of a level launch: its tile variants, and for levels with two kernel families
 // the tile variants of both (choice = variant + kNumVariants for the streamed family).
-int num_choices(const Launch& l) { return is_family(l) ? 2 * kNumVariants : kNumVariants; }
+int num_choices(const Launch& l) {
+  return is_family(l) ? 2 * kNumVariants : l.kind == K_LP_DOWN_A1 ? 1 : kNumVariants;
+}
 void apply_choice(Launch& l, const Geo& g, int c, int64_t batch) {
   if (is_family(l)) l.kind = c >= kNumVariants ? streamed_kind(l.kind) : tiled_kind(l.kind);
   apply_variant(l, g, c % kNumVariants, batch);
@@ -554,6 +596,29 @@ es_status build_schedule_raw(int op, const Geo& g, int64_t batch, const float* i
     const bool tail = T >= 0;
     const int down_to = tail ? T : m - 1;
     for (int i = 1; i <= down_to; ++i) {
+      if (lp_split(g, i, batch)) {
+        // the planes' array (a quarter of the level's input) goes to `out`, which the last launch writes
+        Launch p = level_launch(K_LP_DOWN_P, g, i, batch), q = level_launch(K_LP_DOWN_A1, g, i, batch);
+        int d_in[3], d_out[3];
+        lvl_dims(i - 1, d_in);
+        lvl_dims(i, d_out);
+        const int d_mid[3] = {d_out[0], d_in[1], d_out[2]};
+        p.task.in0 = i == 1 ? in : lvl_ptr(i - 1);
+        p.task.bs_in0 = i == 1 ? N : wsi;
+        strides_of(d_in, p.task.st_in0);
+        q.task.in0 = p.task.out0 = out;
+        q.task.bs_in0 = p.task.bs_out0 = N;
+        strides_of(d_mid, p.task.st_out0);
+        strides_of(d_mid, q.task.st_in0);
+        q.task.out0 = lvl_ptr(i);
+        q.task.bs_out0 = wsi;
+        strides_of(d_out, q.task.st_out0);
+        finish_level(p, g);
+        finish_level(q, g);
+        sc->launches.push_back(p);
+        sc->launches.push_back(q);
+        continue;
+      }
       Launch l = level_launch(K_LP_DOWN, g, i, batch);
       int d_in[3], d_out[3];
       lvl_dims(i - 1, d_in);
@@ -840,6 +905,14 @@ void launch_accesses(const Launch& l, std::vector<Access>* acc) {
       add(t.in0, t.bs_in0, block_span(t.b, t.st_in0[0], t.st_in0[1]), false);
       add(t.out0, t.bs_out0, dense_span(h), true);
       break;
+    case K_LP_DOWN_P:
+    case K_LP_DOWN_A1: {
+      const int mid[3] = {h[0], t.b[1], h[2]};
+      const bool first = l.kind == K_LP_DOWN_P;
+      add(t.in0, t.bs_in0, first ? block_span(t.b, t.st_in0[0], t.st_in0[1]) : dense_span(mid), false);
+      add(t.out0, t.bs_out0, dense_span(first ? mid : h), true);
+      break;
+    }
     case K_LP_UP:
     case K_LP_UP_S:
       add(t.in0, t.bs_in0, dense_span(h), false);
@@ -1309,7 +1382,8 @@ bool rebase(T*& ptr, const float* in, float* out, void* ws) {
   return false;
 }
 
-// Phase of step j of an instance schedule: down steps get their level index, the tail 1000,
+// Phase of step j of an instance schedule: down steps get twice their level index (the axis-1 pass of a
+// split level one more), the tail 1000,
 // up steps 2000 - (level they produce).
 void step_phases(int op, const Geo& g, const Schedule& sc, std::vector<int>* ph) {
   ph->clear();
@@ -1317,8 +1391,10 @@ void step_phases(int op, const Geo& g, const Schedule& sc, std::vector<int>* ph)
   for (const Launch& l : sc.launches) {
     if (l.is_tail) {
       ph->push_back(op == ES_OP_APPLY ? 0 : 1000);
+    } else if (l.kind == K_LP_DOWN_A1) {  // second half of the level before it
+      ph->push_back(2 * down + 1);
     } else if (kind_is_analysis(l.kind)) {
-      ph->push_back(++down);
+      ph->push_back(2 * ++down);
     } else {
       // LP_UP / FB_UP: task.b is the full-res output block; its level index follows from size
       int lev = 0;
@@ -2636,8 +2712,8 @@ es_status es_schedule_describe(int op, int ndim, const int64_t* shape, int64_t b
   if (st != ES_OK) return st;
   if (index < 0 || index >= (int32_t)sc.launches.size()) return fail(ES_EINVAL, "step index out of range");
   const Launch& l = sc.launches[index];
-  static const char* kinds[9] = {"lp_down", "lp_up", "fb_down", "fb_up", "lp_up2", "fb_down_s", "fb_up_s", "lp_down_s",
-                                 "lp_up_s"};
+  static const char* kinds[11] = {"lp_down", "lp_up", "fb_down", "fb_up", "lp_up2", "fb_down_s", "fb_up_s", "lp_down_s",
+                                  "lp_up_s", "lp_down_p", "lp_down_a1"};
   static const char* tails[4] = {"tail_lp_off", "tail_fb_analysis", "tail_fb_synthesis", "lp_coarse"};
   char buf[128];
   int lev = 0;

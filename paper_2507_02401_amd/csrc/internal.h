@@ -104,10 +104,14 @@ enum KernelKind {
   K_FB_DOWN_S = 5,  // 3-D full analysis level, streamed along axis 0 (same Task fields as FB_DOWN)
   K_FB_UP_S = 6,    // 3-D full synthesis level, streamed along axis 0 (same Task fields as FB_UP)
   K_LP_DOWN_S = 7,  // low-pass analysis level, streamed along axis 1 (2-D) or axis 0 (3-D) (same Task fields as LP_DOWN)
-  K_LP_UP_S = 8     // 3-D low-pass synthesis level, streamed along axis 0 (same Task fields as LP_UP)
+  K_LP_UP_S = 8,    // 3-D low-pass synthesis level, streamed along axis 0 (same Task fields as LP_UP)
+  // 3-D low-pass analysis level in two launches: axes 2 and 0 on the planes of axis 1 (in0 -> out0 of dims
+  // (b0/2, b1, b2/2)), then axis 1 (that array in0 -> out0, the level); b = the level's input block in both
+  K_LP_DOWN_P = 9,
+  K_LP_DOWN_A1 = 10
 };
 inline bool kind_is_analysis(int k) {
-  return k == K_LP_DOWN || k == K_FB_DOWN || k == K_FB_DOWN_S || k == K_LP_DOWN_S;
+  return k == K_LP_DOWN || k == K_FB_DOWN || k == K_FB_DOWN_S || k == K_LP_DOWN_S || k == K_LP_DOWN_P || k == K_LP_DOWN_A1;
 }
 
 // Tile shape selection: each (kind, ndim, taps) has wide (0), narrow (1) and medium (2) tiles.

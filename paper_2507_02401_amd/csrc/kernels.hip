@@ -58,6 +58,69 @@ __global__ void __launch_bounds__(NT) k_lp_up(TaskArgs args, Filter f) {
   lp_up_tile<D, L, U0, U1, U2, NT, VEC>(t, wg, f, sm);
 }
 
+// A 3-D analysis level in two launches.  A 3-D tile of a long filter is mostly halo: the plain 2 x 4 x 8
+// tile of 16 taps filters 18 x 22 x 30 samples for 64 outputs, the streamed one keeps the halo of axes 1
+// and 2 and walks axis 0 in sequence.  Planes: axes 2 and 0 as the 2-D tile on every plane of axis 1 (rows
+// of a plane are b1 * b2 apart), a quarter of the level's samples to scratch.  Axis-1 pass: lines of that
+// array.  Taps and axes (2, 0, 1) in the order of the 3-D tiles: identical bits.
+// 4 x 128^3, 16 taps: the two finest levels 33.1 + 16.6 -> (13.3 + 5.4) + (5.2 + 4.9) us.  What bounds the
+// planes now: their row and column filters (46 x 142 staged samples for 16 x 64 outputs).
+template <int L, int T1, int T2, int NT>
+__global__ void __launch_bounds__(NT) k_lp_down_p(TaskArgs args, Filter f) {
+  __shared__ LpDownSmem<2, L, 1, T1, T2> sm;
+  const int wg = logical_wg(args.total_wg, args.reverse);
+  if (wg < 0) return;
+  const Task t = pick_task<Task>(args, wg);
+  lp_down_tile<2, L, 1, T1, T2, NT, true, true>(t, wg, f, sm);
+}
+
+// Axis 1 of a split level: a thread takes C outputs of four adjacent lines, all loads of its window in
+// flight before the first sum; chunks of the same lines, which share most of their windows, follow each
+// other on one XCD.  Memory (L2) bound.
+template <int L, int C, int NT, bool VEC>
+__global__ void __launch_bounds__(NT) k_lp_down_a1(TaskArgs args, Filter f) {
+  constexpr int W = 2 * C + L - 2;
+  const int wg = logical_wg(args.total_wg, args.reverse);
+  if (wg < 0) return;
+  const Task t = pick_task<Task>(args, wg);
+  const Tile tl = decode_tile(t, wg);
+  const int b1 = t.b[1], n0o = t.b[0] >> 1, n1o = b1 >> 1, n2o = t.b[2] >> 1;
+  const int groups = (n2o + 3) >> 2, line = tl.c0 * NT + int(threadIdx.x);
+  if (line >= n0o * groups) return;
+  const int i0 = line / groups, c = 4 * (line - i0 * groups), k0 = C * tl.c1;
+  const float* __restrict__ src = t.in0 + tl.inst * t.bs_in0 + i0 * t.st_in0[0] + c;
+  float* __restrict__ dst = t.out0 + tl.inst * t.bs_out0 + i0 * t.st_out0[0] + c;
+  const int nc = VEC ? 4 : min(4, n2o - c);
+  float4 w[W];
+#pragma unroll
+  for (int j = 0; j < W; ++j) {
+    const float* p = src + pmod(2 * k0 + j, b1) * t.st_in0[1];
+    if constexpr (VEC) w[j] = gld4(p);
+    else w[j] = make_float4(gld(p), gld(p + min(1, nc - 1)), gld(p + min(2, nc - 1)), gld(p + min(3, nc - 1)));
+  }
+#pragma unroll
+  for (int q = 0; q < C; ++q) {
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+      const float4 v = w[2 * q + k];
+      a.x = fmaf(f.h[k], v.x, a.x); a.y = fmaf(f.h[k], v.y, a.y);
+      a.z = fmaf(f.h[k], v.z, a.z); a.w = fmaf(f.h[k], v.w, a.w);
+    }
+    if (k0 + q < n1o) {
+      float* o = dst + (k0 + q) * t.st_out0[1];
+      if constexpr (VEC) {
+        gst4(o, a);
+      } else {
+        gst(o, a.x);
+        if (nc > 1) gst(o + 1, a.y);
+        if (nc > 2) gst(o + 2, a.z);
+        if (nc > 3) gst(o + 3, a.w);
+      }
+    }
+  }
+}
+
 // LP_UP with the conjugate-gradient solver's epilogue (2-D vector path): out = (alpha + gamma m)
 // same + beta A^T z, and each work-group's sum of same * out (see lp_up_tile).
 template <int L, int U1, int U2, int NT>
@@ -1572,6 +1635,13 @@ hipError_t launch_kind(const TaskArgs& a, int grid, const Filter& f, hipStream_t
     hipLaunchKernelGGL((k_lp_up<D, L, ES_TILE(K, D, V, L), kThreads, VEC>), dim3(grid), dim3(kThreads), 0, s, a, f);
   else if constexpr (K == K_FB_DOWN)
     hipLaunchKernelGGL((k_fb_down<D, L, ES_TILE(K, D, V, L), kThreads, VEC>), dim3(grid), dim3(kThreads), 0, s, a, f);
+  else if constexpr (K == K_LP_DOWN_P && !VEC)
+    return hipErrorInvalidValue;  // split levels have rows of whole 16-byte groups
+  else if constexpr (K == K_LP_DOWN_P)
+    hipLaunchKernelGGL((k_lp_down_p<L, shape_of(K, 3, V, L).b, shape_of(K, 3, V, L).c, kThreads>), dim3(grid),
+                       dim3(kThreads), 0, s, a, f);
+  else if constexpr (K == K_LP_DOWN_A1)
+    hipLaunchKernelGGL((k_lp_down_a1<L, kA1Rows, kThreads, VEC>), dim3(grid), dim3(kThreads), 0, s, a, f);
   else if constexpr (K == K_LP_DOWN_S && D == 3)
     hipLaunchKernelGGL((k_lp_down_s3<L, ES_TILE(K, D, V, L), kThreads, VEC>), dim3(grid), dim3(kThreads), 0, s, a, f);
   else if constexpr (K == K_LP_DOWN_S)
@@ -1712,6 +1782,12 @@ hipError_t launch_level(int kind, int ndim, int taps, int variant, const TaskArg
       if (ndim == 3) return launch_kd<K_LP_DOWN_S, 3>(taps, variant, vec, args, grid, f, stream);
       if (ndim != 2) return hipErrorInvalidValue;
       return launch_kd<K_LP_DOWN_S, 2>(taps, variant, vec, args, grid, f, stream);
+    case K_LP_DOWN_P:
+      if (ndim != 3) return hipErrorInvalidValue;
+      return launch_kd<K_LP_DOWN_P, 3>(taps, variant, vec, args, grid, f, stream);
+    case K_LP_DOWN_A1:
+      if (ndim != 3) return hipErrorInvalidValue;
+      return launch_kd<K_LP_DOWN_A1, 3>(taps, 0, vec, args, grid, f, stream);
     case K_LP_UP_S:
       if (ndim != 3) return hipErrorInvalidValue;
       return launch_kd<K_LP_UP_S, 3>(taps, variant, vec, args, grid, f, stream);

@@ -22,7 +22,8 @@ struct LpDownSmem {
 };
 
 // One LP_DOWN tile: work-group index `wg` of task `t` (decoded with the task's tile counts).
-template <int D, int L, int T0, int T1, int T2, int NT, bool VEC>
+// PLANE (D = 2): axes 0 and 2 of a 3-D block on the plane c0 of axis 1; output rows b1 * b2/2 apart.
+template <int D, int L, int T0, int T1, int T2, int NT, bool VEC, bool PLANE = false>
 DEVI void lp_down_tile(const Task& t, int wg, const Filter& f, LpDownSmem<D, L, T0, T1, T2>& sm) {
   using G = DownGeom<D, L, T0, T1, T2>;
   constexpr int P2 = 4, P1 = 4, P0 = 2;
@@ -31,14 +32,17 @@ DEVI void lp_down_tile(const Task& t, int wg, const Filter& f, LpDownSmem<D, L, 
   int* s_row = sm.s_row;
   int* s_col = sm.s_col;
   const Tile tl = decode_tile(t, wg);
-  const float* __restrict__ src = t.in0 + tl.inst * t.bs_in0;
-  float* __restrict__ dst = t.out0 + tl.inst * t.bs_out0;
-  const int b0 = t.b[0], b1 = t.b[1], b2 = t.b[2];
+  static_assert(!PLANE || D == 2, "planes are 2-D tiles");
+  const int plane = PLANE ? tl.c0 : 0;
+  const float* __restrict__ src = t.in0 + tl.inst * t.bs_in0 + plane * t.st_in0[1];
+  float* __restrict__ dst = t.out0 + tl.inst * t.bs_out0 + plane * t.st_out0[1];
+  const int b0 = t.b[0], b1 = PLANE ? t.b[0] : t.b[1], b2 = t.b[2];
   const int o0 = 2 * T0 * tl.c0, o1 = 2 * T1 * tl.c1, o2 = 2 * T2 * tl.c2;
+  const int st1 = PLANE ? t.st_in0[0] : t.st_in0[1];
 
   for (int i = threadIdx.x; i < G::NROW; i += NT) {
     const int i1 = i % G::I1, i0 = i / G::I1;
-    s_row[i] = (D >= 3 ? pmod(o0 + i0, b0) * t.st_in0[0] : 0) + (D >= 2 ? pmod(o1 + i1, b1) * t.st_in0[1] : 0);
+    s_row[i] = (D >= 3 ? pmod(o0 + i0, b0) * t.st_in0[0] : 0) + (D >= 2 ? pmod(o1 + i1, b1) * st1 : 0);
   }
   for (int i = threadIdx.x; i < G::NV; i += NT) s_col[i] = VEC ? pmod(o2 + 4 * i, b2) : o2 + 4 * i;
   __syncthreads();
@@ -66,7 +70,7 @@ DEVI void lp_down_tile(const Task& t, int wg, const Filter& f, LpDownSmem<D, L, 
         },
         [&](int c, int k, float lo, float) {
           const int g1 = T1 * tl.c1 + k, g2 = T2 * tl.c2 + c;
-          if (g1 < n1o && g2 < n2o) gst(dst + g1 * n2o + g2, lo);
+          if (g1 < n1o && g2 < n2o) gst(dst + g1 * (PLANE ? t.st_out0[0] : n2o) + g2, lo);
         });
   } else {
     // dim 0: (I0, I1, T2) -> (T0, I1, T2), lines are (i1, c)

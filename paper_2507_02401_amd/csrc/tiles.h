@@ -7,12 +7,17 @@
 
 namespace es {
 
+constexpr int kThreads = 256;  // threads of every level-kernel work-group
+constexpr int kA1Rows = 4;     // outputs a thread of the axis-1 pass (K_LP_DOWN_A1) forms
+
 struct Shape3 {
   int a, b, c;
 };
 constexpr Shape3 shape_of(int K, int D, int V, int L) {
   // V: 0 wide, 1 narrow, 2 medium
   if (K == K_LP_UP2) return V == 0 ? Shape3{1, 64, 128} : (V == 1 ? Shape3{1, 32, 64} : Shape3{1, 32, 128});
+  if (K == K_LP_DOWN_P) return V == 0 ? Shape3{1, 16, 64} : (V == 1 ? Shape3{1, 16, 16} : Shape3{1, 16, 32});  // plane, axis 0, axis 2
+  if (K == K_LP_DOWN_A1) return Shape3{kThreads, kA1Rows, 1};  // lines (16-byte groups), axis 1
   if (K == K_LP_DOWN_S && D == 3) return V == 0 ? Shape3{16, 8, 32} : (V == 1 ? Shape3{8, 8, 16} : Shape3{8, 8, 32});
   if (K == K_LP_DOWN_S) return V == 0 ? Shape3{1, 64, 64} : (V == 1 ? Shape3{1, 16, 64} : Shape3{1, 32, 64});
   if (K == K_LP_UP_S) return V == 0 ? Shape3{16, 16, 32} : (V == 1 ? Shape3{8, 8, 32} : Shape3{8, 16, 32});
@@ -43,8 +48,6 @@ constexpr Shape3 shape_of(int K, int D, int V, int L) {
                     : (V == 1 ? Shape3{4, 8, 16} : (L <= 8 ? Shape3{4, 8, 32} : Shape3{4, 8, 16}));
   }
 }
-constexpr int kThreads = 256;       // threads of every level-kernel work-group
-
 // Output rows per chunk of the streamed 2-D low-pass analysis kernel (measured on 64 x 1024^2 and
 // 64 x 512^2 db8 levels against 4 and 16, with strips of 64, 128 and 256 columns).
 constexpr int kStreamRows = 8;
