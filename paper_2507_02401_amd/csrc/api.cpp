@@ -256,6 +256,7 @@ struct Launch {
 struct Schedule {
   std::vector<Launch> launches;
   bool identity = false;  // plain copy
+  bool tuned = false;     // the tune cache chose its tiles
   Filter f;
 };
 
@@ -328,28 +329,20 @@ int64_t level_wgs(int kind, const Geo& g, int level, int variant, int64_t batch)
 // launches below that take the narrow tiles.  Calls with the earlier thresholds (wide or medium tiles
 // from 1024 work-groups on) against these: 16 x 512^2 db6 48.8 -> 42 us, 8 x 1024^2 db8 68 -> 57, 64 x 256^2
 // db2 34 -> 28, 2 x 128^3 db6 es_adjoint 71 -> 44.
-int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
-  if (g_mode.persist) return kPVariant;
-  const int fv = forced_variant();
-  if (fv >= 0) return fv;
-  auto wgs = [&](int v) { return level_wgs(kind, g, level, v, batch); };
-  if (g.D == 2) {
+// wgs(v): work-groups of the launch with tile variant v.
+template <class W>
+int variant_rule(int kind, int D, int L, W wgs) {
+  if (D == 2) {
     switch (kind) {
       case K_FB_DOWN: return wgs(2) >= 1024 ? 2 : wgs(0) >= 128 ? 0 : 1;
       case K_FB_UP: return wgs(0) >= 128 ? 0 : 1;
       default: return wgs(2) >= 128 ? 2 : 1;  // LP_DOWN, LP_UP and the opt-in kinds
     }
   }
-  if (g.D == 3) {
+  if (D == 3) {
     switch (kind) {
-      case K_LP_DOWN: return g.L > 8 ? 1 : wgs(0) >= 256 ? 0 : wgs(2) >= 128 ? 2 : 1;
+      case K_LP_DOWN: return L > 8 ? 1 : wgs(0) >= 256 ? 0 : wgs(2) >= 128 ? 2 : 1;
       case K_LP_DOWN_S: return wgs(2) >= 512 ? 2 : 1;
-      case K_LP_DOWN_P: {  // the widest tile that a plane's rows fill
-        int b[3];
-        g.level_dims(level - 1, b);
-        return b[2] >= 96 ? 0 : b[2] >= 48 ? 2 : 1;
-      }
-      case K_LP_DOWN_A1: return 0;
       case K_LP_UP: return wgs(0) >= 512 ? 0 : wgs(2) >= 256 ? 2 : 1;
       case K_LP_UP_S: return wgs(0) >= 512 ? 0 : 1;
       case K_FB_DOWN: return wgs(2) >= 64 ? 2 : 1;
@@ -359,6 +352,19 @@ int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
     }
   }
   return wgs(0) >= 1024 ? (kind == K_LP_UP || kind == K_FB_UP ? 2 : 0) : 1;
+}
+
+int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
+  if (g_mode.persist) return kPVariant;
+  const int fv = forced_variant();
+  if (fv >= 0) return fv;
+  if (kind == K_LP_DOWN_A1) return 0;
+  if (kind == K_LP_DOWN_P) {  // the widest tile that a plane's rows fill
+    int b[3];
+    g.level_dims(level - 1, b);
+    return b[2] >= 96 ? 0 : b[2] >= 48 ? 2 : 1;
+  }
+  return variant_rule(kind, g.D, g.L, [&](int v) { return level_wgs(kind, g, level, v, batch); });
 }
 
 // Row-alignment condition of the vector staging path for one launch.
@@ -443,6 +449,7 @@ Launch level_launch(int kind, const Geo& g, int level, int64_t batch) {
   l.level = level;
   l.variant = pick_variant(kind, g, level, batch);
   set_tiles(l.task, kind, g, level, l.variant, batch);
+  l.task.taps = g.L;
   return l;
 }
 
@@ -548,6 +555,7 @@ void apply_tuned(Schedule* sc, int op, const Geo& g, int64_t batch) {
     Launch& l = sc->launches[j];
     if (!l.is_tail && v[j] >= 0 && v[j] < num_choices(l)) apply_choice(l, g, v[j], batch);
   }
+  sc->tuned = true;
 }
 
 // Consecutive launches walk their tiles in opposite orders, and the last launch (the finest
@@ -646,6 +654,7 @@ es_status build_schedule_raw(int op, const Geo& g, int64_t batch, const float* i
       t.bs_out = T == 0 ? N : wsi;
       lvl_dims(T, t.b);
       t.nlev = K;
+      t.taps = g.L;
       t.batch = (int32_t)batch;
       t.coef[0] = (float)(T == 0 ? w[1] : c[T]);
       for (int j = 1; j <= K; ++j) t.coef[j] = (float)c[T + j];
@@ -1289,6 +1298,7 @@ struct PlanGroup {
   Launch proto;           // kernel instantiation (kind, D, L, variant, vec, lds)
   std::vector<int> inst;  // instances, in table order
   std::vector<int> step;  // index of the step in the instance's schedule
+  bool mixed = false;     // holds several filter lengths
   int64_t table_off;      // first entry in the task (or tail) table
   int total_wg;
 };
@@ -1299,7 +1309,7 @@ struct es_plan {
   int op = 0;
   int device = 0;
   std::vector<Geo> geos;
-  std::map<std::pair<int, int>, int64_t> class_voxels;  // (D, L) -> voxels of its instances
+  std::map<std::pair<int, int>, int64_t> class_voxels;  // launch class -> voxels of its instances
   std::vector<int64_t> ws_off;
   std::vector<int64_t> ws_len;  // floats of each instance's workspace slice
   int64_t ws_total = 0;
@@ -1358,9 +1368,20 @@ constexpr uintptr_t kSentinelOut = (uintptr_t)2 << 44;
 constexpr uintptr_t kSentinelWs = (uintptr_t)3 << 44;
 constexpr uintptr_t kSentinelSpan = (uintptr_t)1 << 44;
 
+// Instances of one class share launches, those of two never do: dimensionality and filter length, except
+// that the 2-D low-pass launches hold every filter length (mixed.hip).
+std::pair<int, int> launch_class(int op, int D, int L) {
+  return {D, D == 2 && (op == ES_OP_COV || op == ES_OP_SAMPLE) ? 0 : L};
+}
+
+// Launches that may share a kernel with ones of another filter length.
+bool mixable(const Launch& l) {
+  return l.D == 2 && (l.is_tail ? l.kind == 3 : l.kind == K_LP_UP || (l.kind == K_LP_DOWN && l.vec));
+}
+
 es_status instance_schedule_frozen(const es_plan* p, int k, Schedule* sc) {
   const Geo& g = p->geos[k];
-  g_variant_share = (double)p->class_voxels.at({g.D, g.L}) / (double)g.N();
+  g_variant_share = (double)p->class_voxels.at(launch_class(p->op, g.D, g.L)) / (double)g.N();
   const es_status st = build_schedule(p->op, g, 1, (const float*)kSentinelIn, (float*)kSentinelOut,
                                       (float*)kSentinelWs + p->ws_off[k], sc);
   g_variant_share = 0;
@@ -1406,8 +1427,8 @@ void step_phases(int op, const Geo& g, const Schedule& sc, std::vector<int>* ph)
 
 // A member launch may share a group's kernel only if it is the same instantiation.
 bool same_kernel(const Launch& a, const Launch& proto) {
-  return a.is_tail == proto.is_tail && a.kind == proto.kind && a.D == proto.D && a.L == proto.L &&
-         a.variant == proto.variant && a.vec == proto.vec && (!a.is_tail || a.lds <= proto.lds);
+  return a.is_tail == proto.is_tail && a.kind == proto.kind && a.D == proto.D &&
+         (a.L == proto.L || (mixable(a) && mixable(proto))) && a.variant == proto.variant && a.vec == proto.vec && (!a.is_tail || a.lds <= proto.lds);
 }
 
 es_status plan_fill_tables(es_plan* p, const float* const* in, float* const* out, void* ws) {
@@ -1466,9 +1487,16 @@ es_status plan_fill_tables(es_plan* p, const float* const* in, float* const* out
 }
 
 es_status plan_launch_group(es_plan* p, const PlanGroup& gr, hipStream_t s) {
-  const Filter& f = p->filt[gr.proto.L];
-  return run_launch(gr.proto, f, s, gr.proto.is_tail ? nullptr : p->d_tasks + gr.table_off, (int)gr.inst.size(),
-                    gr.total_wg, gr.proto.is_tail ? p->d_tails + gr.table_off : nullptr);
+  const Task* tasks = gr.proto.is_tail ? nullptr : p->d_tasks + gr.table_off;
+  const TailTask* tails = gr.proto.is_tail ? p->d_tails + gr.table_off : nullptr;
+  if (gr.mixed) {
+    FilterBank bank;
+    for (int o = 1; o <= kMaxTaps / 2; ++o) bank.f[o - 1] = p->filt[2 * o];
+    Launch l = gr.proto;
+    l.L = kMixedTaps;
+    return run_launch(l, bank.f[0], s, tasks, (int)gr.inst.size(), gr.total_wg, tails);
+  }
+  return run_launch(gr.proto, p->filt[gr.proto.L], s, tasks, (int)gr.inst.size(), gr.total_wg, tails);
 }
 
 // All groups in order on one stream.
@@ -1480,11 +1508,11 @@ es_status plan_launch_all(es_plan* p, hipStream_t s) {
   return ES_OK;
 }
 
-// Graph capture with concurrent chains: instances of one dimensionality and filter length share their
-// launches and no others, so the groups of such a class are a chain that no other chain waits for.  The
+// Graph capture with concurrent chains: instances of different launch classes share no launches, so the
+// groups of a class are a chain that no other chain waits for.  The
 // chains are dealt to the stream and `nside` side streams, longest first to the least loaded, forked once
-// at the start and joined once at the end.  Joining the branches after every phase instead cost more
-// than the overlap gained (see es_plan_execute).  Events are created here and destroyed by the caller
+// at the start and joined once at the end.  Joining the branches after every phase instead cost
+// more than the overlap gained (4 branches, 48 instances: 285-440 us, differing from process to process).  Events are created here and destroyed by the caller
 // after the capture ends.
 es_status plan_launch_all_forked(es_plan* p, hipStream_t s, hipStream_t* side, int nside,
                                  std::vector<hipEvent_t>* events) {
@@ -1494,10 +1522,10 @@ es_status plan_launch_all_forked(es_plan* p, hipStream_t s, hipStream_t* side, i
     return ES_OK;
   };
   // cost of a chain in voxels: a launch that is too small to fill the chip takes as long as some 2^20 voxels
-  std::map<std::pair<int, int>, std::pair<int64_t, int>> chains;  // (D, L) -> (cost, branch)
-  for (const PlanGroup& gr : p->groups) chains[{gr.proto.D, gr.proto.L}].first += 1 << 20;
+  std::map<std::pair<int, int>, std::pair<int64_t, int>> chains;  // launch class -> (cost, branch)
+  for (const PlanGroup& gr : p->groups) chains[launch_class(p->op, gr.proto.D, gr.proto.L)].first += 1 << 20;
   for (const Geo& g : p->geos) {
-    auto it = chains.find({g.D, g.L});
+    auto it = chains.find(launch_class(p->op, g.D, g.L));
     if (it != chains.end()) it->second.first += g.N();
   }
   std::vector<std::pair<int64_t, std::pair<int, int>>> order;
@@ -1518,7 +1546,7 @@ es_status plan_launch_all_forked(es_plan* p, hipStream_t s, hipStream_t* side, i
     for (int k = 1; k < width; ++k) ES_HIP(hipStreamWaitEvent(side[k - 1], fork, 0), "hipStreamWaitEvent");
   }
   for (const PlanGroup& gr : p->groups) {
-    const int k = chains[{gr.proto.D, gr.proto.L}].second;
+    const int k = chains[launch_class(p->op, gr.proto.D, gr.proto.L)].second;
     es_status st = plan_launch_group(p, gr, k == 0 ? s : side[k - 1]);
     if (st != ES_OK) return st;
   }
@@ -1767,6 +1795,36 @@ void plan_layout(es_plan* p, bool persist) {
 
 // Host part of plan creation: geometries, workspace offsets, frozen schedules, launch groups and
 // host tables (no device call).
+// The tiles of the plain level launches from the work-groups that each launch really has: members of one
+// phase, kind and alignment share it.  Instances whose tiles the tune cache chose keep them.
+void plan_shared_tiles(const es_plan* p, std::vector<Schedule>* scs, const std::vector<std::vector<int>>& phases) {
+  if (forced_variant() >= 0) return;
+  std::map<std::tuple<int, int, std::pair<int, int>, int>, std::vector<std::pair<int, int>>> sets;
+  for (int k = 0; k < (int)scs->size(); ++k) {
+    const Schedule& sc = (*scs)[k];
+    if (sc.identity || sc.tuned) continue;
+    for (int j = 0; j < (int)sc.launches.size(); ++j) {
+      const Launch& l = sc.launches[j];
+      if (!l.is_tail && (l.kind == K_LP_DOWN || l.kind == K_LP_UP || l.kind == K_FB_DOWN || l.kind == K_FB_UP))
+        sets[{phases[k][j], l.kind, launch_class(p->op, l.D, l.L), l.vec}].push_back({k, j});
+    }
+  }
+  for (const auto& set : sets) {
+    auto launch = [&](const std::pair<int, int>& m) -> Launch& { return (*scs)[m.first].launches[m.second]; };
+    const Launch& l0 = launch(set.second[0]);
+    const int v = variant_rule(l0.kind, l0.D, l0.L, [&](int v) {
+      int64_t n = 0;
+      for (const auto& m : set.second) {
+        Task t{};
+        set_tiles(t, l0.kind, p->geos[m.first], launch(m).level, v, 1);
+        n += t.tiles_per_inst;
+      }
+      return n;
+    });
+    for (const auto& m : set.second) apply_variant(launch(m), p->geos[m.first], v, 1);
+  }
+}
+
 es_status plan_build(const es_desc* descs, int32_t count, int op, es_plan** out, int64_t lp_coarse = -1) {
   *out = nullptr;
   if (count < 0 || (count > 0 && !descs)) return fail(ES_EINVAL, "descs must hold count >= 0 entries");
@@ -1782,7 +1840,7 @@ es_status plan_build(const es_desc* descs, int32_t count, int op, es_plan** out,
     const es_desc& d = descs[k];
     st = make_geo(d.ndim, d.shape, d.order, d.levels, d.s, &p->geos[k]);
     if (st != ES_OK) { delete p; return fail(st, "desc %d: %s", k, g_last_error.c_str()); }
-    p->class_voxels[{p->geos[k].D, p->geos[k].L}] += p->geos[k].N();
+    p->class_voxels[launch_class(op, p->geos[k].D, p->geos[k].L)] += p->geos[k].N();
   }
   plan_layout(p, persistent_wanted(op));
   // freeze every instance schedule: for persistent execution when every level launch can take
@@ -1819,21 +1877,30 @@ es_status plan_build(const es_desc* descs, int32_t count, int op, es_plan** out,
     plan_layout(p, false);  // phase-merged after all: in-place level arrays
   }
   p->lp_coarse = lp_coarse;
+  std::vector<std::vector<int>> phases(count);
   for (int k = 0; k < count; ++k) {
     g_lp_coarse = lp_coarse;
     st = instance_schedule_frozen(p, k, &scs[k]);
     g_lp_coarse = -1;
     if (st != ES_OK) { delete p; return st; }
     if (scs[k].identity) { p->identity_inst.push_back(k); continue; }
+    step_phases(op, p->geos[k], scs[k], &phases[k]);
+  }
+  plan_shared_tiles(p, &scs, phases);
+  for (int k = 0; k < count; ++k) {
+    if (scs[k].identity) continue;
     p->frozen[k] = scs[k].launches;
-    std::vector<int> ph;
-    step_phases(op, p->geos[k], scs[k], &ph);
+    const std::vector<int>& ph = phases[k];
     for (size_t j = 0; j < scs[k].launches.size(); ++j) {
       const Launch& l = scs[k].launches[j];
       PlanGroup* gr = nullptr;
       for (PlanGroup& c : p->groups)
         if (c.phase == ph[j] && c.proto.is_tail == l.is_tail && c.proto.kind == l.kind && c.proto.D == l.D &&
-            c.proto.L == l.L && c.proto.variant == l.variant && c.proto.vec == l.vec) { gr = &c; break; }
+            (c.proto.L == l.L || (mixable(l) && mixable(c.proto))) && c.proto.variant == l.variant && c.proto.vec == l.vec) {
+          gr = &c;
+          break;
+        }
+      if (gr) gr->mixed = gr->mixed || gr->proto.L != l.L;
       if (!gr) {
         p->groups.push_back(PlanGroup{});
         gr = &p->groups.back();
@@ -2137,7 +2204,7 @@ es_status plan_autotune_merged(es_plan* p, const float* const* in, float* const*
       gr.proto.lds = proto0.lds;
       p->tables_valid = false;
     };
-    const int nc = num_choices(proto0);
+    const int nc = gr.mixed ? kNumVariants : num_choices(proto0);
     int best = -1;
     float t_best = 1e30f;
     for (int c = 0; c < nc && st == ES_OK; ++c) {
@@ -2534,21 +2601,15 @@ es_status es_plan_execute(es_plan* p, const float* const* in, float* const* out,
   if (!p->exec) {
     // kernels read everything through the device tables, so the captured graph stays valid
     // when the caller's pointers change (only the tables are refreshed, above)
-    // the chains of the instance classes run as parallel branches, ESWAVE_PLAN_BRANCHES of them at most
-    // (default: 2, or 1 -- one chain -- for plans under 2^22 voxels).  48 instances of 23 M voxels, same /
-    // new buffers on each call, us: 1 branch 318 / 320, 2 branches 236-257 / 295-305, 3 261-277 / 290-300,
-    // 4 245-270 / 335-360; 36 instances of 13.6 M voxels: 251 / 253, 202 / 250, 210 / 255, 208 / 277.
-    // Submitting a branched graph costs the host 3.5 us a launch against 1.5 us for one chain.  Joining 4
-    // branches after every phase: 285-440, differing from process to process.
+    // one chain, or, with ESWAVE_PLAN_BRANCHES, that many parallel branches at most.  48 instances of 23 M
+    // voxels, same / new buffers on each call, us: 1 branch 216 / 218, 2 branches 200 / 245, 3 192 / 265;
+    // 36 instances of 13.6 M voxels: 148 / 149, 145 / 187, 152 / 208 -- submitting a branched graph costs the
+    // host 3.5 us a launch against 1.5 us for one chain.
     constexpr int kSide = 15;
-    constexpr int64_t kBranchMinVoxels = 1 << 22;
     hipStream_t cap = nullptr, side[kSide] = {};
     ES_HIP(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking), "hipStreamCreate");
     const char* br = getenv("ESWAVE_PLAN_BRANCHES");
-    int64_t voxels = 0;
-    for (const Geo& g : p->geos) voxels += g.N();
-    const int def_br = voxels < kBranchMinVoxels ? 1 : 2;
-    int nside = std::max(0, std::min(kSide, (br && *br ? atoi(br) : def_br) - 1));
+    int nside = std::max(0, std::min(kSide, (br && *br ? atoi(br) : 1) - 1));
     if (p->persistent) nside = std::min(kSide, (int)p->pgroups.size() - 1);  // one branch per launch
     hipError_t e = hipSuccess;
     for (int k = 0; k < nside && e == hipSuccess; ++k) e = hipStreamCreateWithFlags(&side[k], hipStreamNonBlocking);

@@ -16,6 +16,9 @@ struct Filter {
   float h[kMaxTaps];  // low-pass (scaling) filter
   float g[kMaxTaps];  // high-pass g[t] = (-1)^t h[L-1-t]
 };
+struct FilterBank {  // of 2, 4 .. kMaxTaps taps
+  Filter f[kMaxTaps / 2];
+};
 
 // Work of one instance group for one kernel launch.  A group is `batch` instances with the
 // same geometry whose arrays sit `bs_*` elements apart.  Dims are padded to three:
@@ -48,6 +51,7 @@ struct Task {
   int32_t tiles_per_inst;
   int32_t tile_begin;  // first work-group index of this task within the launch
   int32_t flags;       // kNorm*: squared-norm mode of the full-bank analysis kernels
+  int32_t taps;        // filter length (read by launches that hold several)
 };
 // Squared-norm mode (FB_DOWN / FB_DOWN_S / full-bank coarse analysis): the weighted coefficients
 // are summed as squares instead of stored; each work-group writes its partial sum, a compensated
@@ -86,6 +90,7 @@ struct TailTask {
   int32_t tile_begin;
   int32_t dense;     // 2-D LP: coarse level from which the block (at most 32 x 32 samples) goes through
                      // matrix products; -1: none
+  int32_t taps;      // filter length (read by launches that hold several)
 };
 
 struct TailArgs {
@@ -121,11 +126,18 @@ struct TileShape {
              // full-res for synthesis kinds); padded dims are 1
 };
 
-// Launchers (kernels.hip).  All return hipError_t of the launch.
+// Launchers (kernels.hip).  All return hipError_t of the launch.  taps = kMixedTaps: a table launch of
+// instances of different filter lengths (2-D low-pass kinds); f is then the first filter of a FilterBank.
+constexpr int kMixedTaps = 0;
 hipError_t launch_level(int kind, int ndim, int taps, int variant, const TaskArgs& args, int grid,
                         const Filter& f, hipStream_t stream);
 hipError_t launch_tail(int kind, int ndim, int taps, const TailArgs& args, int grid, size_t lds_bytes,
                        const Filter& f, hipStream_t stream);
+// Their launches of several filter lengths (mixed.hip).
+hipError_t launch_mixed_level(int kind, int variant, const TaskArgs& args, int grid, const FilterBank& bank,
+                              hipStream_t stream);
+hipError_t launch_mixed_coarse(const TailArgs& args, int grid, size_t lds_bytes, const FilterBank& bank,
+                               hipStream_t stream);
 // Largest block (floats) the low-pass coarse-level kernel (tail kind 3) holds in LDS: the small
 // instantiation (32 KB of LDS) and the large one (128 KB: one work-group per CU), used when a call
 // has so few instances that its level kernels could not fill the chip anyway.
