@@ -142,10 +142,12 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
     }
   }
   const int base2 = 2 * o2 - (L - 2), a2 = base2 - SH;
-  // rows start at multiples of 4 floats (and so do instances): 16-byte loads inside the row
-  const bool vec = ((t.si[0] | t.si[1] | t.bs_in) & 3) == 0 && a2 >= 0 && a2 + 4 * NVL <= n2;
+  // rows start at multiples of 4 floats (and so do instances): 16-byte loads of the groups [ga, gb) inside
+  // the row; the columns before and after them go through the table one by one
+  const bool vec = ((t.si[0] | t.si[1] | t.bs_in) & 3) == 0 && n2 >= 4;
+  const int ga = a2 >= 0 ? 0 : min(-a2 / 4, NVL), gb = max(min((n2 - a2) >> 2, NVL), ga);
   const bool inner = base2 >= 0 && base2 + I2 <= n2;
-  if (!inner)
+  if (!inner || ga > 0 || gb < NVL)
     for (int i = threadIdx.x; i < I2; i += NT) {
       const int j = base2 + i;
       s_x2[i] = ZX ? (j >= 0 && j < n2 ? j : -1) : sym_ix(j, n2);
@@ -153,19 +155,30 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
   __syncthreads();
   if (vec) {
     // 16-byte loads from the aligned start a2 (row offsets are multiples of 4), all issued before
-    // the first LDS store; group v of a row lands at LDS positions 4v - SH .. 4v - SH + 3
+    // the first LDS store; group v of a row lands at LDS positions 4v - SH .. 4v - SH + 3.  Groups outside
+    // the row load its nearest group and store nothing.
+    const int last = (n2 & ~3) - 4;
     float4 v[ITL];
 #pragma unroll
     for (int it = 0; it < ITL; ++it) {
       const int q = min(int(threadIdx.x) + it * NT, NLD - 1);
       const int r = q / NVL, g = q - r * NVL;
-      v[it] = !ZX || s_row[r] >= 0 ? gld4(src + s_row[r] + a2 + 4 * g) : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[it] = !ZX || s_row[r] >= 0 ? gld4(src + s_row[r] + min(max(a2 + 4 * g, 0), last)) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (ga > 0 || gb < NVL) {
+      // columns [0, il) and [ir, I2) of every row, 16 lanes a row
+      const int il = max(4 * ga - SH, 0), ir = max(min(4 * gb - SH, I2), il), nout = il + I2 - ir;
+      for (int r = threadIdx.x / 16; r < NROW; r += NT / 16)
+        for (int j = threadIdx.x % 16; j < nout; j += 16) {
+          const int i = j < il ? j : ir + j - il, c = s_x2[i];
+          s_in[r * I2P + i] = !ZX || (s_row[r] >= 0 && c >= 0) ? gld(src + s_row[r] + c) : 0.f;
+        }
     }
 #pragma unroll
     for (int it = 0; it < ITL; ++it) {
       const int q = int(threadIdx.x) + it * NT;
-      if (q < NLD) {
-        const int r = q / NVL, g = q - r * NVL;
+      const int r = q / NVL, g = q - r * NVL;
+      if (q < NLD && g >= ga && g < gb) {
         float* row = s_in + r * I2P;
         if constexpr (SH == 0) {
           *reinterpret_cast<float4*>(row + 4 * g) = v[it];
