@@ -237,14 +237,15 @@ DEVI void lds_window(const float* base16, float* w) {
 
 // Contiguous-dim analysis of NROW staged rows, results written back over the staging buffer
 // as rows of T2 (FB: [lo T2 | hi T2]) floats.  Each task is P consecutive outputs of one row;
-// a thread holds its results in registers across the barrier that frees the buffer.
-template <int L, int P, int NROW, int T2, int I2P, int NT, bool FB>
+// a thread holds its results in registers across the barrier that frees the buffer.  OFF: position of the
+// first sample in a row (the 16-byte reads stay aligned).
+template <int L, int P, int NROW, int T2, int I2P, int NT, bool FB, int OFF = 0>
 DEVI void row_pass_inplace(float* s_in, const Filter& f) {
   constexpr int NCH = T2 / P;
   constexpr int NTASK = NROW * NCH;
   constexpr int IT = (NTASK + NT - 1) / NT;
   constexpr int W = 2 * P + L - 2;
-  constexpr int W4 = (W + 3) / 4;
+  constexpr int W4 = (OFF + W + 3) / 4;
   constexpr int OUTW = FB ? 2 * T2 : T2;
   static_assert(NROW * OUTW <= NROW * I2P, "row results must fit in the staging buffer");
   float lo[IT][P], hi[FB ? IT : 1][P];
@@ -259,14 +260,17 @@ DEVI void row_pass_inplace(float* s_in, const Filter& f) {
       for (int v = 0; v < W4; ++v) {
         const float4 x = p[v];
         win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
+        // the samples before the window count as read: left out, the compiler reads 8-byte halves, which
+        // conflict (64 x 1024^2, 16 taps, the finest non-periodic level: 96 -> 113 us instead of 93)
+        if (OFF > 0 && v == 0) asm volatile("" : : "v"(x.x), "v"(x.y));
       }
 #pragma unroll
       for (int q = 0; q < P; ++q) {
         float a = 0.f, d = 0.f;
 #pragma unroll
         for (int t = 0; t < L; ++t) {
-          a = fmaf(f.h[t], win[2 * q + t], a);
-          if (FB) d = fmaf(f.g[t], win[2 * q + t], d);
+          a = fmaf(f.h[t], win[OFF + 2 * q + t], a);
+          if (FB) d = fmaf(f.g[t], win[OFF + 2 * q + t], d);
         }
         lo[it][q] = a;
         if (FB) hi[it][q] = d;

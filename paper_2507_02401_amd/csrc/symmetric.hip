@@ -101,13 +101,13 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
   constexpr int I0 = D >= 3 ? 2 * T0 + L - 2 : 1;
   constexpr int I1 = D >= 2 ? 2 * T1 + L - 2 : 1;
   constexpr int I2 = 2 * T2 + L - 2;
-  constexpr int I2P = (I2 + 3) & ~3;
+  // the window start 2 o_2 - (L - 2) is SH floats past a 16-byte boundary (T2 even), in memory and in LDS
+  constexpr int SH = (L - 2) & 3 ? 4 - ((L - 2) & 3) : 0;
+  constexpr int I2P = (SH + I2 + 3) & ~3;
   constexpr int NROW = I0 * I1;
   constexpr int NB = D >= 3 ? I0 * T1 * T2 : 1;
   constexpr int P1 = D >= 3 ? 2 : 4, P0 = 2;
-  // the window start 2 o_2 - (L - 2) is SH floats past a 16-byte boundary (T2 even)
-  constexpr int SH = (L - 2) & 3 ? 4 - ((L - 2) & 3) : 0;
-  constexpr int NVL = (SH + I2 + 3) / 4;  // 16-byte groups loaded per row
+  constexpr int NVL = I2P / 4;  // 16-byte groups per row
   constexpr int NLD = NROW * NVL, ITL = (NLD + NT - 1) / NT;
   static_assert(T2 % 4 == 0 && (D < 2 || T1 % P1 == 0) && (D < 3 || T0 % P0 == 0), "tile shape");
   static_assert(NROW * T2 + NB <= NROW * I2P, "axis-1 results must fit past the axis-2 rows");
@@ -155,8 +155,7 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
   __syncthreads();
   if (vec) {
     // 16-byte loads from the aligned start a2 (row offsets are multiples of 4), all issued before
-    // the first LDS store; group v of a row lands at LDS positions 4v - SH .. 4v - SH + 3.  Groups outside
-    // the row load its nearest group and store nothing.
+    // the first LDS store; groups outside the row load its nearest group and store nothing
     const int last = (n2 & ~3) - 4;
     float4 v[ITL];
 #pragma unroll
@@ -171,22 +170,14 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
       for (int r = threadIdx.x / 16; r < NROW; r += NT / 16)
         for (int j = threadIdx.x % 16; j < nout; j += 16) {
           const int i = j < il ? j : ir + j - il, c = s_x2[i];
-          s_in[r * I2P + i] = !ZX || (s_row[r] >= 0 && c >= 0) ? gld(src + s_row[r] + c) : 0.f;
+          s_in[r * I2P + SH + i] = !ZX || (s_row[r] >= 0 && c >= 0) ? gld(src + s_row[r] + c) : 0.f;
         }
     }
 #pragma unroll
     for (int it = 0; it < ITL; ++it) {
       const int q = int(threadIdx.x) + it * NT;
       const int r = q / NVL, g = q - r * NVL;
-      if (q < NLD && g >= ga && g < gb) {
-        float* row = s_in + r * I2P;
-        if constexpr (SH == 0) {
-          *reinterpret_cast<float4*>(row + 4 * g) = v[it];
-        } else {
-          if (g > 0) *reinterpret_cast<float2*>(row + 4 * g - 2) = make_float2(v[it].x, v[it].y);
-          if (4 * g + 2 <= I2P) *reinterpret_cast<float2*>(row + 4 * g) = make_float2(v[it].z, v[it].w);
-        }
-      }
+      if (q < NLD && g >= ga && g < gb) *reinterpret_cast<float4*>(s_in + r * I2P + 4 * g) = v[it];
     }
   } else {
     gather_to_lds<NT, 8>(
@@ -198,13 +189,13 @@ __global__ void __launch_bounds__(NT) k_sym_down(SymTask t, Filter f) {
         },
         [&](int e, float x) {
           const int r = e / I2;
-          s_in[r * I2P + e - r * I2] = x;
+          s_in[r * I2P + SH + e - r * I2] = x;
         });
   }
   __syncthreads();
 
   // axis 2: (NROW, I2) -> (NROW, T2), written back over the staging buffer
-  row_pass_inplace<L, 4, NROW, T2, I2P, NT, false>(s_in, f);
+  row_pass_inplace<L, 4, NROW, T2, I2P, NT, false, SH>(s_in, f);
 
   if constexpr (D == 1) {
     for (int k = threadIdx.x; k < T2; k += NT) {
