@@ -1265,129 +1265,191 @@ DEVI void fbc_synthesis_w(float* sm, int src, int dst, int S0, int S1, int b0, i
   }
 }
 
-// Register-window versions (as coarse_analysis_v / coarse_synthesis_v, for the strided packed
-// layout of the full bank: low half at k, high half at half + k along the axis).
-template <int L>
-DEVI void fbc_analysis_v(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
-  constexpr int PO = 4, WN = 2 * PO + L - 2, W4 = (WN + 3) / 4;
-  const int n = ax == 0 ? b0 : (ax == 1 ? b1 : b2), half = n >> 1;
-  const int p0 = ax == 0 ? half / PO : b0, p1 = ax == 1 ? half / PO : b1, p2 = ax == 2 ? half / PO : b2;
-  const int l1 = ilog2_or_neg(p1), l2 = ilog2_or_neg(p2);
-  const int step = ax == 0 ? S0 : (ax == 1 ? S1 : 1);
-  const int total = p0 * p1 * p2;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    int c0, c1, c2;
-    split3(e, p1, p2, l1, l2, c0, c1, c2);
-    const int k0 = PO * (ax == 0 ? c0 : (ax == 1 ? c1 : c2));
-    const int other = (ax == 0 ? 0 : c0 * S0) + (ax == 1 ? 0 : c1 * S1) + (ax == 2 ? 0 : c2);
+// Lean passes (as those of the low-pass coarse kernel) for the strided packed layout of the full bank: low
+// half at k, high half at half + k along the axis.  A thread keeps its place along the contiguous direction
+// and steps along the other one; windows are 16-byte vectors along the contiguous axis and four columns
+// per lane along the strided ones; per output the taps are summed in the order of the _w versions.  A pass
+// is bound by issued instructions and by the barrier after it.  One block of a launch alone, us, against
+// passes that split and wrapped every index: 64^2 16 taps 11.8 -> 10.5; 16^3 8 taps 8.6 -> 7.1 and back
+// 8.7 -> 8.2; calls, 64 blocks of 64^2, 16 taps 16.4 -> 14.4 and back 14.8 -> 12.8, 16 of 80 x 96 back 16.2 -> 12.4.
+
+// axis 2 of `lines` rows (line l = (c0, c1) at c0 S0 + c1 S1); n / 2, S0 and S1 multiples of 4
+template <int D, int L, int NT>
+DEVI void fbc_rows_down(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int n, const Filter& f) {
+  constexpr int PO = 4, W4 = (2 * PO + L - 2 + 3) / 4;
+  const int half = n >> 1, nch = half / PO, lg = ceil_log2(nch), lines = b0 * b1;
+  const int ch = threadIdx.x & ((1 << lg) - 1), l0 = threadIdx.x >> lg;
+  if (ch >= nch) return;
+  int off[W4];
+#pragma unroll
+  for (int v = 0; v < W4; ++v) {
+    const int i = 2 * PO * ch + 4 * v;
+    off[v] = i >= n ? i - n : i;
+  }
+  for (int l = l0; l < lines; l += NT >> lg) {
+    const int base = D < 3 ? l * S1 : (l / b1) * S0 + (l % b1) * S1;
     float win[4 * W4];
-    if (ax == 2) {
 #pragma unroll
-      for (int v = 0; v < W4; ++v) {
-        int i = 2 * k0 + 4 * v;
-        i = i >= n ? i - n : i;
-        const float4 x = *reinterpret_cast<const float4*>(sm + src + other + i);
-        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
-      }
-    } else {
-      const int a0 = src + other + 2 * k0 * step, a0w = a0 - n * step, wrap = n - 2 * k0;
-#pragma unroll
-      for (int j = 0; j < WN; ++j) win[j] = sm[(j >= wrap ? a0w : a0) + j * step];
+    for (int v = 0; v < W4; ++v) {
+      const float4 x = *reinterpret_cast<const float4*>(sm + src + base + off[v]);
+      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
     }
+    float lo[PO], hi[PO];
 #pragma unroll
     for (int q = 0; q < PO; ++q) {
-      float lo = 0.f, hi = 0.f;
+      lo[q] = hi[q] = 0.f;
 #pragma unroll
       for (int t = 0; t < L; ++t) {
-        lo = fmaf(f.h[t], win[2 * q + t], lo);
-        hi = fmaf(f.g[t], win[2 * q + t], hi);
+        lo[q] = fmaf(f.h[t], win[2 * q + t], lo[q]);
+        hi[q] = fmaf(f.g[t], win[2 * q + t], hi[q]);
       }
-      sm[dst + other + (k0 + q) * step] = lo;
-      sm[dst + other + (half + k0 + q) * step] = hi;
     }
+    float* o = sm + dst + base + PO * ch;
+    *reinterpret_cast<float4*>(o) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+    *reinterpret_cast<float4*>(o + half) = make_float4(hi[0], hi[1], hi[2], hi[3]);
   }
 }
 
-template <int L>
-DEVI void fbc_synthesis_v(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
-  constexpr int H = L / 2, PO = 8, A = (H - 1 + 3) & ~3, WN = A + 4, W4 = WN / 4;
-  const int n = ax == 0 ? b0 : (ax == 1 ? b1 : b2), half = n >> 1;
-  const int p0 = ax == 0 ? b0 / PO : b0, p1 = ax == 1 ? b1 / PO : b1, p2 = ax == 2 ? b2 / PO : b2;
-  const int l1 = ilog2_or_neg(p1), l2 = ilog2_or_neg(p2);
-  const int step = ax == 0 ? S0 : (ax == 1 ? S1 : 1);
-  const int total = p0 * p1 * p2;
-  for (int e = threadIdx.x; e < total; e += blockDim.x) {
-    int c0, c1, c2;
-    split3(e, p1, p2, l1, l2, c0, c1, c2);
-    const int q0 = (PO / 2) * (ax == 0 ? c0 : (ax == 1 ? c1 : c2));
-    const int other = (ax == 0 ? 0 : c0 * S0) + (ax == 1 ? 0 : c1 * S1) + (ax == 2 ? 0 : c2);
-    float lo[WN], hi[WN];
-    if (ax == 2) {
+// an axis of stride `step` and length n, for `outer` positions of the other strided axis (stride So) and
+// `inner` columns; inner and the strides multiples of 4
+template <int L, int NT>
+DEVI void fbc_cols_down(float* sm, int src, int dst, int step, int n, int So, int outer, int inner, const Filter& f) {
+  const int half = n >> 1;
+  const ColItems it = col_items<NT>(inner);
+  if (it.c < 0) return;
+  for (int p = it.p; p < outer * half; p += it.ps) {
+    const int q = outer == 1 ? 0 : p / half, k = p - q * half, wrap = n - 2 * k;
+    const float* in = sm + src + q * So + 2 * k * step + it.c;
+    float4 win[L];
 #pragma unroll
-      for (int v = 0; v < W4; ++v) {
-        int k = q0 - A + 4 * v;
-        k = k < 0 ? k + half : k;
-        const float4 x = *reinterpret_cast<const float4*>(sm + src + other + k);
-        const float4 y = *reinterpret_cast<const float4*>(sm + src + other + half + k);
-        lo[4 * v] = x.x; lo[4 * v + 1] = x.y; lo[4 * v + 2] = x.z; lo[4 * v + 3] = x.w;
-        hi[4 * v] = y.x; hi[4 * v + 1] = y.y; hi[4 * v + 2] = y.z; hi[4 * v + 3] = y.w;
-      }
-    } else {
-      const int a0 = src + other + (q0 - A) * step, a0w = a0 + half * step, hs = half * step;
+    for (int j = 0; j < L; ++j) win[j] = *reinterpret_cast<const float4*>(in + (j >= wrap ? j - n : j) * step);
+    float4 lo = make_float4(0.f, 0.f, 0.f, 0.f), hi = lo;
 #pragma unroll
-      for (int j = 0; j < WN; ++j) {
-        const int a = (q0 - A + j < 0 ? a0w : a0) + j * step;
-        lo[j] = sm[a];
-        hi[j] = sm[a + hs];
-      }
+    for (int j = 0; j < L; ++j) {
+      lo = axpy4(f.h[j], win[j], lo);
+      hi = axpy4(f.g[j], win[j], hi);
     }
+    float* o = sm + dst + q * So + k * step + it.c;
+    *reinterpret_cast<float4*>(o) = lo;
+    *reinterpret_cast<float4*>(o + half * step) = hi;
+  }
+}
+
+template <int D, int L, int NT>
+DEVI void fbc_rows_up(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int n, const Filter& f) {
+  constexpr int H = L / 2, PO = 4, A = (H - 1 + 3) & ~3, NW = (A + PO) / 4;
+  const int half = n >> 1, nch = half / PO, lg = ceil_log2(nch), lines = b0 * b1;
+  const int ch = threadIdx.x & ((1 << lg) - 1), l0 = threadIdx.x >> lg;
+  if (ch >= nch) return;
+  int off[NW];
 #pragma unroll
-    for (int r = 0; r < PO; ++r) {
-      const int par = r & 1, qq = r >> 1;  // output 2 (q0 + qq) + par
-      float acc = 0.f;
+  for (int v = 0; v < NW; ++v) {
+    const int k = PO * ch - A + 4 * v;
+    off[v] = k < 0 ? k + half : k;
+  }
+  for (int l = l0; l < lines; l += NT >> lg) {
+    const int base = D < 3 ? l * S1 : (l / b1) * S0 + (l % b1) * S1;
+    float lo[A + PO], hi[A + PO];
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+      const float4 x = *reinterpret_cast<const float4*>(sm + src + base + off[v]);
+      const float4 y = *reinterpret_cast<const float4*>(sm + src + base + half + off[v]);
+      lo[4 * v] = x.x; lo[4 * v + 1] = x.y; lo[4 * v + 2] = x.z; lo[4 * v + 3] = x.w;
+      hi[4 * v] = y.x; hi[4 * v + 1] = y.y; hi[4 * v + 2] = y.z; hi[4 * v + 3] = y.w;
+    }
+    float v[2 * PO];
+#pragma unroll
+    for (int r = 0; r < 2 * PO; ++r) {
+      v[r] = 0.f;
 #pragma unroll
       for (int j = 0; j < H; ++j) {
-        acc = fmaf(f.h[2 * j + par], lo[A + qq - j], acc);
-        acc = fmaf(f.g[2 * j + par], hi[A + qq - j], acc);
+        v[r] = fmaf(f.h[2 * j + (r & 1)], lo[A + (r >> 1) - j], v[r]);
+        v[r] = fmaf(f.g[2 * j + (r & 1)], hi[A + (r >> 1) - j], v[r]);
       }
-      sm[dst + other + (2 * q0 + r) * step] = acc;
     }
+    float4* o = reinterpret_cast<float4*>(sm + dst + base + 2 * PO * ch);
+    o[0] = make_float4(v[0], v[1], v[2], v[3]);
+    o[1] = make_float4(v[4], v[5], v[6], v[7]);
   }
 }
 
-template <int L>
+template <int L, int NT>
+DEVI void fbc_cols_up(float* sm, int src, int dst, int step, int n, int So, int outer, int inner, const Filter& f) {
+  constexpr int H = L / 2;
+  const int half = n >> 1;
+  const ColItems it = col_items<NT>(inner);
+  if (it.c < 0) return;
+  for (int p = it.p; p < outer * half; p += it.ps) {
+    const int q = outer == 1 ? 0 : p / half, k = p - q * half;
+    const float* in = sm + src + q * So + k * step + it.c;
+    float4 lo[H], hi[H];
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      const float* x = in - (j > k ? j - half : j) * step;
+      lo[j] = *reinterpret_cast<const float4*>(x);
+      hi[j] = *reinterpret_cast<const float4*>(x + half * step);
+    }
+    float4 e0 = make_float4(0.f, 0.f, 0.f, 0.f), e1 = e0;
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      e0 = axpy4(f.g[2 * j], hi[j], axpy4(f.h[2 * j], lo[j], e0));
+      e1 = axpy4(f.g[2 * j + 1], hi[j], axpy4(f.h[2 * j + 1], lo[j], e1));
+    }
+    float* o = sm + dst + q * So + 2 * k * step + it.c;
+    *reinterpret_cast<float4*>(o) = e0;
+    *reinterpret_cast<float4*>(o + step) = e1;
+  }
+}
+
+// Whether the lean pass of an axis takes a block: whole vectors, and columns (or chunks) within the threads.
+DEVI bool fbc_lean(int src, int dst, int S0, int S1, int n, int b2, int ax, int nt) {
+  if ((src | dst | S0 | S1) & 3) return false;
+  return ax == 2 ? (n >> 1) % 4 == 0 && n <= 8 * nt : b2 % 4 == 0 && b2 <= 4 * nt;
+}
+
+template <int D, int L>
 DEVI void fbc_analysis(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
+  constexpr int NT = kFbCoarseThreads;
   const int n = ax == 0 ? b0 : (ax == 1 ? b1 : b2);
-  if (n >= L && (n >> 1) % 4 == 0 && (ax != 2 || (src % 4 == 0 && S1 % 4 == 0 && S0 % 4 == 0)))
-    fbc_analysis_v<L>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
-  else if (n >= L) fbc_analysis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
-  else fbc_analysis_w<L, true>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  if (n < L) return fbc_analysis_w<L, true>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  if (!fbc_lean(src, dst, S0, S1, n, b2, ax, NT)) return fbc_analysis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  if (ax == 2) return fbc_rows_down<D, L, NT>(sm, src, dst, S0, S1, b0, b1, n, f);
+  fbc_cols_down<L, NT>(sm, src, dst, ax == 1 ? S1 : S0, n, ax == 1 ? S0 : S1, ax == 1 ? b0 : b1, b2, f);
 }
-template <int L>
+template <int D, int L>
 DEVI void fbc_synthesis(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
-  const int half = (ax == 0 ? b0 : (ax == 1 ? b1 : b2)) >> 1;
-  if (half >= L / 2 && half % 4 == 0 && (ax != 2 || (src % 4 == 0 && S1 % 4 == 0 && S0 % 4 == 0)))
-    fbc_synthesis_v<L>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
-  else if (half >= L / 2) fbc_synthesis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
-  else fbc_synthesis_w<L, true>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  constexpr int NT = kFbCoarseThreads;
+  const int n = ax == 0 ? b0 : (ax == 1 ? b1 : b2);
+  if ((n >> 1) < L / 2) return fbc_synthesis_w<L, true>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  if (!fbc_lean(src, dst, S0, S1, n, b2, ax, NT)) return fbc_synthesis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  if (ax == 2) return fbc_rows_up<D, L, NT>(sm, src, dst, S0, S1, b0, b1, n, f);
+  fbc_cols_up<L, NT>(sm, src, dst, ax == 1 ? S1 : S0, n, ax == 1 ? S0 : S1, ax == 1 ? b0 : b1, b2, f);
 }
 
-// Weight of the packed-pyramid element at (c0,c1,c2) of a coarse block: detail of coarse
-// level j -> coef[j]; approximation (inside the block >> nlev) -> coef[nlev].
-DEVI float fbc_weight(const float* coef, int nlev, int n0, int n1, int n2, int c0, int c1, int c2, int D) {
-  int j = 0;
-  while (j < nlev) {
-    const int sh = j + 1;
-    const bool inside = (c2 < (n2 >> sh)) && (D < 2 || c1 < (n1 >> sh)) && (D < 3 || c0 < (n0 >> sh));
-    if (!inside) break;
-    ++j;
+// Weight of the packed-pyramid element at (c0,c1,c2) of a coarse block: detail of coarse level j -> coef[j];
+// approximation (inside the block >> nlev) -> coef[nlev].  Per axis the levels that hold a coordinate
+// (c < n >> 1, c < n >> 2, ..) are counted once into a table; the element's level is the axes' minimum.
+struct FbcWeights {
+  uint8_t lev[kFbCoarseMax + 8];  // tables of axes 0, 1, 2, one after the other (sides of a block of kFbCoarseMax)
+  float coef[33];
+};
+template <int D>
+DEVI void fbc_weight_tables(FbcWeights& w, const float* coef, int nlev, int n0, int n1, int n2) {
+  for (int e = threadIdx.x; e < n0 + n1 + n2; e += kFbCoarseThreads) {
+    const int ax = e < n0 ? 0 : (e < n0 + n1 ? 1 : 2);
+    const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), c = ax == 0 ? e : (ax == 1 ? e - n0 : e - n0 - n1);
+    int j = 0;
+    if (ax < 3 - D) j = nlev;
+    else while (j < nlev && c < (n >> (j + 1))) ++j;
+    w.lev[e] = (uint8_t)j;
   }
-  return coef[j];
+  for (int j = threadIdx.x; j <= nlev; j += kFbCoarseThreads) w.coef[j] = coef[j];
 }
 
 template <int D, int L, bool SYN>
 __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, Filter f) {
   __shared__ __attribute__((aligned(16))) float sm[2 * kFbCoarseMax];
+  __shared__ FbcWeights wt;
   const int wg = logical_wg(args.total_wg);
   if (wg < 0) return;
   int ti = 0;
@@ -1419,23 +1481,43 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
       sm[CUR + o] = sm[TMP + o];
     }
   };
-  constexpr int U = kFbCoarseMax / kFbCoarseThreads;
+  constexpr int U = kFbCoarseMax / kFbCoarseThreads, U4 = U / 4;
+  // element e of the block: its place in the strided block and its weight
+  auto place = [&](int e, int s0, int s1, float* w) {
+    int c0, c1, c2;
+    split3(e, n1, n2, l1, l2, c0, c1, c2);
+    *w = wt.coef[min(min((int)wt.lev[c0], (int)wt.lev[n0 + c1]), (int)wt.lev[n0 + n1 + c2])];
+    return (D >= 3 ? c0 * s0 : 0) + (D >= 2 ? c1 * s1 : 0) + c2;
+  };
+  // four elements e .. e + 3 of one row (n2 a multiple of 4)
+  auto place4 = [&](int e, int s0, int s1, float4* w) {
+    int c0, c1, c2;
+    split3(e, n1, n2, l1, l2, c0, c1, c2);
+    const int r = min((int)wt.lev[c0], (int)wt.lev[n0 + c1]);
+    const uint8_t* t = wt.lev + n0 + n1 + c2;
+    *w = make_float4(wt.coef[min(r, (int)t[0])], wt.coef[min(r, (int)t[1])], wt.coef[min(r, (int)t[2])],
+                     wt.coef[min(r, (int)t[3])]);
+    return (D >= 3 ? c0 * s0 : 0) + (D >= 2 ? c1 * s1 : 0) + c2;
+  };
+  const float* gl = SYN ? in : out;  // the strided block
+  const int gs0 = SYN ? in0 : out0, gs1 = SYN ? in1 : out1;
+  const bool rows4 = (n2 & 3) == 0 && ((uintptr_t)gl & 15) == 0 && (D < 2 || (gs1 & 3) == 0) && (D < 3 || (gs0 & 3) == 0);
   if (!SYN) {
-    gather_to_lds<kFbCoarseThreads, U>(
-        B, [&](int e) { return gld(in + e); }, [&](int e, float v) { sm[CUR + e] = v; });
+    block_to_lds<kFbCoarseThreads, kFbCoarseMax>(in, sm + CUR, B,
+                                                 [&] { fbc_weight_tables<D>(wt, tp->coef, nl, n0, n1, n2); });
     __syncthreads();
     for (int j = 0; j < nl; ++j) {
       const int b0 = D >= 3 ? n0 >> j : 1, b1 = D >= 2 ? n1 >> j : 1, b2 = n2 >> j;
       // dim 2: CUR -> TMP, dim 1: TMP -> CUR, dim 0: CUR -> TMP
-      fbc_analysis<L>(sm, CUR, TMP, S0, S1, b0, b1, b2, 2, f);
+      fbc_analysis<D, L>(sm, CUR, TMP, S0, S1, b0, b1, b2, 2, f);
       __syncthreads();
       bool in_tmp = true;
       if (D >= 2) {
-        fbc_analysis<L>(sm, TMP, CUR, S0, S1, b0, b1, b2, 1, f);
+        fbc_analysis<D, L>(sm, TMP, CUR, S0, S1, b0, b1, b2, 1, f);
         __syncthreads();
         in_tmp = false;
         if (D >= 3) {
-          fbc_analysis<L>(sm, CUR, TMP, S0, S1, b0, b1, b2, 0, f);
+          fbc_analysis<D, L>(sm, CUR, TMP, S0, S1, b0, b1, b2, 0, f);
           __syncthreads();
           in_tmp = true;
         }
@@ -1447,54 +1529,85 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
     }
     const bool norm = (tp->flags & kNormSq) != 0;
     KSum nsq;
-    for (int e = threadIdx.x; e < B; e += blockDim.x) {
-      int c0, c1, c2;
-      split3(e, n1, n2, l1, l2, c0, c1, c2);
-      const float w = fbc_weight(tp->coef, nl, n0, n1, n2, c0, c1, c2, D);
-      const float v = w * sm[CUR + e];
-      if (norm) nsq.add(v * v);
-      else gst(out + (D >= 3 ? c0 * out0 : 0) + (D >= 2 ? c1 * out1 : 0) + c2, v);
+    if (rows4 || (norm && (n2 & 3) == 0)) {
+      for (int e = 4 * threadIdx.x; e < B; e += 4 * kFbCoarseThreads) {
+        float4 w;
+        const int o = place4(e, out0, out1, &w);
+        const float4 x = *reinterpret_cast<const float4*>(sm + CUR + e);
+        const float4 v = make_float4(w.x * x.x, w.y * x.y, w.z * x.z, w.w * x.w);
+        if (norm) {
+          nsq.add(v.x * v.x); nsq.add(v.y * v.y); nsq.add(v.z * v.z); nsq.add(v.w * v.w);
+        } else {
+          gst4(out + o, v);
+        }
+      }
+    } else {
+      for (int e = threadIdx.x; e < B; e += kFbCoarseThreads) {
+        float w;
+        const int o = place(e, out0, out1, &w);
+        const float v = w * sm[CUR + e];
+        if (norm) nsq.add(v * v);
+        else gst(out + o, v);
+      }
     }
     if (norm) store_wg_sum<kFbCoarseThreads>(nsq, reinterpret_cast<float2*>(tp->out) + inst);
   } else {
-    gather_to_lds<kFbCoarseThreads, U>(
-        B,
-        [&](int e) {
-          int c0, c1, c2;
-          split3(e, n1, n2, l1, l2, c0, c1, c2);
-          return gld(in + (D >= 3 ? c0 * in0 : 0) + (D >= 2 ? c1 * in1 : 0) + c2);
-        },
-        [&](int e, float v) {
-          int c0, c1, c2;
-          split3(e, n1, n2, l1, l2, c0, c1, c2);
-          sm[CUR + e] = fbc_weight(tp->coef, nl, n0, n1, n2, c0, c1, c2, D) * v;
-        });
+    fbc_weight_tables<D>(wt, tp->coef, nl, n0, n1, n2);
+    if (rows4) {
+      float4 v[U4];
+#pragma unroll
+      for (int u = 0; u < U4; ++u) {
+        const int e = 4 * (int(threadIdx.x) + u * kFbCoarseThreads);
+        int c0, c1, c2;
+        split3(min(e, B - 4), n1, n2, l1, l2, c0, c1, c2);
+        v[u] = gld4(in + (D >= 3 ? c0 * in0 : 0) + (D >= 2 ? c1 * in1 : 0) + c2);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < U4; ++u) {
+        const int e = 4 * (int(threadIdx.x) + u * kFbCoarseThreads);
+        if (e < B) {
+          float4 w;
+          place4(e, in0, in1, &w);
+          *reinterpret_cast<float4*>(sm + CUR + e) = make_float4(w.x * v[u].x, w.y * v[u].y, w.z * v[u].z, w.w * v[u].w);
+        }
+      }
+    } else {
+      __syncthreads();
+      gather_to_lds<kFbCoarseThreads, U>(
+          B, [&](int e) { float w; return gld(in + place(e, in0, in1, &w)); },
+          [&](int e, float v) { float w; place(e, in0, in1, &w); sm[CUR + e] = w * v; });
+    }
     __syncthreads();
     for (int j = nl - 1; j >= 0; --j) {
       const int b0 = D >= 3 ? n0 >> j : 1, b1 = D >= 2 ? n1 >> j : 1, b2 = n2 >> j;
       // dim 0 (3-D), dim 1, dim 2, ping-pong starting from CUR
       int a = CUR, bb = TMP;
       if (D >= 3) {
-        fbc_synthesis<L>(sm, a, bb, S0, S1, b0, b1, b2, 0, f);
+        fbc_synthesis<D, L>(sm, a, bb, S0, S1, b0, b1, b2, 0, f);
         __syncthreads();
         const int t = a; a = bb; bb = t;
       }
       if (D >= 2) {
-        fbc_synthesis<L>(sm, a, bb, S0, S1, b0, b1, b2, 1, f);
+        fbc_synthesis<D, L>(sm, a, bb, S0, S1, b0, b1, b2, 1, f);
         __syncthreads();
         const int t = a; a = bb; bb = t;
       }
-      fbc_synthesis<L>(sm, a, bb, S0, S1, b0, b1, b2, 2, f);
+      fbc_synthesis<D, L>(sm, a, bb, S0, S1, b0, b1, b2, 2, f);
       __syncthreads();
       if (bb != CUR) {
         copy_back(b0, b1, b2);
         __syncthreads();
       }
     }
-    for (int e = threadIdx.x; e < B; e += blockDim.x) {
+    const bool st4 = (n2 & 3) == 0 && ((uintptr_t)out & 15) == 0 && (D < 2 || (out1 & 3) == 0) && (D < 3 || (out0 & 3) == 0);
+    const int ev = st4 ? 4 : 1;
+    for (int e = ev * threadIdx.x; e < B; e += ev * kFbCoarseThreads) {
       int c0, c1, c2;
       split3(e, n1, n2, l1, l2, c0, c1, c2);
-      gst(out + (D >= 3 ? c0 * out0 : 0) + (D >= 2 ? c1 * out1 : 0) + c2, sm[CUR + e]);
+      float* o = out + (D >= 3 ? c0 * out0 : 0) + (D >= 2 ? c1 * out1 : 0) + c2;
+      if (st4) gst4(o, *reinterpret_cast<const float4*>(sm + CUR + e));
+      else gst(o, sm[CUR + e]);
     }
   }
 }
