@@ -568,6 +568,14 @@ void set_orders(Schedule* sc) {
   if (n >= 2 && reverse_orders()) sc->launches[n - 1].reverse = sc->launches[0].reverse ^ 1;
 }
 
+// Flag of the finest 2-D synthesis level: outputs from 96 MB on are stored past the caches.  They would
+// displace what the call (and the next one's input) still has there, and are too large to stay for
+// a reader.  Calls with other inputs each time / the same input / a call on the result, 16 taps, us, stored as
+// usual -> past the caches: 192 MB 191.8 / 188.0 / 378.5 -> 182.8 / 171.5 / 365.2, 128 MB 142.7 / 132.4 / 280.7 ->
+// 139.8 / 125.8 / 270.2, but 64 MB 84.2 / 79.0 / 157.3 -> 79.5 / 79.6 / 162.9.  Not on the 3-D kernels, whose
+// 4-byte stores gain nothing.
+int32_t stream_out(int64_t floats) { return floats * 4 >= (int64_t)96 << 20 ? kStream : 0; }
+
 es_status build_schedule_raw(int op, const Geo& g, int64_t batch, const float* in, float* out, float* ws,
                              Schedule* sc) {
   sc->launches.clear();
@@ -695,6 +703,7 @@ es_status build_schedule_raw(int op, const Geo& g, int64_t batch, const float* i
       strides_of(d_o, l.task.st_out0);
       l.task.alpha = (float)(i == 0 ? w[1] : c[i]);
       l.task.beta = (!tail && i == m - 2) ? (float)c[m - 1] : 1.f;
+      if (i == 0 && D == 2) l.task.flags = stream_out(batch * N);
       finish_level(l, g);
       sc->launches.push_back(l);
     }

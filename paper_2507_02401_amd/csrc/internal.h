@@ -50,7 +50,7 @@ struct Task {
   int32_t ntile[3];
   int32_t tiles_per_inst;
   int32_t tile_begin;  // first work-group index of this task within the launch
-  int32_t flags;       // kNorm*: squared-norm mode of the full-bank analysis kernels
+  int32_t flags;       // kNorm*: squared-norm mode of the full-bank analysis kernels; kStream
   int32_t taps;        // filter length (read by launches that hold several)
 };
 // Squared-norm mode (FB_DOWN / FB_DOWN_S / full-bank coarse analysis): the weighted coefficients
@@ -59,6 +59,7 @@ struct Task {
 // (tail: ((float2*)out)[instance]).
 constexpr int32_t kNormSq = 1;   // detail bands are summed, not stored
 constexpr int32_t kNormLL = 2;   // the approximation output is final: summed, not stored
+constexpr int32_t kStream = 4;   // a level's final output (out0) is stored past the caches
 
 // Launch arguments: tasks either inline (count == 1) or in a device table.
 struct TaskArgs {

@@ -32,6 +32,20 @@ DEVI void gst4(float* p, float4 v) {
   *(GAS f4v*)p = w;
 }
 
+// Store of an output that the caches should not keep (see kStream).  The empty statements keep the compiler
+// from joining the two stores into a plain one.
+DEVI void gst4_if(bool stream, float* p, float4 v) {
+  if (stream) {
+    f4v w;
+    w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
+    asm volatile("" : : : "memory");
+    __builtin_nontemporal_store(w, (GAS f4v*)p);
+    asm volatile("" : : : "memory");
+  } else {
+    gst4(p, v);
+  }
+}
+
 // Load n (at most U * NT) elements into LDS with every load of a thread issued before the
 // first LDS store, so that one work-group keeps U loads per thread in flight.  src(e) gives
 // the element's value (a global load), dst(e) its LDS slot.

@@ -285,6 +285,7 @@ DEVI void lp_up_tile(const Task& t, int wg, const Filter& f, LpUpSmem<D, L, U0, 
     }
   }
   KSum cg_acc;
+  const bool stream = (t.flags & kStream) != 0;
 
   for (int i = threadIdx.x; i < G::NROW; i += NT) {
     const int i1 = i % G::J1, i0 = i / G::J1;
@@ -359,8 +360,8 @@ DEVI void lp_up_tile(const Task& t, int wg, const Filter& f, LpUpSmem<D, L, U0, 
                                             fmaf(alpha, s0.z, beta * e0.z), fmaf(alpha, s0.w, beta * e0.w));
               const float4 y1 = make_float4(fmaf(alpha, s1.x, beta * e1.x), fmaf(alpha, s1.y, beta * e1.y),
                                             fmaf(alpha, s1.z, beta * e1.z), fmaf(alpha, s1.w, beta * e1.w));
-              gst4(out + g1 * b2 + g2, y0);
-              gst4(out + (g1 + 1) * b2 + g2, y1);
+              gst4_if(stream, out + g1 * b2 + g2, y0);
+              gst4_if(stream, out + (g1 + 1) * b2 + g2, y1);
             }
           }
         }
