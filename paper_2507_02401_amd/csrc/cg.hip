@@ -9,8 +9,8 @@
 //
 // Every step runs on the device: the two operator applications per iteration are the library's
 // matern_cov_apply (smoothness -s and +s), the vector updates are fused element-wise kernels
-// that also produce per-work-group partial inner products, and one work-group per instance
-// reduces those partials in a fixed order and updates the instance's CG scalars.  All sums are
+// that also produce per-work-group partial inner products; the next launch's work-groups each sum
+// those partials in one fixed order and form the instance's CG scalars.  All sums are
 // FP32 with compensation (Neumaier) per thread and pairwise trees across threads; results are
 // deterministic.  The host looks at the residuals only every `check_every` iterations.
 #include <hip/hip_runtime.h>
