@@ -177,6 +177,17 @@ int dense_from(int D, const int b[3], int nlev) {
   return -1;
 }
 
+// Scale of the largest element that a block may hold for its matrix products (lp_coarse_block), from the
+// coefficients c_0 .. c_K of its levels.  The tables' rows have unit 2-norms (orthonormal filters, folded or not).
+// With A the largest magnitude in the block and c a bound of the coefficients, the sums of magnitudes are
+// then at most sqrt(32) A in T1 a, 32 A in (T1 a) T2^T, 32 c A in M, 4 * 32 c A in M T2 (rows of one level, at most 16)
+// and, over the rows of every level, (4 + sqrt(8) + 2 + sqrt(2)) * 128 c A + c A < 2^11 c A in the result.
+float dense_scale(const float* coef, int count) {
+  float c = 1.f;
+  for (int j = 0; j < count; ++j) c += std::fabs(coef[j]);  // not finite: every block takes the passes
+  return 2048.f * c;
+}
+
 int64_t align64(int64_t v) { return (v + 63) & ~(int64_t)63; }
 
 // Schedule mode of persistent plans (set around their schedule builds): every level launch uses
@@ -667,6 +678,7 @@ es_status build_schedule_raw(int op, const Geo& g, int64_t batch, const float* i
       t.coef[0] = (float)(T == 0 ? w[1] : c[T]);
       for (int j = 1; j <= K; ++j) t.coef[j] = (float)c[T + j];
       t.dense = dense_from(D, t.b, K);
+      if (t.dense >= 0) t.dense_scale = dense_scale(t.coef + t.dense, K - t.dense + 1);
       l.lds = tail_lds_bytes(3, D, t.b, K);  // selects the kernel's LDS size class
       // the kernel's LDS layout: pyramid A_0 .. A_K, then the temporaries (2-D: B/2; 3-D: B/2 + B/2) or, where
       // larger, the matrix products' two arrays, and those products' matrices and tables

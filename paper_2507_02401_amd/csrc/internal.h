@@ -92,6 +92,7 @@ struct TailTask {
   int32_t dense;     // 2-D LP: coarse level from which the block (at most 32 x 32 samples) goes through
                      // matrix products; -1: none
   int32_t taps;      // filter length (read by launches that hold several)
+  float dense_scale;  // an element whose product with it overflows keeps the block from the matrix products
 };
 
 struct TailArgs {

@@ -731,8 +731,10 @@ DEVI void coarse_synthesis(float* sm, int src, int dst, int n0, int n1, int n2, 
 // and T2 (s2 x n2), s = sum_i n / 2^i < n <= 32, that is four products of at most 32 x 32 x 32 on the matrix
 // cores, one 16 x 16 tile per wave:
 //   P = T1 a,  M = (P T2^T) on the blocks of equal level, times c_i,  Q = M T2,  z = c_0 a + T1^T Q.
-// FP32 products and sums throughout.  A block with an infinity or a NaN goes through the passes
-// instead, so that such values reach exactly the outputs that depend on them.
+// FP32 products and sums throughout.  Where an infinity or a NaN met the zeros of the tables, it would reach
+// every output of the block.  So a block that holds one, or a value so large that a product or sum
+// could overflow (dense_scale), goes through the passes instead, which keep it to the outputs that depend on
+// it.
 // Scratch of the dense levels: P (then Q) and M over the passes' temporaries, then T1, T2 and tables.  Rows
 // of kDenseRow floats: the 16 rows x 4 columns that a wave reads of a left factor hit distinct banks.
 struct DenseLds {
@@ -808,11 +810,11 @@ DEVI mfma_f4 dense_mul(const DenseOp& a, const DenseOp& b, int len) {
 }
 
 // z over a in place for the (n1, n2) block at sm[ao], K levels below it.  Returns false, with a unchanged,
-// where a holds a value that is not finite.  Ends with a barrier.  T1 and T2 are zero past s x n, a is
+// where a holds a value that is not finite or overflows times `scale`.  Ends with a barrier.  T1 and T2 are zero past s x n, a is
 // masked, and P, M and Q are written as whole tiles up to the inner lengths.  What a product takes from
 // the tables and from a is read before the barrier that its other factor waits for.
 template <int NT>
-DEVI bool coarse_dense(float* sm, const DenseLds& d, int ao, int n1, int n2, int K) {
+DEVI bool coarse_dense(float* sm, const DenseLds& d, int ao, int n1, int n2, int K, float scale) {
   constexpr int S = kDenseRow;
   const int s1 = n1 - (n1 >> K), s2 = n2 - (n2 >> K);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -831,11 +833,11 @@ DEVI bool coarse_dense(float* sm, const DenseLds& d, int ao, int n1, int n2, int
   if (tP) {
     DenseOp av = dense_get(sm + ao + hi * n2 + col, 4 * n2);
     const int rows = (col < n2 ? n1 : 0) - hi;
-    float zero = 0.f;  // NaN once a value is not finite
+    float zero = 0.f;  // NaN once a value is not finite or too large
 #pragma unroll
     for (int s = 0; s < kDenseSteps; ++s) {
       av.x[s] = 4 * s < rows ? av.x[s] : 0.f;
-      zero = fmaf(av.x[s], 0.f, zero);
+      zero = fmaf(av.x[s] * scale, 0.f, zero);
     }
     const mfma_f4 v = dense_mul(dense_get(sm + d.T1 + (r0 + lo) * S + hi, 4), av, n1);
 #pragma unroll
@@ -907,7 +909,7 @@ DEVI void lp_coarse_block(const TailTask* tp, int inst, const Filter& f, float* 
   int off = 0;
   for (int j = 0;; ++j) {
     if (D == 2 && j == Kd && Kd < K) {
-      if (coarse_dense<NT>(sm, dl, off, m1 >> j, m2 >> j, K - j)) break;
+      if (coarse_dense<NT>(sm, dl, off, m1 >> j, m2 >> j, K - j, tp->dense_scale)) break;
       Kd = K;
     }
     if (j == K) break;
