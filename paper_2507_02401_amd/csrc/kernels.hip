@@ -1171,8 +1171,8 @@ __global__ void __launch_bounds__(NT) k_fb_up(TaskArgs args, Filter f) {
 }
 
 template <int D, int L, int CMAX>
-__global__ void __launch_bounds__(kCoarseThreads) k_lp_coarse(TailArgs args, Filter f) {
-  __shared__ __attribute__((aligned(16))) float sm[coarse_lds_floats(CMAX)];
+__global__ void __launch_bounds__(coarse_threads(CMAX)) k_lp_coarse(TailArgs args, Filter f) {
+  __shared__ __attribute__((aligned(16))) float sm[coarse_lds_floats(D, CMAX)];
   const int wg = logical_wg(args.total_wg);
   if (wg < 0) return;
   int ti = 0;
@@ -1186,18 +1186,17 @@ __global__ void __launch_bounds__(kCoarseThreads) k_lp_coarse(TailArgs args, Fil
     ti = lo;
   }
   const TailTask* tp = args.table != nullptr ? args.table + ti : &args.t0;
-  lp_coarse_block<D, L, CMAX, kCoarseThreads>(tp, wg - tp->tile_begin, f, sm);
+  lp_coarse_block<D, L, CMAX, coarse_threads(CMAX)>(tp, wg - tp->tile_begin, f, sm);
 }
 
 // ---------------------------------------------------------------------------------------
 // FB_COARSE: the coarse levels of the full filter bank for one instance in one work-group.
-// The packed pyramid of a block of at most kFbCoarseMax floats lives in a static LDS array
+// The packed pyramid of a block of at most BMAX floats lives in a static LDS array
 // (two copies for ping-pong), addressed by integer offsets; level j works on the leading
 // sub-block (n_k >> j per axis).  SYN = false: analysis of levels T+1..m from a_T (contiguous
 // input) into the packed coefficient block (strided output, detail bands weighted).
 // SYN = true: synthesis from the packed block (strided input, weighted) down to a_T.
 
-constexpr int kFbCoarseMax = kFbCoarseMaxBlock;
 
 template <int L, bool SHORT>
 DEVI void fbc_analysis_w(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
@@ -1401,55 +1400,124 @@ DEVI void fbc_cols_up(float* sm, int src, int dst, int step, int n, int So, int 
   }
 }
 
+// Strided axes of blocks whose rows are no whole vectors: a thread forms four (two pairs of) outputs of one column
+// from one window.  33 blocks of 64 x 50, 12 taps, take 10.5 us with it and 13.0 with one output a thread.
+template <int L, int NT>
+DEVI void fbc_cols_down_1(float* sm, int src, int dst, int step, int n, int So, int outer, int inner, const Filter& f) {
+  constexpr int PO = 4, WN = 2 * PO + L - 2;
+  const int half = n >> 1, per = half / PO * inner;
+  for (int e = threadIdx.x; e < outer * per; e += NT) {
+    const int q = outer == 1 ? 0 : e / per, r = e - q * per, k0 = PO * (r / inner), c = r % inner;
+    const float* in = sm + src + q * So + 2 * k0 * step + c;
+    const int wrap = n - 2 * k0;
+    float win[WN];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) win[j] = in[(j >= wrap ? j - n : j) * step];
+    float* o = sm + dst + q * So + k0 * step + c;
+#pragma unroll
+    for (int p = 0; p < PO; ++p) {
+      float lo = 0.f, hi = 0.f;
+#pragma unroll
+      for (int t = 0; t < L; ++t) {
+        lo = fmaf(f.h[t], win[2 * p + t], lo);
+        hi = fmaf(f.g[t], win[2 * p + t], hi);
+      }
+      o[p * step] = lo;
+      o[(half + p) * step] = hi;
+    }
+  }
+}
+
+template <int L, int NT>
+DEVI void fbc_cols_up_1(float* sm, int src, int dst, int step, int n, int So, int outer, int inner, const Filter& f) {
+  constexpr int H = L / 2, PO = 4, WN = H - 1 + PO;  // half-resolution positions k0 - (H - 1) .. k0 + PO - 1
+  const int half = n >> 1, per = half / PO * inner;
+  for (int e = threadIdx.x; e < outer * per; e += NT) {
+    const int q = outer == 1 ? 0 : e / per, r = e - q * per, k0 = PO * (r / inner), c = r % inner;
+    const float* in = sm + src + q * So + c;
+    float lo[WN], hi[WN];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) {
+      const int k = k0 - (H - 1) + j;
+      const float* x = in + (k < 0 ? k + half : k) * step;
+      lo[j] = x[0];
+      hi[j] = x[half * step];
+    }
+    float* o = sm + dst + q * So + 2 * k0 * step + c;
+#pragma unroll
+    for (int p = 0; p < 2 * PO; ++p) {
+      float v = 0.f;
+#pragma unroll
+      for (int j = 0; j < H; ++j) {
+        v = fmaf(f.h[2 * j + (p & 1)], lo[H - 1 + (p >> 1) - j], v);
+        v = fmaf(f.g[2 * j + (p & 1)], hi[H - 1 + (p >> 1) - j], v);
+      }
+      o[p * step] = v;
+    }
+  }
+}
+
 // Whether the lean pass of an axis takes a block: whole vectors, and columns (or chunks) within the threads.
 DEVI bool fbc_lean(int src, int dst, int S0, int S1, int n, int b2, int ax, int nt) {
   if ((src | dst | S0 | S1) & 3) return false;
   return ax == 2 ? (n >> 1) % 4 == 0 && n <= 8 * nt : b2 % 4 == 0 && b2 <= 4 * nt;
 }
 
-template <int D, int L>
+template <int D, int L, int NT>
 DEVI void fbc_analysis(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
-  constexpr int NT = kFbCoarseThreads;
   const int n = ax == 0 ? b0 : (ax == 1 ? b1 : b2);
   if (n < L) return fbc_analysis_w<L, true>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
-  if (!fbc_lean(src, dst, S0, S1, n, b2, ax, NT)) return fbc_analysis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  const int step = ax == 1 ? S1 : S0, So = ax == 1 ? S0 : S1, outer = ax == 1 ? b0 : b1;
+  if (!fbc_lean(src, dst, S0, S1, n, b2, ax, NT)) {
+    if (D > 1 && NT <= 512 && ax != 2 && (n >> 1) % 4 == 0) return fbc_cols_down_1<L, NT>(sm, src, dst, step, n, So, outer, b2, f);
+    return fbc_analysis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  }
   if (ax == 2) return fbc_rows_down<D, L, NT>(sm, src, dst, S0, S1, b0, b1, n, f);
-  fbc_cols_down<L, NT>(sm, src, dst, ax == 1 ? S1 : S0, n, ax == 1 ? S0 : S1, ax == 1 ? b0 : b1, b2, f);
+  fbc_cols_down<L, NT>(sm, src, dst, step, n, So, outer, b2, f);
 }
-template <int D, int L>
+template <int D, int L, int NT>
 DEVI void fbc_synthesis(float* sm, int src, int dst, int S0, int S1, int b0, int b1, int b2, int ax, const Filter& f) {
-  constexpr int NT = kFbCoarseThreads;
   const int n = ax == 0 ? b0 : (ax == 1 ? b1 : b2);
   if ((n >> 1) < L / 2) return fbc_synthesis_w<L, true>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
-  if (!fbc_lean(src, dst, S0, S1, n, b2, ax, NT)) return fbc_synthesis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  const int step = ax == 1 ? S1 : S0, So = ax == 1 ? S0 : S1, outer = ax == 1 ? b0 : b1;
+  if (!fbc_lean(src, dst, S0, S1, n, b2, ax, NT)) {
+    if (D > 1 && NT <= 512 && ax != 2 && (n >> 1) % 4 == 0) return fbc_cols_up_1<L, NT>(sm, src, dst, step, n, So, outer, b2, f);
+    return fbc_synthesis_w<L, false>(sm, src, dst, S0, S1, b0, b1, b2, ax, f);
+  }
   if (ax == 2) return fbc_rows_up<D, L, NT>(sm, src, dst, S0, S1, b0, b1, n, f);
-  fbc_cols_up<L, NT>(sm, src, dst, ax == 1 ? S1 : S0, n, ax == 1 ? S0 : S1, ax == 1 ? b0 : b1, b2, f);
+  fbc_cols_up<L, NT>(sm, src, dst, step, n, So, outer, b2, f);
 }
 
 // Weight of the packed-pyramid element at (c0,c1,c2) of a coarse block: detail of coarse level j -> coef[j];
 // approximation (inside the block >> nlev) -> coef[nlev].  Per axis the levels that hold a coordinate
-// (c < n >> 1, c < n >> 2, ..) are counted once into a table; the element's level is the axes' minimum.
+// (c < n >> 1, c < n >> 2, ..) are counted once into a table; the element's level is the axes' minimum.  A 1-D
+// block would have a table of its own size: its elements count their levels themselves.
+DEVI int fbc_level(int c, int n, int nlev) {
+  int j = 0;
+  while (j < nlev && c < (n >> (j + 1))) ++j;
+  return j;
+}
+template <int D, int BMAX>
 struct FbcWeights {
-  uint8_t lev[kFbCoarseMax + 8];  // tables of axes 0, 1, 2, one after the other (sides of a block of kFbCoarseMax)
+  uint8_t lev[D > 1 ? BMAX / 2 + 8 : 1];  // tables of axes 0, 1, 2, one after the other (2-D: sides 2 and BMAX / 2 at most)
   float coef[33];
 };
-template <int D>
-DEVI void fbc_weight_tables(FbcWeights& w, const float* coef, int nlev, int n0, int n1, int n2) {
-  for (int e = threadIdx.x; e < n0 + n1 + n2; e += kFbCoarseThreads) {
+template <int D, int BMAX, int NT>
+DEVI void fbc_weight_tables(FbcWeights<D, BMAX>& w, const float* coef, int nlev, int n0, int n1, int n2) {
+  if constexpr (D == 1) return;
+  for (int j = threadIdx.x; j <= nlev; j += NT) w.coef[j] = coef[j];
+  for (int e = threadIdx.x; e < n0 + n1 + n2; e += NT) {
     const int ax = e < n0 ? 0 : (e < n0 + n1 ? 1 : 2);
     const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), c = ax == 0 ? e : (ax == 1 ? e - n0 : e - n0 - n1);
-    int j = 0;
-    if (ax < 3 - D) j = nlev;
-    else while (j < nlev && c < (n >> (j + 1))) ++j;
-    w.lev[e] = (uint8_t)j;
+    w.lev[e] = (uint8_t)(ax < 3 - D ? nlev : fbc_level(c, n, nlev));
   }
-  for (int j = threadIdx.x; j <= nlev; j += kFbCoarseThreads) w.coef[j] = coef[j];
 }
 
-template <int D, int L, bool SYN>
-__global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, Filter f) {
-  __shared__ __attribute__((aligned(16))) float sm[2 * kFbCoarseMax];
-  __shared__ FbcWeights wt;
+template <int D, int L, bool SYN, int BMAX>
+__global__ void __launch_bounds__(fb_coarse_threads(D, BMAX), fb_coarse_waves(D, L, SYN, BMAX)) k_fb_coarse(TailArgs args, Filter f) {
+  constexpr int NT = fb_coarse_threads(D, BMAX);
+  __shared__ __attribute__((aligned(16))) float sm[2 * BMAX];
+  __shared__ FbcWeights<D, BMAX> wt;
   const int wg = logical_wg(args.total_wg);
   if (wg < 0) return;
   int ti = 0;
@@ -1471,53 +1539,59 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
   const int l1 = ilog2_or_neg(n1), l2 = ilog2_or_neg(n2);
   const int nl = tp->nlev;
   const int in0 = tp->st_in[0], in1 = tp->st_in[1], out0 = tp->st_out[0], out1 = tp->st_out[1];
-  constexpr int CUR = 0, TMP = kFbCoarseMax;
+  constexpr int CUR = 0, TMP = BMAX;
   auto copy_back = [&](int b0, int b1, int b2) {  // TMP sub-block -> CUR
     const int t1 = ilog2_or_neg(b1), t2 = ilog2_or_neg(b2);
-    for (int e = threadIdx.x; e < b0 * b1 * b2; e += blockDim.x) {
+    for (int e = threadIdx.x; e < b0 * b1 * b2; e += NT) {
       int c0, c1, c2;
       split3(e, b1, b2, t1, t2, c0, c1, c2);
       const int o = c0 * S0 + c1 * S1 + c2;
       sm[CUR + o] = sm[TMP + o];
     }
   };
-  constexpr int U = kFbCoarseMax / kFbCoarseThreads, U4 = U / 4;
+  constexpr int U = BMAX / NT, U4 = U / 4;
   // element e of the block: its place in the strided block and its weight
   auto place = [&](int e, int s0, int s1, float* w) {
     int c0, c1, c2;
     split3(e, n1, n2, l1, l2, c0, c1, c2);
-    *w = wt.coef[min(min((int)wt.lev[c0], (int)wt.lev[n0 + c1]), (int)wt.lev[n0 + n1 + c2])];
+    *w = D == 1 ? tp->coef[fbc_level(c2, n2, nl)]
+                : wt.coef[min(min((int)wt.lev[c0], (int)wt.lev[n0 + c1]), (int)wt.lev[n0 + n1 + c2])];
     return (D >= 3 ? c0 * s0 : 0) + (D >= 2 ? c1 * s1 : 0) + c2;
   };
   // four elements e .. e + 3 of one row (n2 a multiple of 4)
   auto place4 = [&](int e, int s0, int s1, float4* w) {
     int c0, c1, c2;
     split3(e, n1, n2, l1, l2, c0, c1, c2);
-    const int r = min((int)wt.lev[c0], (int)wt.lev[n0 + c1]);
-    const uint8_t* t = wt.lev + n0 + n1 + c2;
-    *w = make_float4(wt.coef[min(r, (int)t[0])], wt.coef[min(r, (int)t[1])], wt.coef[min(r, (int)t[2])],
-                     wt.coef[min(r, (int)t[3])]);
+    if constexpr (D == 1) {
+      *w = make_float4(tp->coef[fbc_level(c2, n2, nl)], tp->coef[fbc_level(c2 + 1, n2, nl)],
+                       tp->coef[fbc_level(c2 + 2, n2, nl)], tp->coef[fbc_level(c2 + 3, n2, nl)]);
+    } else {
+      const int r = min((int)wt.lev[c0], (int)wt.lev[n0 + c1]);
+      const uint8_t* t = wt.lev + n0 + n1 + c2;
+      *w = make_float4(wt.coef[min(r, (int)t[0])], wt.coef[min(r, (int)t[1])], wt.coef[min(r, (int)t[2])],
+                       wt.coef[min(r, (int)t[3])]);
+    }
     return (D >= 3 ? c0 * s0 : 0) + (D >= 2 ? c1 * s1 : 0) + c2;
   };
   const float* gl = SYN ? in : out;  // the strided block
   const int gs0 = SYN ? in0 : out0, gs1 = SYN ? in1 : out1;
   const bool rows4 = (n2 & 3) == 0 && ((uintptr_t)gl & 15) == 0 && (D < 2 || (gs1 & 3) == 0) && (D < 3 || (gs0 & 3) == 0);
   if (!SYN) {
-    block_to_lds<kFbCoarseThreads, kFbCoarseMax>(in, sm + CUR, B,
-                                                 [&] { fbc_weight_tables<D>(wt, tp->coef, nl, n0, n1, n2); });
+    block_to_lds<NT, BMAX>(in, sm + CUR, B,
+                           [&] { fbc_weight_tables<D, BMAX, NT>(wt, tp->coef, nl, n0, n1, n2); });
     __syncthreads();
     for (int j = 0; j < nl; ++j) {
       const int b0 = D >= 3 ? n0 >> j : 1, b1 = D >= 2 ? n1 >> j : 1, b2 = n2 >> j;
       // dim 2: CUR -> TMP, dim 1: TMP -> CUR, dim 0: CUR -> TMP
-      fbc_analysis<D, L>(sm, CUR, TMP, S0, S1, b0, b1, b2, 2, f);
+      fbc_analysis<D, L, NT>(sm, CUR, TMP, S0, S1, b0, b1, b2, 2, f);
       __syncthreads();
       bool in_tmp = true;
       if (D >= 2) {
-        fbc_analysis<D, L>(sm, TMP, CUR, S0, S1, b0, b1, b2, 1, f);
+        fbc_analysis<D, L, NT>(sm, TMP, CUR, S0, S1, b0, b1, b2, 1, f);
         __syncthreads();
         in_tmp = false;
         if (D >= 3) {
-          fbc_analysis<D, L>(sm, CUR, TMP, S0, S1, b0, b1, b2, 0, f);
+          fbc_analysis<D, L, NT>(sm, CUR, TMP, S0, S1, b0, b1, b2, 0, f);
           __syncthreads();
           in_tmp = true;
         }
@@ -1530,7 +1604,7 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
     const bool norm = (tp->flags & kNormSq) != 0;
     KSum nsq;
     if (rows4 || (norm && (n2 & 3) == 0)) {
-      for (int e = 4 * threadIdx.x; e < B; e += 4 * kFbCoarseThreads) {
+      for (int e = 4 * threadIdx.x; e < B; e += 4 * NT) {
         float4 w;
         const int o = place4(e, out0, out1, &w);
         const float4 x = *reinterpret_cast<const float4*>(sm + CUR + e);
@@ -1542,7 +1616,7 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
         }
       }
     } else {
-      for (int e = threadIdx.x; e < B; e += kFbCoarseThreads) {
+      for (int e = threadIdx.x; e < B; e += NT) {
         float w;
         const int o = place(e, out0, out1, &w);
         const float v = w * sm[CUR + e];
@@ -1550,22 +1624,22 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
         else gst(out + o, v);
       }
     }
-    if (norm) store_wg_sum<kFbCoarseThreads>(nsq, reinterpret_cast<float2*>(tp->out) + inst);
+    if (norm) store_wg_sum<NT>(nsq, reinterpret_cast<float2*>(tp->out) + inst);
   } else {
-    fbc_weight_tables<D>(wt, tp->coef, nl, n0, n1, n2);
     if (rows4) {
       float4 v[U4];
 #pragma unroll
       for (int u = 0; u < U4; ++u) {
-        const int e = 4 * (int(threadIdx.x) + u * kFbCoarseThreads);
+        const int e = 4 * (int(threadIdx.x) + u * NT);
         int c0, c1, c2;
         split3(min(e, B - 4), n1, n2, l1, l2, c0, c1, c2);
         v[u] = gld4(in + (D >= 3 ? c0 * in0 : 0) + (D >= 2 ? c1 * in1 : 0) + c2);
       }
-      __syncthreads();
+      fbc_weight_tables<D, BMAX, NT>(wt, tp->coef, nl, n0, n1, n2);
+      if constexpr (D > 1) __syncthreads();
 #pragma unroll
       for (int u = 0; u < U4; ++u) {
-        const int e = 4 * (int(threadIdx.x) + u * kFbCoarseThreads);
+        const int e = 4 * (int(threadIdx.x) + u * NT);
         if (e < B) {
           float4 w;
           place4(e, in0, in1, &w);
@@ -1573,8 +1647,9 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
         }
       }
     } else {
-      __syncthreads();
-      gather_to_lds<kFbCoarseThreads, U>(
+      fbc_weight_tables<D, BMAX, NT>(wt, tp->coef, nl, n0, n1, n2);
+      if constexpr (D > 1) __syncthreads();
+      gather_to_lds<NT, U>(
           B, [&](int e) { float w; return gld(in + place(e, in0, in1, &w)); },
           [&](int e, float v) { float w; place(e, in0, in1, &w); sm[CUR + e] = w * v; });
     }
@@ -1584,16 +1659,16 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
       // dim 0 (3-D), dim 1, dim 2, ping-pong starting from CUR
       int a = CUR, bb = TMP;
       if (D >= 3) {
-        fbc_synthesis<D, L>(sm, a, bb, S0, S1, b0, b1, b2, 0, f);
+        fbc_synthesis<D, L, NT>(sm, a, bb, S0, S1, b0, b1, b2, 0, f);
         __syncthreads();
         const int t = a; a = bb; bb = t;
       }
       if (D >= 2) {
-        fbc_synthesis<D, L>(sm, a, bb, S0, S1, b0, b1, b2, 1, f);
+        fbc_synthesis<D, L, NT>(sm, a, bb, S0, S1, b0, b1, b2, 1, f);
         __syncthreads();
         const int t = a; a = bb; bb = t;
       }
-      fbc_synthesis<D, L>(sm, a, bb, S0, S1, b0, b1, b2, 2, f);
+      fbc_synthesis<D, L, NT>(sm, a, bb, S0, S1, b0, b1, b2, 2, f);
       __syncthreads();
       if (bb != CUR) {
         copy_back(b0, b1, b2);
@@ -1602,7 +1677,7 @@ __global__ void __launch_bounds__(kFbCoarseThreads) k_fb_coarse(TailArgs args, F
     }
     const bool st4 = (n2 & 3) == 0 && ((uintptr_t)out & 15) == 0 && (D < 2 || (out1 & 3) == 0) && (D < 3 || (out0 & 3) == 0);
     const int ev = st4 ? 4 : 1;
-    for (int e = ev * threadIdx.x; e < B; e += ev * kFbCoarseThreads) {
+    for (int e = ev * threadIdx.x; e < B; e += ev * NT) {
       int c0, c1, c2;
       split3(e, n1, n2, l1, l2, c0, c1, c2);
       float* o = out + (D >= 3 ? c0 * out0 : 0) + (D >= 2 ? c1 * out1 : 0) + c2;
@@ -1807,16 +1882,23 @@ hipError_t launch_k(int ndim, int taps, int variant, bool vec, const TaskArgs& a
   return hipErrorInvalidValue;
 }
 
+template <int D, int L, bool SYN>
+void launch_fb_coarse(const TailArgs& a, int grid, size_t lds, const Filter& f, hipStream_t s) {
+  constexpr int S = fb_coarse_small(D), M = kFbCoarseMaxBlock;
+  if (lds > sizeof(float) * 2 * S) hipLaunchKernelGGL((k_fb_coarse<D, L, SYN, M>), dim3(grid), dim3(fb_coarse_threads(D, M)), 0, s, a, f);
+  else hipLaunchKernelGGL((k_fb_coarse<D, L, SYN, S>), dim3(grid), dim3(fb_coarse_threads(D, S)), 0, s, a, f);
+}
+
 template <int D, int L>
 hipError_t launch_tail_dl(int kind, const TailArgs& a, int grid, size_t lds, const Filter& f, hipStream_t s) {
   switch (kind) {
-    case 1: hipLaunchKernelGGL((k_fb_coarse<D, L, false>), dim3(grid), dim3(kFbCoarseThreads), 0, s, a, f); break;
-    case 2: hipLaunchKernelGGL((k_fb_coarse<D, L, true>), dim3(grid), dim3(kFbCoarseThreads), 0, s, a, f); break;
+    case 1: launch_fb_coarse<D, L, false>(a, grid, lds, f, s); break;
+    case 2: launch_fb_coarse<D, L, true>(a, grid, lds, f, s); break;
     case 3:
-      if (lds > sizeof(float) * (size_t)coarse_lds_floats(kCoarseMaxBlock))
-        hipLaunchKernelGGL((k_lp_coarse<D, L, kCoarseMaxBlockBig>), dim3(grid), dim3(kCoarseThreads), 0, s, a, f);
+      if (lds > sizeof(float) * (size_t)coarse_lds_floats(D, kCoarseMaxBlock))
+        hipLaunchKernelGGL((k_lp_coarse<D, L, kCoarseMaxBlockBig>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlockBig)), 0, s, a, f);
       else
-        hipLaunchKernelGGL((k_lp_coarse<D, L, kCoarseMaxBlock>), dim3(grid), dim3(kCoarseThreads), 0, s, a, f);
+        hipLaunchKernelGGL((k_lp_coarse<D, L, kCoarseMaxBlock>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlock)), 0, s, a, f);
       break;
     default: return hipErrorInvalidValue;  // kind 0 (first low-pass tail) was removed
   }

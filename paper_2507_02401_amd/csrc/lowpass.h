@@ -544,33 +544,33 @@ DEVI int ceil_log2(int v) { return v <= 1 ? 0 : 32 - __builtin_clz(v - 1); }
 template <int L, int NT>
 DEVI void coarse_rows_down(float* sm, int src, int dst, int lines, int n, const Filter& f) {
   constexpr int PO = 4, W4 = (2 * PO + L - 2 + 3) / 4;
-  const int o = n >> 1, nch = o / PO, lg = ceil_log2(nch);
-  const int ch = threadIdx.x & ((1 << lg) - 1), l0 = threadIdx.x >> lg;
-  if (ch >= nch || l0 >= lines) return;
-  int off[W4];
-#pragma unroll
-  for (int v = 0; v < W4; ++v) {
-    const int i = 2 * PO * ch + 4 * v;
-    off[v] = i >= n ? i - n : i;
-  }
-  const float* in = sm + src + l0 * n;
-  float* out = sm + dst + l0 * o + PO * ch;
-  const int ls = NT >> lg;
-  for (int l = l0; l < lines; l += ls, in += ls * n, out += ls * o) {
-    float win[4 * W4];
+  const int o = n >> 1, nch = o / PO, lg = min(ceil_log2(nch), ceil_log2(NT));
+  const int l0 = threadIdx.x >> lg, ls = NT >> lg;
+  for (int ch = threadIdx.x & ((1 << lg) - 1); ch < nch; ch += 1 << lg) {  // more than one: lines of over 8 NT samples
+    int off[W4];
 #pragma unroll
     for (int v = 0; v < W4; ++v) {
-      const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
-      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
+      const int i = 2 * PO * ch + 4 * v;
+      off[v] = i >= n ? i - n : i;
     }
-    float r[PO];
+    const float* in = sm + src + l0 * n;
+    float* out = sm + dst + l0 * o + PO * ch;
+    for (int l = l0; l < lines; l += ls, in += ls * n, out += ls * o) {
+      float win[4 * W4];
 #pragma unroll
-    for (int q = 0; q < PO; ++q) {
-      r[q] = 0.f;
+      for (int v = 0; v < W4; ++v) {
+        const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
+        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
+      }
+      float r[PO];
 #pragma unroll
-      for (int t = 0; t < L; ++t) r[q] = fmaf(f.h[t], win[2 * q + t], r[q]);
+      for (int q = 0; q < PO; ++q) {
+        r[q] = 0.f;
+#pragma unroll
+        for (int t = 0; t < L; ++t) r[q] = fmaf(f.h[t], win[2 * q + t], r[q]);
+      }
+      *reinterpret_cast<float4*>(out) = make_float4(r[0], r[1], r[2], r[3]);
     }
-    *reinterpret_cast<float4*>(out) = make_float4(r[0], r[1], r[2], r[3]);
   }
 }
 
@@ -613,38 +613,38 @@ DEVI void coarse_cols_down(float* sm, int src, int dst, int outer, int n, int in
 template <int L, int NT>
 DEVI void coarse_rows_up(float* sm, int src, int dst, int lines, int n, const Filter& f, bool combine, float alpha) {
   constexpr int H = L / 2, PO = 4, A = (H - 1 + 3) & ~3, NW = (A + PO) / 4;
-  const int half = n >> 1, nch = half / PO, lg = ceil_log2(nch);
-  const int ch = threadIdx.x & ((1 << lg) - 1), l0 = threadIdx.x >> lg;
-  if (ch >= nch || l0 >= lines) return;
-  int off[NW];
-#pragma unroll
-  for (int v = 0; v < NW; ++v) {
-    const int k = PO * ch - A + 4 * v;
-    off[v] = k < 0 ? k + half : k;
-  }
-  const float* in = sm + src + l0 * half;
-  float* out = sm + dst + l0 * n + 2 * PO * ch;
-  const int ls = NT >> lg;
-  for (int l = l0; l < lines; l += ls, in += ls * half, out += ls * n) {
-    float win[A + PO];
+  const int half = n >> 1, nch = half / PO, lg = min(ceil_log2(nch), ceil_log2(NT));
+  const int l0 = threadIdx.x >> lg, ls = NT >> lg;
+  for (int ch = threadIdx.x & ((1 << lg) - 1); ch < nch; ch += 1 << lg) {
+    int off[NW];
 #pragma unroll
     for (int v = 0; v < NW; ++v) {
-      const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
-      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
+      const int k = PO * ch - A + 4 * v;
+      off[v] = k < 0 ? k + half : k;
     }
-    float v[2 * PO];
+    const float* in = sm + src + l0 * half;
+    float* out = sm + dst + l0 * n + 2 * PO * ch;
+    for (int l = l0; l < lines; l += ls, in += ls * half, out += ls * n) {
+      float win[A + PO];
 #pragma unroll
-    for (int r = 0; r < 2 * PO; ++r) {
-      v[r] = 0.f;
+      for (int v = 0; v < NW; ++v) {
+        const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
+        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
+      }
+      float v[2 * PO];
 #pragma unroll
-      for (int j = 0; j < H; ++j) v[r] = fmaf(f.h[2 * j + (r & 1)], win[A + (r >> 1) - j], v[r]);
-    }
+      for (int r = 0; r < 2 * PO; ++r) {
+        v[r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 2 * PO; r += 4) {
-      float4 s = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
-      float4* o = reinterpret_cast<float4*>(out + r);
-      if (combine) s = axpy4(alpha, *o, s);
-      *o = s;
+        for (int j = 0; j < H; ++j) v[r] = fmaf(f.h[2 * j + (r & 1)], win[A + (r >> 1) - j], v[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < 2 * PO; r += 4) {
+        float4 s = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+        float4* o = reinterpret_cast<float4*>(out + r);
+        if (combine) s = axpy4(alpha, *o, s);
+        *o = s;
+      }
     }
   }
 }
@@ -686,6 +686,29 @@ DEVI void coarse_cols_up(float* sm, int src, int dst, int outer, int n, int inne
   }
 }
 
+// Analysis of strided axes whose inner count is no multiple of 4 (rows halved to 18, say; the synthesis has whole
+// rows): a thread forms four outputs of one column from one window.
+template <int L, int NT>
+DEVI void coarse_cols_down_1(float* sm, int src, int dst, int outer, int n, int inner, const Filter& f) {
+  constexpr int PO = 4, WN = 2 * PO + L - 2;
+  const int o = n >> 1, per = o / PO * inner;
+  for (int e = threadIdx.x; e < outer * per; e += NT) {
+    const int q = outer == 1 ? 0 : e / per, r = e - q * per, k0 = PO * (r / inner), c = r % inner, wrap = n - 2 * k0;
+    const float* in = sm + src + (q * n + 2 * k0) * inner + c;
+    float win[WN];
+#pragma unroll
+    for (int j = 0; j < WN; ++j) win[j] = in[(j >= wrap ? j - n : j) * inner];
+    float* out = sm + dst + (q * o + k0) * inner + c;
+#pragma unroll
+    for (int p = 0; p < PO; ++p) {
+      float v = 0.f;
+#pragma unroll
+      for (int t = 0; t < L; ++t) v = fmaf(f.h[t], win[2 * p + t], v);
+      out[p * inner] = v;
+    }
+  }
+}
+
 // Uniform dispatch over an (n0, n1, n2) block.  Axes shorter than the filter (halves shorter than L / 2
 // for the synthesis) fold periodically: the _w versions, as where a count or an offset does not divide.
 // One instantiation serves every level: variants of its own for the largest and the smallest levels were
@@ -698,9 +721,11 @@ DEVI void coarse_analysis(float* sm, int src, int dst, int n0, int n1, int n2, i
   const bool v4 = ((src | dst) & 3) == 0;
   if (n < L) return coarse_analysis_w<L, true, NT>(sm, src, dst, n0, n1, n2, ax, f);
   if (ax == 2) {
-    if (v4 && o % 4 == 0 && o <= 4 * NT) return coarse_rows_down<L, NT>(sm, src, dst, outer, n, f);
+    if (v4 && o % 4 == 0) return coarse_rows_down<L, NT>(sm, src, dst, outer, n, f);
   } else if (v4 && inner % 4 == 0 && ceil_log2(inner / 4) <= ceil_log2(NT)) {
     return coarse_cols_down<L, NT>(sm, src, dst, outer, n, inner, f);
+  } else if (o % 4 == 0) {
+    return coarse_cols_down_1<L, NT>(sm, src, dst, outer, n, inner, f);
   }
   coarse_analysis_w<L, false, NT>(sm, src, dst, n0, n1, n2, ax, f);
 }
@@ -713,7 +738,7 @@ DEVI void coarse_synthesis(float* sm, int src, int dst, int n0, int n1, int n2, 
   const bool v4 = ((src | dst) & 3) == 0;
   if (half < L / 2) return coarse_synthesis_w<L, true, NT>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
   if (ax == 2) {
-    if (v4 && half % 4 == 0 && half <= 4 * NT) return coarse_rows_up<L, NT>(sm, src, dst, outer, n, f, combine, alpha);
+    if (v4 && half % 4 == 0) return coarse_rows_up<L, NT>(sm, src, dst, outer, n, f, combine, alpha);
   } else if (v4 && inner % 4 == 0 && ceil_log2(inner / 4) <= ceil_log2(NT)) {
     if (direct) *direct = true;
     return coarse_cols_up<L, NT>(sm, src, dst, outer, n, inner, f, combine, alpha, gout);
@@ -887,7 +912,7 @@ DEVI bool coarse_dense(float* sm, const DenseLds& d, int ao, int n1, int n2, int
 }
 
 // Every coarse level of instance `inst` of tail task `tp` in one work-group of NT threads; `sm`
-// holds coarse_lds_floats(CMAX) floats of LDS (16-byte aligned).
+// holds coarse_lds_floats(D, CMAX) floats of LDS (16-byte aligned).
 template <int D, int L, int CMAX, int NT>
 DEVI void lp_coarse_block(const TailTask* tp, int inst, const Filter& f, float* sm) {
   const float* in = tp->in + inst * tp->bs_in;

@@ -55,8 +55,8 @@ __global__ void __launch_bounds__(kThreads) k_mixed_up(TaskArgs args, FilterBank
 }
 
 template <int CMAX>
-__global__ void __launch_bounds__(kCoarseThreads) k_mixed_coarse(TailArgs args, FilterBank bank) {
-  __shared__ __attribute__((aligned(16))) float sm[coarse_lds_floats(CMAX)];
+__global__ void __launch_bounds__(coarse_threads(CMAX)) k_mixed_coarse(TailArgs args, FilterBank bank) {
+  __shared__ __attribute__((aligned(16))) float sm[coarse_lds_floats(2, CMAX)];
   const int wg = logical_wg(args.total_wg);
   if (wg < 0) return;
   int lo = 0, hi = args.count - 1;
@@ -68,7 +68,7 @@ __global__ void __launch_bounds__(kCoarseThreads) k_mixed_coarse(TailArgs args, 
   const TailTask* tp = args.table + lo;
   switch (__builtin_amdgcn_readfirstlane(tp->taps)) {
 #define ES_CASE(L) \
-  case L: lp_coarse_block<2, L, CMAX, kCoarseThreads>(tp, wg - tp->tile_begin, bank.f[L / 2 - 1], sm); break;
+  case L: lp_coarse_block<2, L, CMAX, coarse_threads(CMAX)>(tp, wg - tp->tile_begin, bank.f[L / 2 - 1], sm); break;
     ES_EACH_TAPS(ES_CASE)
 #undef ES_CASE
   }
@@ -100,10 +100,10 @@ hipError_t launch_mixed_level(int kind, int variant, const TaskArgs& args, int g
 
 hipError_t launch_mixed_coarse(const TailArgs& args, int grid, size_t lds_bytes, const FilterBank& bank, hipStream_t s) {
   if (args.table == nullptr) return hipErrorInvalidValue;
-  if (lds_bytes <= sizeof(float) * coarse_lds_floats(kCoarseMaxBlock))
-    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlock>), dim3(grid), dim3(kCoarseThreads), 0, s, args, bank);
+  if (lds_bytes <= sizeof(float) * coarse_lds_floats(2, kCoarseMaxBlock))
+    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlock>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlock)), 0, s, args, bank);
   else
-    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlockBig>), dim3(grid), dim3(kCoarseThreads), 0, s, args, bank);
+    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlockBig>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlockBig)), 0, s, args, bank);
   return hipGetLastError();
 }
 

@@ -30,7 +30,7 @@ constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
 template <int D, int L>
 constexpr size_t persist_lds() {
   return cmax(cmax(sizeof(typename PTiles<D, L>::Down), sizeof(typename PTiles<D, L>::Up)),
-              sizeof(float) * (size_t)coarse_lds_floats(kPCoarseMax));
+              sizeof(float) * (size_t)coarse_lds_floats(D, kPCoarseMax));
 }
 
 DEVI void run_copy(const PStep* st, int tile) {

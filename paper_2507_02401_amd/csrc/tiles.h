@@ -51,8 +51,19 @@ constexpr Shape3 shape_of(int K, int D, int V, int L) {
 // Output rows per chunk of the streamed 2-D low-pass analysis kernel (measured on 64 x 1024^2 and
 // 64 x 512^2 db8 levels against 4 and 16, with strips of 64, 128 and 256 columns).
 constexpr int kStreamRows = 8;
-constexpr int kCoarseThreads = 1024;    // low-pass coarse kernel
-constexpr int kFbCoarseThreads = 1024;  // full-bank coarse kernels
+// Threads of the low-pass coarse kernel for blocks of at most cmax floats.  A pass of a block of 4096 has 512
+// items of four outputs or fewer, and the kernel takes up to 128 registers: 512 threads leave room for two
+// work-groups per CU, 1024 for one (batches of more than 256 such blocks then take up to twice as long: 8178 of
+// 12 x 20, 8 taps, 110 -> 62 us; 4230 of 16 x 32, 8 taps, 61 -> 34 us; single blocks are as fast with either).
+constexpr int coarse_threads(int cmax) { return cmax <= kCoarseMaxBlock ? 512 : 1024; }
+// The full-bank coarse kernels' two sizes likewise (41287 blocks of 16 x 8, 16 taps, 1063 -> 550 us; blocks above
+// 4096 floats are up to 8 % slower with 512 threads).  Their 3-D analysis of 14 and 16 taps needs 66 registers
+// unless it is held to the 64 of two work-groups of 1024.
+constexpr int fb_coarse_small(int D) { return D == 1 ? 2048 : 4096; }
+constexpr int fb_coarse_threads(int D, int bmax) { return bmax <= fb_coarse_small(D) ? 512 : 1024; }
+constexpr int fb_coarse_waves(int D, int L, bool syn, int bmax) {
+  return D == 3 && L >= 14 && !syn && bmax > fb_coarse_small(D) ? 8 : 4;
+}
 
 // LDS of a block of at most CMAX floats: the pyramid (< 2B in 1-D, < 4B/3 in 2-D, < 8B/7 in 3-D)
 // plus the temporaries (1-D: none; 2-D: B/2; 3-D: B/2 + B/2, the second synthesis pass writes a
@@ -62,9 +73,9 @@ constexpr int kDenseRow = kDenseSide + 4;
 constexpr int kDenseBuf = kDenseSide * kDenseRow;
 constexpr int kDenseTables = 2 * kDenseSide + kDenseLevels + 2;
 constexpr int dense_extra_floats(int tmp) { return (tmp > 2 * kDenseBuf ? tmp : 2 * kDenseBuf) + 2 * kDenseBuf + kDenseTables; }
-constexpr int coarse_lds_floats(int cmax) {
+constexpr int coarse_lds_floats(int D, int cmax) {
   const int passes = cmax / 4 * 9, dense = (cmax / 3 * 4 + 8 + dense_extra_floats(cmax / 2) + 3) & ~3;
-  return passes > dense ? passes : dense;
+  return D != 2 || passes > dense ? passes : dense;
 }
 
 inline TileShape tile_shape(int kind, int ndim, int variant, int taps) {
@@ -76,13 +87,11 @@ inline TileShape tile_shape(int kind, int ndim, int variant, int taps) {
   return t;
 }
 inline int tile_threads(int, int, int) { return kThreads; }
-inline int tail_threads() { return kFbCoarseThreads; }
 
-// LDS the low-pass coarse kernel needs for a block (static arrays in two sizes, chosen at launch
-// from this value); the full-bank coarse kernels use one fixed size.
-inline size_t tail_lds_bytes(int kind, int, const int b[3], int) {
-  if (kind != 3) return 0;
-  return sizeof(float) * (size_t)coarse_lds_floats(b[0] * b[1] * b[2]);
+// LDS that a coarse kernel needs for a block; it selects one of the kernel's two sizes at launch.
+inline size_t tail_lds_bytes(int kind, int D, const int b[3], int) {
+  const int block = b[0] * b[1] * b[2];
+  return sizeof(float) * (size_t)(kind == 3 ? coarse_lds_floats(D, block) : 2 * block);
 }
 
 }  // namespace es
