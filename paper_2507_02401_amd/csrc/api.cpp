@@ -36,7 +36,7 @@
 
 #include "../../include/eswave.h"
 #include "internal.h"
-#include "tiles.h"
+#include "tile_cost.h"
 
 using namespace es;
 
@@ -169,14 +169,14 @@ bool get_filter(int L, Filter* f) {
 double wdet(const Geo& g, double tau, int i) { return std::exp2(-tau * g.s * (double)(g.m - i)); }
 
 // First coarse level of a 2-D block whose remaining levels run as matrix products (lp_coarse_block): the
-// first of at most 32 x 32 samples with two levels below it or more, or with one and an axis shorter than the
-// filter (whose passes fold index by index); -1: none.  The four products of a single level take longer than
-// its four passes otherwise: 8178 images of 12 x 20, 8 taps, 67 against 62 us.
+// first of at most 32 x 32 samples with a level below it; -1: none.  A block that has one level in all takes its
+// four passes instead, unless an axis is shorter than the filter (passes then fold index by index): the four
+// products and their tables take longer (8178 images of 12 x 20, 8 taps, 67 against 62 us).
 int dense_from(int D, int L, const int b[3], int nlev) {
   if (D != 2) return -1;
   for (int j = 0; j < nlev; ++j)
     if ((b[1] >> j) <= kDenseSide && (b[2] >> j) <= kDenseSide)
-      return nlev - j >= 2 || std::min(b[1] >> j, b[2] >> j) < L ? j : -1;
+      return nlev > 1 || std::min(b[1], b[2]) < L ? j : -1;
   return -1;
 }
 
@@ -274,35 +274,29 @@ struct Schedule {
   Filter f;
 };
 
-void set_tiles(Task& t, int kind, const Geo& g, int level, int variant, int64_t batch) {
+// Tiles of a level's block along each axis.
+void tile_counts(int kind, const Geo& g, int level, int variant, int32_t n[3]) {
   int b[3];
   g.level_dims(level - 1, b);  // full-res block of the level
-  if (kind == K_LP_DOWN_P || kind == K_LP_DOWN_A1) {
-    const TileShape ts = tile_shape(kind, g.D, variant, g.L);
-    for (int k = 0; k < 3; ++k) t.b[k] = b[k];
-    auto tiles = [](int64_t n, int tile) { return (int32_t)((n + tile - 1) / tile); };
-    if (kind == K_LP_DOWN_P) {  // planes of axis 1; axes 0 and 2 tiled
-      t.ntile[0] = b[1];
-      t.ntile[1] = tiles(b[0] / 2, ts.t[1]);
-      t.ntile[2] = tiles(b[2] / 2, ts.t[2]);
-    } else {  // lines along axis 1 in 16-byte groups; axis 1 in chunks
-      t.ntile[0] = tiles((int64_t)(b[0] / 2) * ((b[2] / 2 + 3) / 4), ts.t[0]);
-      t.ntile[1] = tiles(b[1] / 2, ts.t[1]);
-      t.ntile[2] = 1;
-    }
-    t.tiles_per_inst = t.ntile[0] * t.ntile[1] * t.ntile[2];
-    t.batch = (int32_t)batch;
-    t.tile_begin = 0;
-    return;
-  }
   const TileShape ts = tile_shape(kind, g.D, variant, g.L);
-  const bool analysis = kind_is_analysis(kind);
-  for (int k = 0; k < 3; ++k) {
-    t.b[k] = b[k];
-    const bool real = k >= 3 - g.D;
-    const int extent = real ? (analysis ? b[k] / 2 : b[k]) : 1;
-    t.ntile[k] = real ? (extent + ts.t[k] - 1) / ts.t[k] : 1;
+  auto tiles = [](uint32_t len, uint32_t tile) { return (int32_t)((len + tile - 1) / tile); };
+  if (kind == K_LP_DOWN_P) {  // planes of axis 1; axes 0 and 2 tiled
+    n[0] = b[1];
+    n[1] = tiles(b[0] / 2, ts.t[1]);
+    n[2] = tiles(b[2] / 2, ts.t[2]);
+  } else if (kind == K_LP_DOWN_A1) {  // lines along axis 1 in 16-byte groups; axis 1 in chunks
+    n[0] = tiles((uint32_t)(b[0] / 2) * (uint32_t)((b[2] / 2 + 3) / 4), ts.t[0]);
+    n[1] = tiles(b[1] / 2, ts.t[1]);
+    n[2] = 1;
+  } else {
+    const int half = kind_is_analysis(kind) ? 1 : 0;
+    for (int k = 0; k < 3; ++k) n[k] = k < 3 - g.D ? 1 : tiles((uint32_t)b[k] >> half, ts.t[k]);
   }
+}
+
+void set_tiles(Task& t, int kind, const Geo& g, int level, int variant, int64_t batch) {
+  g.level_dims(level - 1, t.b);
+  tile_counts(kind, g, level, variant, t.ntile);
   t.tiles_per_inst = t.ntile[0] * t.ntile[1] * t.ntile[2];
   t.batch = (int32_t)batch;
   t.tile_begin = 0;
@@ -329,14 +323,33 @@ int64_t lp_tail_limit(const Geo&) {
   return kCoarseMaxBlockBig;
 }
 
-// Work-groups of a level launch with the given tile variant.
-int64_t level_wgs(int kind, const Geo& g, int level, int variant, int64_t batch) {
-  Task t{};
-  set_tiles(t, kind, g, level, variant, batch);
-  return (int64_t)((double)t.tiles_per_inst * std::max((double)batch, g_variant_share));
+// A launch holds fewer than 2^32 threads (its grid is rounded up to a multiple of 8).
+bool launchable(double wgs) { return (wgs + 7) * kThreads < 4294967296.0; }
+
+// Rows that a launch stages: whole 16-byte groups (the callers' and the level arrays start at 16 bytes).
+bool whole_rows(int kind, const Geo& g, int level) {
+  int b[3];
+  g.level_dims(level - 1, b);
+  return ((kind_is_analysis(kind) && kind != K_LP_DOWN_A1 ? b[2] : b[2] / 2) & 3) == 0;
 }
 
-// Tile variant of a level (the kernel family is chosen by level_launch).  The rule follows what
+// Modelled time of a launch that holds one or more levels (tile_cost.h), us; far more than any where the
+// runtime refuses the launch.
+struct LaunchCost {
+  double wgs = 0, fixed = 0, rest = 0;
+  void add(int kind, const Geo& g, int level, int variant, double instances) {
+    int32_t n[3];
+    tile_counts(kind, g, level, variant, n);
+    const TileCost& c = tile_cost(kind, g.D, g.L, variant, whole_rows(kind, g, level));
+    const double w = (double)n[0] * n[1] * n[2] * instances;
+    wgs += w;
+    fixed = std::max(fixed, (double)c.fixed);
+    rest += w * c.group * 1e-3 + (double)g.level_size(level - 1) * instances * c.sample / (1 << 20);
+  }
+  double us() const { return launchable(wgs) ? fixed + rest : 1e12; }
+};
+
+// Tile variant by the work-groups that a launch has with each.  The rule follows what
 // es_autotune picked, launch by launch inside whole calls, on 28 geometries from 7 x 360 x 600 to 64 x
 // 1024^2 and 64^3 to 256^3, 4 to 16 taps (all tiles give the same bits): large tiles win as soon as they
 // make about half a work-group per CU, because the filter halo of a small one is most of its work; only
@@ -368,17 +381,47 @@ int variant_rule(int kind, int D, int L, W wgs) {
   return wgs(0) >= 1024 ? (kind == K_LP_UP || kind == K_FB_UP ? 2 : 0) : 1;
 }
 
-int pick_variant(int kind, const Geo& g, int level, int64_t batch) {
-  if (g_mode.persist) return kPVariant;
-  const int fv = forced_variant();
-  if (fv >= 0) return fv;
-  if (kind == K_LP_DOWN_A1) return 0;
-  if (kind == K_LP_DOWN_P) {  // the widest tile that a plane's rows fill
-    int b[3];
-    g.level_dims(level - 1, b);
-    return b[2] >= 96 ? 0 : b[2] >= 48 ? 2 : 1;
+// Tile variant of a level launch and its modelled time: the rule's, unless another tile's time is modelled more than
+// 8 % shorter.  The rule was taken from whole calls, where tiles that differ by less in the replays
+// behind the model rank otherwise (256^3, 8 taps, second level: 6.6 % shorter modelled, 1.6 % longer as a call); it does
+// not know narrow rows, thin axes and rows that are no whole 16-byte groups, which the model does.
+constexpr double kModelMargin = 1.08;
+struct Pick {
+  int variant;
+  double us;
+};
+// cost(v): LaunchCost of tile variant v
+template <class C>
+Pick pick_tile(int kind, int D, int L, C cost) {
+  LaunchCost c[kNumVariants];
+  int best = 0;
+  for (int v = 0; v < kNumVariants; ++v) {
+    c[v] = cost(v);
+    if (c[v].us() < c[best].us()) best = v;
   }
-  return variant_rule(kind, g.D, g.L, [&](int v) { return level_wgs(kind, g, level, v, batch); });
+  if (kind != K_LP_DOWN_P) {
+    const int r = variant_rule(kind, D, L, [&](int v) { return c[v].wgs; });
+    if (c[r].us() <= kModelMargin * c[best].us()) best = r;
+  }
+  return Pick{best, c[best].us()};
+}
+
+Pick pick_variant(int kind, const Geo& g, int level, int64_t batch, int fv) {  // fv: the forced variant, -1: none
+  auto cost = [&](int v) {
+    LaunchCost c;
+    c.add(kind, g, level, v, std::max((double)batch, g_variant_share));
+    return c;
+  };
+  if (g_mode.persist) fv = kPVariant;
+  if (kind == K_LP_DOWN_A1) fv = 0;
+  return fv >= 0 ? Pick{fv, cost(fv).us()} : pick_tile(kind, g.D, g.L, cost);
+}
+
+// Work-groups of a level launch with a tile variant.
+double rule_wgs(int kind, const Geo& g, int level, int variant, int64_t batch) {
+  int32_t n[3];
+  tile_counts(kind, g, level, variant, n);
+  return (double)n[0] * n[1] * n[2] * std::max((double)batch, g_variant_share);
 }
 
 // Row-alignment condition of the vector staging path for one launch.
@@ -422,46 +465,58 @@ int tiled_kind(int kind) {
   return kind_is_analysis(kind) ? K_FB_DOWN : K_FB_UP;
 }
 
-// Whether a level with two families streams: 3-D levels that then still have a work-group or two per CU,
+// Whether a 3-D low-pass analysis level runs as planes and an axis-1 pass (K_LP_DOWN_P, K_LP_DOWN_A1), by the
+// modelled times: the second launch costs 3-4 us of a small call, and a plane's tile is 16 rows of axis 0 high
+// however few there are; the halo saved grows with the taps and the samples.  Calls with the finest level in
+// one launch / split, us, 16 taps: 96^3 42.5 / 37.6, 4 x 128^3 86.7 / 73.7, 256^3 125 / 105, 64^3 28.2 / 28.6.
+// Single volumes split up to 1.4 times the other time: few work-groups of partial tiles cost the planes less than
+// modelled (calls of 4 x 448 x 452, 16 taps, and 20 x 420 x 100, 12 taps: 24.0 / 25.5 and 19.6 / 20.0).
+bool lp_split(const Geo& g, int level, int64_t batch) {
+  if (g.D != 3 || g_mode.persist || streamed_mode() != 1 || forced_variant() >= 0) return false;
+  int b[3];
+  g.level_dims(level - 1, b);
+  if (b[2] & 3) return false;  // the plane kernel has the 16-byte path only
+  const auto us = [&](int kind) { return pick_variant(kind, g, level, batch, -1).us; };
+  const double split = us(K_LP_DOWN_P) + us(K_LP_DOWN_A1), one = std::min(us(K_LP_DOWN), us(K_LP_DOWN_S));
+  const bool single = std::max((double)batch, g_variant_share) <= 1 && g.L >= 12 && g.level_size(level - 1) >= 3 << 18;
+  return split < (single ? 1.4 : 1.0) * one;
+}
+
+// Whether a level with two families streams by rule: 3-D levels that then still have a work-group or two per CU,
 // except the low-pass synthesis of up to 10 taps, whose wide plain tile is as fast (256^3 db4: 94 -> 82 us
 // a call); 2-D levels take the plain 16 x 64 tile at every size (64 x 1024^2 db8: 254 -> 241 us a call).
 bool streams(int kind, const Geo& g, int level, int64_t batch) {
   if (g.D != 3) return false;
   const int sk = streamed_kind(kind);
   switch (sk) {
-    case K_LP_UP_S: return g.L >= 12 && level_wgs(sk, g, level, 0, batch) >= 512;
-    case K_FB_UP_S: return level_wgs(sk, g, level, 1, batch) >= (g.L >= 12 ? 128 : 256);
-    case K_LP_DOWN_S: return g.L <= 8 ? level_wgs(sk, g, level, 2, batch) >= 512 : level_wgs(sk, g, level, 1, batch) >= 256;
-    default: return level_wgs(sk, g, level, 1, batch) >= 256;  // FB_DOWN_S
+    case K_LP_UP_S: return g.L >= 12 && rule_wgs(sk, g, level, 0, batch) >= 512;
+    case K_FB_UP_S: return rule_wgs(sk, g, level, 1, batch) >= (g.L >= 12 ? 128 : 256);
+    case K_LP_DOWN_S: return g.L <= 8 ? rule_wgs(sk, g, level, 2, batch) >= 512 : rule_wgs(sk, g, level, 1, batch) >= 256;
+    default: return rule_wgs(sk, g, level, 1, batch) >= 256;  // FB_DOWN_S
   }
 }
 
-// Whether a 3-D low-pass analysis level runs as planes and an axis-1 pass (K_LP_DOWN_P, K_LP_DOWN_A1): the
-// second launch costs 3-4 us of a small call, the halo saved grows with the taps and the samples.  Calls
-// with the finest level in one launch / split, us: 12 to 16 taps win from ~2^19.5 samples (16 taps: 96^3
-// 42.5 / 37.6, 4 x 128^3 86.7 / 73.7, 256^3 125 / 105; 64^3 28.2 / 28.6), also at the second level (4 x 128^3
-// 73.7 / 68.0), 10 taps from ~2^20.5 (128^3 35.7 / 32.1, 96^3 31.1 / 30.8), 8 taps from ~2^22.5 (4 x 128^3
-// 51.8 / 49.8, 128^3 29.1 / 31.1), 2 to 6 taps nowhere (256^3, 6 taps: 69.0 / 71.5).
-bool lp_split(const Geo& g, int level, int64_t batch) {
-  if (g.D != 3 || g.L < 8 || streamed_mode() != 1 || g_mode.persist || forced_variant() >= 0) return false;
-  int b[3];
-  g.level_dims(level - 1, b);
-  if (b[2] & 3) return false;  // the plane kernel has the 16-byte path only
-  const double samples = (double)g.level_size(level - 1) * std::max((double)batch, g_variant_share);
-  return samples >= (double)((int64_t)3 << (g.L >= 12 ? 18 : g.L == 10 ? 19 : 21));
-}
-
 Launch level_launch(int kind, const Geo& g, int level, int64_t batch) {
-  const int mode = streamed_mode();
-  if (has_family(kind, g.D) && mode != 0 && !g_mode.persist && (mode == 2 || streams(kind, g, level, batch)))
-    kind = streamed_kind(kind);
+  const int mode = streamed_mode(), fv = forced_variant();
+  const bool family = has_family(kind, g.D) && mode != 0 && !g_mode.persist;
+  const bool rule = family && (mode == 2 || streams(kind, g, level, batch));
+  Pick p = pick_variant(rule ? streamed_kind(kind) : kind, g, level, batch, fv);
+  bool streamed = rule;
+  if (family && mode == 1 && g.D == 3) {
+    const Pick q = pick_variant(rule ? kind : streamed_kind(kind), g, level, batch, fv);
+    if (p.us > kModelMargin * q.us) {
+      p = q;
+      streamed = !rule;
+    }
+  }
+  if (streamed) kind = streamed_kind(kind);
   Launch l{};
   l.is_tail = 0;
   l.kind = kind;
   l.D = g.D;
   l.L = g.L;
   l.level = level;
-  l.variant = pick_variant(kind, g, level, batch);
+  l.variant = p.variant;
   set_tiles(l.task, kind, g, level, l.variant, batch);
   l.task.taps = g.L;
   return l;
@@ -1836,15 +1891,11 @@ void plan_shared_tiles(const es_plan* p, std::vector<Schedule>* scs, const std::
   for (const auto& set : sets) {
     auto launch = [&](const std::pair<int, int>& m) -> Launch& { return (*scs)[m.first].launches[m.second]; };
     const Launch& l0 = launch(set.second[0]);
-    const int v = variant_rule(l0.kind, l0.D, l0.L, [&](int v) {
-      int64_t n = 0;
-      for (const auto& m : set.second) {
-        Task t{};
-        set_tiles(t, l0.kind, p->geos[m.first], launch(m).level, v, 1);
-        n += t.tiles_per_inst;
-      }
-      return n;
-    });
+    const int v = pick_tile(l0.kind, l0.D, l0.L, [&](int v) {
+                    LaunchCost c;
+                    for (const auto& m : set.second) c.add(launch(m).kind, p->geos[m.first], launch(m).level, v, 1);
+                    return c;
+                  }).variant;
     for (const auto& m : set.second) apply_variant(launch(m), p->geos[m.first], v, 1);
   }
 }
