@@ -540,37 +540,50 @@ DEVI void coarse_synthesis_w(float* sm, int src, int dst, int n0, int n1, int n2
 
 DEVI int ceil_log2(int v) { return v <= 1 ? 0 : 32 - __builtin_clz(v - 1); }
 
+// Row passes: a thread takes chunk ch (four half-resolution positions) of every 2^lg-th line.  Lines of a 1-D block may
+// have more chunks than the work-group threads (each(): one after the other); those of 2-D and 3-D blocks, whose
+// lines of CMAX / 2 samples at most leave no more, run their pass once.
+template <int D, int NT, class F>
+DEVI void coarse_chunks(int half, int lines, F each) {
+  const int nch = half / 4;
+  if constexpr (D == 1) {
+    const int lg = min(ceil_log2(nch), ceil_log2(NT));
+    for (int ch = threadIdx.x & ((1 << lg) - 1); ch < nch; ch += 1 << lg) each(ch, lg);
+  } else {
+    const int lg = ceil_log2(nch), ch = threadIdx.x & ((1 << lg) - 1);
+    if (ch < nch && (int)(threadIdx.x >> lg) < lines) each(ch, lg);
+  }
+}
+
 // (lines, n) -> (lines, n / 2); n / 2 and the offsets multiples of 4
 template <int L, int NT>
-DEVI void coarse_rows_down(float* sm, int src, int dst, int lines, int n, const Filter& f) {
+DEVI void coarse_rows_down(float* sm, int src, int dst, int lines, int n, int ch, int lg, const Filter& f) {
   constexpr int PO = 4, W4 = (2 * PO + L - 2 + 3) / 4;
-  const int o = n >> 1, nch = o / PO, lg = min(ceil_log2(nch), ceil_log2(NT));
-  const int l0 = threadIdx.x >> lg, ls = NT >> lg;
-  for (int ch = threadIdx.x & ((1 << lg) - 1); ch < nch; ch += 1 << lg) {  // more than one: lines of over 8 NT samples
-    int off[W4];
+  const int o = n >> 1, l0 = threadIdx.x >> lg;
+  int off[W4];
+#pragma unroll
+  for (int v = 0; v < W4; ++v) {
+    const int i = 2 * PO * ch + 4 * v;
+    off[v] = i >= n ? i - n : i;
+  }
+  const float* in = sm + src + l0 * n;
+  float* out = sm + dst + l0 * o + PO * ch;
+  const int ls = NT >> lg;
+  for (int l = l0; l < lines; l += ls, in += ls * n, out += ls * o) {
+    float win[4 * W4];
 #pragma unroll
     for (int v = 0; v < W4; ++v) {
-      const int i = 2 * PO * ch + 4 * v;
-      off[v] = i >= n ? i - n : i;
+      const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
+      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
     }
-    const float* in = sm + src + l0 * n;
-    float* out = sm + dst + l0 * o + PO * ch;
-    for (int l = l0; l < lines; l += ls, in += ls * n, out += ls * o) {
-      float win[4 * W4];
+    float r[PO];
 #pragma unroll
-      for (int v = 0; v < W4; ++v) {
-        const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
-        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
-      }
-      float r[PO];
+    for (int q = 0; q < PO; ++q) {
+      r[q] = 0.f;
 #pragma unroll
-      for (int q = 0; q < PO; ++q) {
-        r[q] = 0.f;
-#pragma unroll
-        for (int t = 0; t < L; ++t) r[q] = fmaf(f.h[t], win[2 * q + t], r[q]);
-      }
-      *reinterpret_cast<float4*>(out) = make_float4(r[0], r[1], r[2], r[3]);
+      for (int t = 0; t < L; ++t) r[q] = fmaf(f.h[t], win[2 * q + t], r[q]);
     }
+    *reinterpret_cast<float4*>(out) = make_float4(r[0], r[1], r[2], r[3]);
   }
 }
 
@@ -611,40 +624,39 @@ DEVI void coarse_cols_down(float* sm, int src, int dst, int outer, int n, int in
 // (lines, n / 2) -> (lines, n): four half-resolution positions per item; n / 2 and the offsets multiples of
 // 4; combine: dst = alpha dst + value
 template <int L, int NT>
-DEVI void coarse_rows_up(float* sm, int src, int dst, int lines, int n, const Filter& f, bool combine, float alpha) {
+DEVI void coarse_rows_up(float* sm, int src, int dst, int lines, int n, int ch, int lg, const Filter& f, bool combine,
+                         float alpha) {
   constexpr int H = L / 2, PO = 4, A = (H - 1 + 3) & ~3, NW = (A + PO) / 4;
-  const int half = n >> 1, nch = half / PO, lg = min(ceil_log2(nch), ceil_log2(NT));
-  const int l0 = threadIdx.x >> lg, ls = NT >> lg;
-  for (int ch = threadIdx.x & ((1 << lg) - 1); ch < nch; ch += 1 << lg) {
-    int off[NW];
+  const int half = n >> 1, l0 = threadIdx.x >> lg;
+  int off[NW];
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
+    const int k = PO * ch - A + 4 * v;
+    off[v] = k < 0 ? k + half : k;
+  }
+  const float* in = sm + src + l0 * half;
+  float* out = sm + dst + l0 * n + 2 * PO * ch;
+  const int ls = NT >> lg;
+  for (int l = l0; l < lines; l += ls, in += ls * half, out += ls * n) {
+    float win[A + PO];
 #pragma unroll
     for (int v = 0; v < NW; ++v) {
-      const int k = PO * ch - A + 4 * v;
-      off[v] = k < 0 ? k + half : k;
+      const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
+      win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
     }
-    const float* in = sm + src + l0 * half;
-    float* out = sm + dst + l0 * n + 2 * PO * ch;
-    for (int l = l0; l < lines; l += ls, in += ls * half, out += ls * n) {
-      float win[A + PO];
+    float v[2 * PO];
 #pragma unroll
-      for (int v = 0; v < NW; ++v) {
-        const float4 x = *reinterpret_cast<const float4*>(in + off[v]);
-        win[4 * v] = x.x; win[4 * v + 1] = x.y; win[4 * v + 2] = x.z; win[4 * v + 3] = x.w;
-      }
-      float v[2 * PO];
+    for (int r = 0; r < 2 * PO; ++r) {
+      v[r] = 0.f;
 #pragma unroll
-      for (int r = 0; r < 2 * PO; ++r) {
-        v[r] = 0.f;
+      for (int j = 0; j < H; ++j) v[r] = fmaf(f.h[2 * j + (r & 1)], win[A + (r >> 1) - j], v[r]);
+    }
 #pragma unroll
-        for (int j = 0; j < H; ++j) v[r] = fmaf(f.h[2 * j + (r & 1)], win[A + (r >> 1) - j], v[r]);
-      }
-#pragma unroll
-      for (int r = 0; r < 2 * PO; r += 4) {
-        float4 s = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
-        float4* o = reinterpret_cast<float4*>(out + r);
-        if (combine) s = axpy4(alpha, *o, s);
-        *o = s;
-      }
+    for (int r = 0; r < 2 * PO; r += 4) {
+      float4 s = make_float4(v[r], v[r + 1], v[r + 2], v[r + 3]);
+      float4* o = reinterpret_cast<float4*>(out + r);
+      if (combine) s = axpy4(alpha, *o, s);
+      *o = s;
     }
   }
 }
@@ -687,7 +699,8 @@ DEVI void coarse_cols_up(float* sm, int src, int dst, int outer, int n, int inne
 }
 
 // Analysis of strided axes whose inner count is no multiple of 4 (rows halved to 18, say; the synthesis has whole
-// rows): a thread forms four outputs of one column from one window.
+// rows): a thread forms four outputs of one column from one window.  In the kernels of small blocks only: the larger
+// ones' code stays short, since much of a launch of few work-groups is the wait for it.
 template <int L, int NT>
 DEVI void coarse_cols_down_1(float* sm, int src, int dst, int outer, int n, int inner, const Filter& f) {
   constexpr int PO = 4, WN = 2 * PO + L - 2;
@@ -714,23 +727,24 @@ DEVI void coarse_cols_down_1(float* sm, int src, int dst, int outer, int n, int 
 // One instantiation serves every level: variants of its own for the largest and the smallest levels were
 // up to 20 % faster per pass in a loop of the same launch, but between other launches each variant's
 // first pass waits for its code (~100 cycles per 64 bytes), which cost more than it gave.
-template <int L, int NT>
+template <int D, int L, int NT>
 DEVI void coarse_analysis(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f) {
   const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), o = n >> 1;
   const int inner = ax == 0 ? n1 * n2 : (ax == 1 ? n2 : 1), outer = ax == 0 ? 1 : (ax == 1 ? n0 : n0 * n1);
   const bool v4 = ((src | dst) & 3) == 0;
   if (n < L) return coarse_analysis_w<L, true, NT>(sm, src, dst, n0, n1, n2, ax, f);
   if (ax == 2) {
-    if (v4 && o % 4 == 0) return coarse_rows_down<L, NT>(sm, src, dst, outer, n, f);
+    if (v4 && o % 4 == 0)
+      return coarse_chunks<D, NT>(o, outer, [&](int ch, int lg) { coarse_rows_down<L, NT>(sm, src, dst, outer, n, ch, lg, f); });
   } else if (v4 && inner % 4 == 0 && ceil_log2(inner / 4) <= ceil_log2(NT)) {
     return coarse_cols_down<L, NT>(sm, src, dst, outer, n, inner, f);
-  } else if (o % 4 == 0) {
+  } else if (NT <= 512 && o % 4 == 0) {
     return coarse_cols_down_1<L, NT>(sm, src, dst, outer, n, inner, f);
   }
   coarse_analysis_w<L, false, NT>(sm, src, dst, n0, n1, n2, ax, f);
 }
 // gout: the block's final place in global memory, taken only where *direct says so
-template <int L, int NT>
+template <int D, int L, int NT>
 DEVI void coarse_synthesis(float* sm, int src, int dst, int n0, int n1, int n2, int ax, const Filter& f, bool combine,
                            float alpha, float* gout = nullptr, bool* direct = nullptr) {
   const int n = ax == 0 ? n0 : (ax == 1 ? n1 : n2), half = n >> 1;
@@ -738,7 +752,10 @@ DEVI void coarse_synthesis(float* sm, int src, int dst, int n0, int n1, int n2, 
   const bool v4 = ((src | dst) & 3) == 0;
   if (half < L / 2) return coarse_synthesis_w<L, true, NT>(sm, src, dst, n0, n1, n2, ax, f, combine, alpha);
   if (ax == 2) {
-    if (v4 && half % 4 == 0) return coarse_rows_up<L, NT>(sm, src, dst, outer, n, f, combine, alpha);
+    if (v4 && half % 4 == 0)
+      return coarse_chunks<D, NT>(half, outer, [&](int ch, int lg) {
+        coarse_rows_up<L, NT>(sm, src, dst, outer, n, ch, lg, f, combine, alpha);
+      });
   } else if (v4 && inner % 4 == 0 && ceil_log2(inner / 4) <= ceil_log2(NT)) {
     if (direct) *direct = true;
     return coarse_cols_up<L, NT>(sm, src, dst, outer, n, inner, f, combine, alpha, gout);
@@ -941,17 +958,17 @@ DEVI void lp_coarse_block(const TailTask* tp, int inst, const Filter& f, float* 
     const int a0 = D >= 3 ? m0 >> j : 1, a1 = D >= 2 ? m1 >> j : 1, a2 = m2 >> j;
     const int nxt = off + a0 * a1 * a2;
     if (D == 1) {
-      coarse_analysis<L, NT>(sm, off, nxt, a0, a1, a2, 2, f);
+      coarse_analysis<D, L, NT>(sm, off, nxt, a0, a1, a2, 2, f);
     } else if (D == 2) {
-      coarse_analysis<L, NT>(sm, off, tmpA, a0, a1, a2, 2, f);
+      coarse_analysis<D, L, NT>(sm, off, tmpA, a0, a1, a2, 2, f);
       __syncthreads();
-      coarse_analysis<L, NT>(sm, tmpA, nxt, a0, a1, a2 >> 1, 1, f);
+      coarse_analysis<D, L, NT>(sm, tmpA, nxt, a0, a1, a2 >> 1, 1, f);
     } else {
-      coarse_analysis<L, NT>(sm, off, tmpA, a0, a1, a2, 2, f);
+      coarse_analysis<D, L, NT>(sm, off, tmpA, a0, a1, a2, 2, f);
       __syncthreads();
-      coarse_analysis<L, NT>(sm, tmpA, tmpB, a0, a1, a2 >> 1, 1, f);
+      coarse_analysis<D, L, NT>(sm, tmpA, tmpB, a0, a1, a2 >> 1, 1, f);
       __syncthreads();
-      coarse_analysis<L, NT>(sm, tmpB, nxt, a0, a1 >> 1, a2 >> 1, 0, f);
+      coarse_analysis<D, L, NT>(sm, tmpB, nxt, a0, a1 >> 1, a2 >> 1, 0, f);
     }
     __syncthreads();
     off = nxt;
@@ -972,18 +989,18 @@ DEVI void lp_coarse_block(const TailTask* tp, int inst, const Filter& f, float* 
     const int cur = off - a0 * a1 * a2;  // A_j precedes A_{j+1}
     const float alpha = tp->coef[j];
     if (D == 1) {
-      coarse_synthesis<L, NT>(sm, off, cur, a0, a1, a2, 2, f, true, alpha);
+      coarse_synthesis<D, L, NT>(sm, off, cur, a0, a1, a2, 2, f, true, alpha);
     } else if (D == 2) {
       // contiguous axis first: (a1/2, a2/2) -> (a1/2, a2) in tmpA, then rows -> A_j
-      coarse_synthesis<L, NT>(sm, off, tmpA, a0, a1 >> 1, a2, 2, f, false, 0.f);
+      coarse_synthesis<D, L, NT>(sm, off, tmpA, a0, a1 >> 1, a2, 2, f, false, 0.f);
       __syncthreads();
-      coarse_synthesis<L, NT>(sm, tmpA, cur, a0, a1, a2, 1, f, true, alpha, g, d);
+      coarse_synthesis<D, L, NT>(sm, tmpA, cur, a0, a1, a2, 1, f, true, alpha, g, d);
     } else {
-      coarse_synthesis<L, NT>(sm, off, tmpA, a0 >> 1, a1 >> 1, a2, 2, f, false, 0.f);
+      coarse_synthesis<D, L, NT>(sm, off, tmpA, a0 >> 1, a1 >> 1, a2, 2, f, false, 0.f);
       __syncthreads();
-      coarse_synthesis<L, NT>(sm, tmpA, tmpB, a0 >> 1, a1, a2, 1, f, false, 0.f);
+      coarse_synthesis<D, L, NT>(sm, tmpA, tmpB, a0 >> 1, a1, a2, 1, f, false, 0.f);
       __syncthreads();
-      coarse_synthesis<L, NT>(sm, tmpB, cur, a0, a1, a2, 0, f, true, alpha, g, d);
+      coarse_synthesis<D, L, NT>(sm, tmpB, cur, a0, a1, a2, 0, f, true, alpha, g, d);
     }
     __syncthreads();
     off = cur;
