@@ -176,7 +176,7 @@ int dense_from(int D, int L, const int b[3], int nlev) {
   if (D != 2) return -1;
   for (int j = 0; j < nlev; ++j)
     if ((b[1] >> j) <= kDenseSide && (b[2] >> j) <= kDenseSide)
-      return nlev > 1 || std::min(b[1], b[2]) < L ? j : -1;
+      return nlev - j > kDenseLevels ? -1 : nlev > 1 || std::min(b[1], b[2]) < L ? j : -1;
   return -1;
 }
 

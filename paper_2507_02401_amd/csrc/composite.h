@@ -31,7 +31,15 @@ constexpr double kDaubechies[kMaxTaps / 2][kMaxTaps] = {
      -0.00039174037337694705, 0.00067544940645056933, -0.00011747678412476953}};
 
 constexpr int kDenseSide = 32;   // longest axis of a block whose levels run as matrix products
-constexpr int kDenseLevels = 5;  // levels such an axis can have
+constexpr int kDenseLevels = 4;  // levels below such a block: the coarsest one is never visited, so 2 divides its sides too
+
+// Level of row r of an axis of length n that stacks the rows of every level, finest first: the distance n - r from
+// the end lies in (n / 2^i, n / 2^(i-1)] for level i.  Above the number of levels for rows past the last one's.
+constexpr int dense_level(int n, int r) {
+  int level = 1;
+  for (int q = 1; q <= kDenseLevels; ++q) level += n - r <= (n >> q);
+  return level;
+}
 
 // c[n / 2][i - 1]: C_i with a_i[k] = sum_j C_i[j] x[(j + 2^i k) mod n], the i-level low-pass analysis of a
 // periodic axis of even length n <= 32 that 2^i divides; formed in FP64, rounded once.

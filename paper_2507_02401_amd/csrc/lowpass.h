@@ -796,9 +796,8 @@ DEVI DenseLds dense_lds(int tmp, int tmp_floats, int n1, int n2) {
 }
 
 // T1, T2 (one array for a square block; zero outside s x n), the rows' levels (0: no row) and the
-// coefficients c_0 .. c_K of the K levels below the (n1, n2) block; no barrier.  Row r of an axis of length n:
-// its distance u = n - r from the end lies in (n / 2^i, n / 2^(i-1)] for level i, where it is row
-// k = n / 2^(i-1) - u.
+// coefficients c_0 .. c_K of the K <= kDenseLevels levels below the (n1, n2) block; no barrier.  Row r of an axis of
+// length n is row n / 2^(i-1) - (n - r) of its level i.
 template <int L, int NT>
 DEVI void dense_tables(float* sm, const DenseLds& d, const TailTask* tp, int j0, int n1, int n2, int K) {
   constexpr int N = kDenseSide * kDenseSide;
@@ -806,9 +805,7 @@ DEVI void dense_tables(float* sm, const DenseLds& d, const TailTask* tp, int j0,
   for (int e = threadIdx.x; e < axes * N; e += NT) {
     const int ax = e / N, r = e / kDenseSide % kDenseSide, j = e % kDenseSide;
     const int n = ax ? n2 : n1, u = n - r;
-    int lev = 1;
-#pragma unroll
-    for (int q = 1; q < kDenseLevels; ++q) lev += u <= (n >> q);
+    const int lev = dense_level(n, r);
     const bool row = u > 0 && lev <= K;
     const int i = j - (((n >> (lev - 1)) - u) << lev);
     const int at = row && j < n ? (n / 2 * kDenseLevels + lev - 1) * kDenseSide + (i < 0 ? i + n : i) : 0;
