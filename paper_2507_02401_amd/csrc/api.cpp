@@ -323,8 +323,8 @@ int64_t lp_tail_limit(const Geo&) {
   return kCoarseMaxBlockBig;
 }
 
-// A launch holds fewer than 2^32 threads (its grid is rounded up to a multiple of 8).
-bool launchable(double wgs) { return (wgs + 7) * kThreads < 4294967296.0; }
+// Whether the runtime takes a level launch (its grid is rounded up to a multiple of 8).
+bool launchable(double wgs) { return wgs < 1e15 && launch_fits((int64_t)wgs + 7, kThreads); }
 
 // Rows that a launch stages: whole 16-byte groups (the callers' and the level arrays start at 16 bytes).
 bool whole_rows(int kind, const Geo& g, int level) {

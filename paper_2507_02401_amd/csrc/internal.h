@@ -289,6 +289,9 @@ class CovApply {
 // Largest parts() a prepare_dot of this grid can produce (0 when it never applies).
 int64_t cov_dot_partials_max(int ndim, const int64_t* shape);
 
+// The runtime takes launches of fewer than 2^32 threads.
+inline bool launch_fits(int64_t groups, int threads) { return groups >= 0 && groups < ((int64_t)1 << 32) / threads; }
+
 // Host filter derivation (filters.cpp).
 bool daubechies_filter(int order, double* h_out);
 

@@ -1219,8 +1219,8 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
   float* mid = transpose ? vext : y;
   const int64_t mid_cap = g.D < 3 || g.m < 2 ? 0 : transpose ? batch * ext_dims(g, 1).stored() : batch * g.size(0);
   for (int i = 1; i < g.m; ++i) {
+    SymLaunch l{};
     if (sym_split(g, i, batch) && sym_mid_floats(g, i, batch) <= mid_cap) {
-      SymLaunch l{};
       l.kind = 0;
       l.D = 2;
       l.zx = transpose;
@@ -1235,7 +1235,6 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
       l.t.bs_in = (int64_t)l.t.ni[1] * l.t.si[1];
       l.t.bs_out = (int64_t)l.t.no[1] * l.t.so[1];
       l.grid = sym_tiling(l.t, sym_tiles(2, g.L).t, batch * g.dims[i - 1][0]);
-      out->push_back(l);
       SymLaunch c{};
       c.kind = 4;
       c.zx = transpose;
@@ -1247,10 +1246,14 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
       c.col.nblk = (int32_t)((c.col.slice / 4 + 255) / 256);
       c.col.nchunk = (c.col.no + kColChunk - 1) / kColChunk;
       c.grid = (int64_t)c.col.nblk * c.col.nchunk * batch;
-      out->push_back(c);
-      continue;
+      // slices of a few samples take more work-groups than the tile: up to four times (64 x 4 x 4)
+      if (launch_fits(l.grid, kSymThreads) && launch_fits(c.grid, 256)) {
+        out->push_back(l);
+        out->push_back(c);
+        continue;
+      }
+      l = SymLaunch{};
     }
-    SymLaunch l{};
     l.kind = 0;
     l.D = g.D;
     l.zx = transpose;
@@ -1388,7 +1391,8 @@ es_status sym_schedule(const SymGeo& g, int64_t batch, const float* x, float* y,
     out->push_back(fl);
   }
   for (const SymLaunch& l : *out)
-    if (l.grid > 0x7fffffffll) return sym_einval("a level needs more than 2^31-1 work-groups (%lld)", l.grid);
+    if (!launch_fits(l.grid, l.kind == 0 && l.D == 3 && g.L <= 12 ? kSym3Threads : kSymThreads))
+      return sym_einval("a level needs 2^32 threads or more (%lld work-groups)", l.grid);
   return ES_OK;
 }
 
