@@ -455,13 +455,14 @@ __global__ void __launch_bounds__(kCgThreads) k_gm_final(int per, int nblk, cons
 // wave per vector), the new Gram column G[j][k] = G[k][j] = <v_j, v_k> into the instance's
 // (m+1) x (m+1) Gram matrix, and c = 2 h - G h (j, i <= k) with h = V^T w: the two classical
 // Gram-Schmidt passes of CGS2, the second written through the Gram matrix (exact when the first
-// subtraction is).
-constexpr int kGmCoefThreads = 1024;
+// subtraction is).  A wave per inner product of a step of eight vectors; fewer waves, which take the same sums
+// in turn, where a launch of so many instances would hold 2^32 threads.
+constexpr int kGmCoefThreads = 1024, kGmCoefThreadsMany = 128;
 __global__ void __launch_bounds__(kGmCoefThreads) k_gm_coef(int k, int per, int nblk, const float* __restrict__ part,
                                                             float* __restrict__ G, int ldG, float* __restrict__ c, int ldc) {
   __shared__ float h[2 * (kGmMaxBasis + 1)];  // h[0..k], then the Gram column [k+1 .. 2k+1]
   const int inst = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int v = wave; v < 2 * (k + 1); v += kGmCoefThreads / 64) {
+  for (int v = wave; v < 2 * (k + 1); v += (int)blockDim.x / 64) {
     const float* p = part + (int64_t)v * nblk + (int64_t)inst * per;
     KSum acc;
     for (int i = lane; i < per; i += 64) acc.add(p[i]);
@@ -1025,6 +1026,7 @@ es_status es_tikhonov_gmres(int ndim, const int64_t* shape, int64_t batch, int o
   // the rate of the steps seen so far would reach 80 % of the way; a step past the end changes
   // nothing but the time.  Problems whose step outweighs the wait: after every step.
   const bool lag = n * batch <= (int64_t)1 << 22;
+  const int coef_threads = launch_fits(batch, kGmCoefThreads) ? kGmCoefThreads : kGmCoefThreadsMany;
   while (1.0 > rtol && it < max_iter) {
     const int steps = std::min(m, max_iter - it);
     int K = 0, read = 0, next = lag ? (rtol > 0 ? std::min(2, steps) : steps) : 1;
@@ -1043,7 +1045,7 @@ es_status es_tikhonov_gmres(int ndim, const int64_t* shape, int64_t batch, int o
       Parts q;
       if ((st = ok("GMRES inner-product launch")) != ES_OK || (st = reduced(2 * (k + 1), &q)) != ES_OK) return st;
       float* col = cd + (int64_t)(k + 1) * row;
-      hipLaunchKernelGGL(k_gm_coef, dim3((unsigned)batch), dim3(kGmCoefThreads), 0, hs, k, q.per, q.nblk, q.p, Gd, ld, col, ld);
+      hipLaunchKernelGGL(k_gm_coef, dim3((unsigned)batch), dim3((unsigned)coef_threads), 0, hs, k, q.per, q.nblk, q.p, Gd, ld, col, ld);
       if ((st = ok("GMRES coefficient launch")) != ES_OK) return st;
       hipLaunchKernelGGL(k_gm_sub, grid, blk, 0, hs, n, (int)per, k + 1, (const float*)V, vs, (const float*)col, ld, w, part);
       if ((st = ok("GMRES update launch")) != ES_OK || (st = normalise(w, V + (int64_t)(k + 1) * vs, col)) != ES_OK) return st;
