@@ -1087,7 +1087,7 @@ int call_regions(const void* in, const void* out, int64_t bytes, const void* ws,
 int64_t round8(int64_t v) { return (v + 7) & ~(int64_t)7; }
 
 es_status run_launch(const Launch& l, const Filter& f, hipStream_t stream, const Task* table, int count,
-                     int total_wg, const TailTask* ttable) {
+                     int total_wg, const TailTask* ttable, const FilterBank* bank = nullptr) {
   if (total_wg <= 0) return ES_OK;
   const int grid = (int)round8(total_wg);
   if (!l.is_tail) {
@@ -1098,6 +1098,7 @@ es_status run_launch(const Launch& l, const Filter& f, hipStream_t stream, const
     a.vec = l.vec;
     a.reverse = l.reverse;
     a.t0 = l.task;
+    a.bank = bank;
     ES_HIP(launch_level(l.kind, l.D, l.L, l.variant, a, grid, f, stream), "level kernel launch");
   } else {
     TailArgs a{};
@@ -1105,6 +1106,7 @@ es_status run_launch(const Launch& l, const Filter& f, hipStream_t stream, const
     a.count = count;
     a.total_wg = total_wg;
     a.t0 = l.tail;
+    a.bank = bank;
     ES_HIP(launch_tail(l.kind, l.D, l.L, a, grid, l.lds, f, stream), "tail kernel launch");
   }
   return ES_OK;
@@ -1571,9 +1573,7 @@ es_status plan_launch_group(es_plan* p, const PlanGroup& gr, hipStream_t s) {
   if (gr.mixed) {
     FilterBank bank;
     for (int o = 1; o <= kMaxTaps / 2; ++o) bank.f[o - 1] = p->filt[2 * o];
-    Launch l = gr.proto;
-    l.L = kMixedTaps;
-    return run_launch(l, bank.f[0], s, tasks, (int)gr.inst.size(), gr.total_wg, tails);
+    return run_launch(gr.proto, p->filt[gr.proto.L], s, tasks, (int)gr.inst.size(), gr.total_wg, tails, &bank);
   }
   return run_launch(gr.proto, p->filt[gr.proto.L], s, tasks, (int)gr.inst.size(), gr.total_wg, tails);
 }

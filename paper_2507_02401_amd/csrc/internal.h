@@ -69,6 +69,7 @@ struct TaskArgs {
   int32_t vec;        // 1: every staged row is 16-byte aligned and a multiple of 4 floats
   int32_t reverse;    // 1: walk the tiles in reverse order (cache reuse between launches)
   Task t0;
+  const FilterBank* bank;  // host: the filters of a table launch that holds several lengths, else null (kernels get null)
 };
 
 // Tail: all coarse levels of one instance in one work-group (LDS resident).
@@ -100,6 +101,7 @@ struct TailArgs {
   int32_t count;
   int32_t total_wg;
   TailTask t0;
+  const FilterBank* bank;  // as in TaskArgs
 };
 
 enum KernelKind {
@@ -128,9 +130,8 @@ struct TileShape {
              // full-res for synthesis kinds); padded dims are 1
 };
 
-// Launchers (kernels.hip).  All return hipError_t of the launch.  taps = kMixedTaps: a table launch of
-// instances of different filter lengths (2-D low-pass kinds); f is then the first filter of a FilterBank.
-constexpr int kMixedTaps = 0;
+// Launchers (kernels.hip).  All return hipError_t of the launch.  args.bank: a table launch of instances of
+// different filter lengths (2-D low-pass kinds), which reads neither taps nor f.
 hipError_t launch_level(int kind, int ndim, int taps, int variant, const TaskArgs& args, int grid,
                         const Filter& f, hipStream_t stream);
 hipError_t launch_tail(int kind, int ndim, int taps, const TailArgs& args, int grid, size_t lds_bytes,

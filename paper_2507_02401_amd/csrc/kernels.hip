@@ -1965,9 +1965,7 @@ hipError_t launch_level(int kind, int ndim, int taps, int variant, const TaskArg
                         hipStream_t stream) {
   // the vector path needs 16-byte rows; the host decides per launch (all tasks agree)
   const bool vec = args.vec != 0;
-  if (taps == kMixedTaps)
-    return ndim == 2 ? launch_mixed_level(kind, variant, args, grid, *reinterpret_cast<const FilterBank*>(&f), stream)
-                     : hipErrorInvalidValue;
+  if (args.bank) return ndim == 2 ? launch_mixed_level(kind, variant, args, grid, *args.bank, stream) : hipErrorInvalidValue;
   switch (kind) {
     case K_LP_DOWN: return launch_k<K_LP_DOWN>(ndim, taps, variant, vec, args, grid, f, stream);
     case K_LP_UP: return launch_k<K_LP_UP>(ndim, taps, variant, vec, args, grid, f, stream);
@@ -2001,10 +1999,8 @@ hipError_t launch_level(int kind, int ndim, int taps, int variant, const TaskArg
 
 hipError_t launch_tail(int kind, int ndim, int taps, const TailArgs& args, int grid, size_t lds_bytes,
                        const Filter& f, hipStream_t stream) {
-  if (taps == kMixedTaps)
-    return ndim == 2 && kind == 3
-               ? launch_mixed_coarse(args, grid, lds_bytes, *reinterpret_cast<const FilterBank*>(&f), stream)
-               : hipErrorInvalidValue;
+  if (args.bank)
+    return ndim == 2 && kind == 3 ? launch_mixed_coarse(args, grid, lds_bytes, *args.bank, stream) : hipErrorInvalidValue;
   switch (ndim) {
     case 1: return launch_tail_d<1>(kind, taps, args, grid, lds_bytes, f, stream);
     case 2: return launch_tail_d<2>(kind, taps, args, grid, lds_bytes, f, stream);

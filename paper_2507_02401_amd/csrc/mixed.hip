@@ -92,18 +92,22 @@ hipError_t launch_mixed_level(int kind, int variant, const TaskArgs& args, int g
   const bool vec = args.vec != 0;
   if (args.table == nullptr || (kind != K_LP_DOWN && kind != K_LP_UP) || (kind == K_LP_DOWN && !vec))
     return hipErrorInvalidValue;
-  if (variant == 0) launch_v<0>(kind, vec, args, grid, bank, s);
-  else if (variant == 2) launch_v<2>(kind, vec, args, grid, bank, s);
-  else launch_v<1>(kind, vec, args, grid, bank, s);
+  TaskArgs a = args;
+  a.bank = nullptr;
+  if (variant == 0) launch_v<0>(kind, vec, a, grid, bank, s);
+  else if (variant == 2) launch_v<2>(kind, vec, a, grid, bank, s);
+  else launch_v<1>(kind, vec, a, grid, bank, s);
   return hipGetLastError();
 }
 
 hipError_t launch_mixed_coarse(const TailArgs& args, int grid, size_t lds_bytes, const FilterBank& bank, hipStream_t s) {
   if (args.table == nullptr) return hipErrorInvalidValue;
+  TailArgs a = args;
+  a.bank = nullptr;
   if (lds_bytes <= sizeof(float) * coarse_lds_floats(2, kCoarseMaxBlock))
-    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlock>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlock)), 0, s, args, bank);
+    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlock>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlock)), 0, s, a, bank);
   else
-    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlockBig>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlockBig)), 0, s, args, bank);
+    hipLaunchKernelGGL((k_mixed_coarse<kCoarseMaxBlockBig>), dim3(grid), dim3(coarse_threads(kCoarseMaxBlockBig)), 0, s, a, bank);
   return hipGetLastError();
 }
 
