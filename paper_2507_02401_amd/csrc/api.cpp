@@ -484,7 +484,9 @@ bool lp_split(const Geo& g, int level, int64_t batch) {
 
 // Whether a level with two families streams by rule: 3-D levels that then still have a work-group or two per CU,
 // except the low-pass synthesis of up to 10 taps, whose wide plain tile is as fast (256^3 db4: 94 -> 82 us
-// a call); 2-D levels take the plain 16 x 64 tile at every size (64 x 1024^2 db8: 254 -> 241 us a call).
+// a call); 2-D levels take the plain 16 x 64 tile at every size (64 x 1024^2 db8: 254 -> 241 us a call).  The
+// limits are whole multiples of the 256 CUs or half of them; level_launch takes the other family where the modelled
+// times differ by more than kModelMargin.
 bool streams(int kind, const Geo& g, int level, int64_t batch) {
   if (g.D != 3) return false;
   const int sk = streamed_kind(kind);
@@ -1588,11 +1590,11 @@ es_status plan_launch_all(es_plan* p, hipStream_t s) {
 }
 
 // Graph capture with concurrent chains: instances of different launch classes share no launches, so the
-// groups of a class are a chain that no other chain waits for.  The
-// chains are dealt to the stream and `nside` side streams, longest first to the least loaded, forked once
-// at the start and joined once at the end.  Joining the branches after every phase instead cost
-// more than the overlap gained (4 branches, 48 instances: 285-440 us, differing from process to process).  Events are created here and destroyed by the caller
-// after the capture ends.
+// groups of a class are a chain that no other chain waits for.  The chains are dealt to the stream and `nside`
+// side streams, longest first to the least loaded, forked once at the start and joined once at the end.  Joining
+// the branches after every phase instead cost more than the overlap gained (4 branches, 48 instances, a launch per
+// filter length: 285-440 us, differing from process to process).  Events are created here and destroyed by the
+// caller after the capture ends.
 es_status plan_launch_all_forked(es_plan* p, hipStream_t s, hipStream_t* side, int nside,
                                  std::vector<hipEvent_t>* events) {
   auto new_event = [&](hipEvent_t* e) -> es_status {
@@ -1872,8 +1874,6 @@ void plan_layout(es_plan* p, bool persist) {
   g_mode = keep;
 }
 
-// Host part of plan creation: geometries, workspace offsets, frozen schedules, launch groups and
-// host tables (no device call).
 // The tiles of the plain level launches from the work-groups that each launch really has: members of one
 // phase, kind and alignment share it.  Instances whose tiles the tune cache chose keep them.
 void plan_shared_tiles(const es_plan* p, std::vector<Schedule>* scs, const std::vector<std::vector<int>>& phases) {
@@ -1900,6 +1900,8 @@ void plan_shared_tiles(const es_plan* p, std::vector<Schedule>* scs, const std::
   }
 }
 
+// Host part of plan creation: geometries, workspace offsets, frozen schedules, launch groups and
+// host tables (no device call).
 es_status plan_build(const es_desc* descs, int32_t count, int op, es_plan** out, int64_t lp_coarse = -1) {
   *out = nullptr;
   if (count < 0 || (count > 0 && !descs)) return fail(ES_EINVAL, "descs must hold count >= 0 entries");
@@ -2677,8 +2679,9 @@ es_status es_plan_execute(es_plan* p, const float* const* in, float* const* out,
     // kernels read everything through the device tables, so the captured graph stays valid
     // when the caller's pointers change (only the tables are refreshed, above)
     // one chain, or, with ESWAVE_PLAN_BRANCHES, that many parallel branches at most.  48 instances of 23 M
-    // voxels, same / new buffers on each call, us: 1 branch 216 / 218, 2 branches 200 / 245, 3 192 / 265;
-    // 36 instances of 13.6 M voxels: 148 / 149, 145 / 187, 152 / 208 -- submitting a branched graph costs the
+    // voxels, calls one after the other with the same / new buffers on each, and one call from submission to a
+    // synchronisation, us: 1 branch 217 / 218 / 256, 2 branches 194 / 236 / 229, 3 190 / 254 / 191; 36 instances
+    // of 13.6 M voxels: 148 / 149 / 181, 147 / 181 / 153, 148 / 206 / 145 -- submitting a branched graph costs the
     // host 3.5 us a launch against 1.5 us for one chain.
     constexpr int kSide = 15;
     hipStream_t cap = nullptr, side[kSide] = {};

@@ -63,8 +63,9 @@ __global__ void __launch_bounds__(NT) k_lp_up(TaskArgs args, Filter f) {
 // and 2 and walks axis 0 in sequence.  Planes: axes 2 and 0 as the 2-D tile on every plane of axis 1 (rows
 // of a plane are b1 * b2 apart), a quarter of the level's samples to scratch.  Axis-1 pass: lines of that
 // array.  Taps and axes (2, 0, 1) in the order of the 3-D tiles: identical bits.
-// 4 x 128^3, 16 taps: the two finest levels 33.1 + 16.6 -> (13.3 + 5.4) + (5.2 + 4.9) us.  What bounds the
-// planes now: their row and column filters (46 x 142 staged samples for 16 x 64 outputs).
+// 4 x 128^3, 16 taps: the two finest levels 33.1 + 16.6 -> (13.4 + 5.5) + (4.7 + 5.0) us.  The
+// planes (42 MB at 3.1 TB/s, 34 % of the vector issue, memory units never stalled) are bound by no one unit: a
+// work-group stages 46 x 142 samples and filters rows, then columns, with a barrier between.
 template <int L, int T1, int T2, int NT>
 __global__ void __launch_bounds__(NT) k_lp_down_p(TaskArgs args, Filter f) {
   __shared__ LpDownSmem<2, L, 1, T1, T2> sm;
@@ -76,7 +77,8 @@ __global__ void __launch_bounds__(NT) k_lp_down_p(TaskArgs args, Filter f) {
 
 // Axis 1 of a split level: a thread takes C outputs of four adjacent lines, all loads of its window in
 // flight before the first sum; chunks of the same lines, which share most of their windows, follow each
-// other on one XCD.  Memory (L2) bound.
+// other on one XCD.  A launch of one work-group per CU or fewer: bound by the latency of its loads (5.5 us for
+// 12.6 MB, 5.0 us for 1.6 MB; vector units 10 % busy, memory units never stalled).
 template <int L, int C, int NT, bool VEC>
 __global__ void __launch_bounds__(NT) k_lp_down_a1(TaskArgs args, Filter f) {
   constexpr int W = 2 * C + L - 2;
@@ -1269,8 +1271,9 @@ DEVI void fbc_synthesis_w(float* sm, int src, int dst, int S0, int S1, int b0, i
 // and steps along the other one; windows are 16-byte vectors along the contiguous axis and four columns
 // per lane along the strided ones; per output the taps are summed in the order of the _w versions.  A pass
 // is bound by issued instructions and by the barrier after it.  One block of a launch alone, us, against
-// passes that split and wrapped every index: 64^2 16 taps 11.8 -> 10.5; 16^3 8 taps 8.6 -> 7.1 and back
-// 8.7 -> 8.2; calls, 64 blocks of 64^2, 16 taps 16.4 -> 14.4 and back 14.8 -> 12.8, 16 of 80 x 96 back 16.2 -> 12.4.
+// passes that split and wrapped every index: 64^2 16 taps 11.8 -> 10.5 (9.3 with the 512 threads of small
+// blocks); 16^3 8 taps 8.6 -> 7.1 (6.4) and back 8.7 -> 8.2 (6.9); calls, 64 blocks of 64^2, 16 taps
+// 16.4 -> 14.4 and back 14.8 -> 12.8, 16 of 80 x 96 back 16.2 -> 12.4.
 
 // axis 2 of `lines` rows (line l = (c0, c1) at c0 S0 + c1 S1); n / 2, S0 and S1 multiples of 4
 template <int D, int L, int NT>

@@ -536,7 +536,7 @@ DEVI void coarse_synthesis_w(float* sm, int src, int dst, int n0, int n1, int n2
 // memory.  Per output the taps are summed in the order of the _w versions.  Together with the matrix
 // products below, between the first and the last instruction of one work-group: 128^2, 8 taps, 5 levels
 // 34800 -> 23200 cycles; 64^2, 16 taps, 4 levels 22600 -> 13900.  As a launch: one 128^2 db4 image 16.2 -> 11.7
-// us, the 64 blocks of 128^2 of a 64 x 1024^2 db8 batch 19.5 -> 17.0, one 128^2 db6 block 15.4 -> 13.0.
+// us, the 64 blocks of 128^2 of a 64 x 1024^2 db8 batch 19.5 -> 17.9, one 128^2 db6 block 15.4 -> 12.5.
 
 DEVI int ceil_log2(int v) { return v <= 1 ? 0 : 32 - __builtin_clz(v - 1); }
 

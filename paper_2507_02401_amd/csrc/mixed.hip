@@ -5,7 +5,8 @@
 // registers, 26.8 KB, five work-groups a CU), which costs the shorter filters less than their own launches.
 // Plans of 2 filter lengths with and without, us: 4 x 1024^2 80 -> 54, 32 x 1024^2 175 -> 143, 64 x 512^2
 // 111 -> 86, 64 x 256^2 65 -> 63 (never slower, so there is no limit); 48 instances of mixed sizes, three
-// lengths and some cubes 298 -> 216, 36 of them 226 -> 148, 8 of them 137 -> 79.
+// lengths and some cubes 298 -> 218, 36 of them 226 -> 149, 8 of them 137 -> 81 (calls one after the other;
+// a call alone, from its submission to a synchronisation, is 256, 181 and 103).
 
 #include "kcommon.h"
 #include "lowpass.h"
