@@ -122,7 +122,7 @@ def source_hash():
     """Hash of the level kernels' source: counter readings are only valid for the kernels they measured."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("kernels.hip", "lowpass.h", "kcommon.h", "tiles.h"):
+    for name in ("kernels.hip", "lowpass.h", "kcommon.h", "tiles.h", "composite.h", "internal.h"):
         with open(os.path.join(ROOT, "paper_2507_02401_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
