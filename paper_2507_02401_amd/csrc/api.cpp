@@ -1088,6 +1088,20 @@ int call_regions(const void* in, const void* out, int64_t bytes, const void* ws,
 
 int64_t round8(int64_t v) { return (v + 7) & ~(int64_t)7; }
 
+// LDS class of a coarse launch.  A full-bank launch of at most one 3-D block per CU has no use for the room that
+// work-groups of 512 threads leave, and their kernel is 3 KB of code longer (first executed cold in a call of many
+// launches): 4 to 12 taps and sides that the lean passes take run with 1024.  In calls, us, 512 / 1024 threads,
+// down and up: one 16^3 block, 8 taps, 7.4 / 6.4 and 7.7 / 7.1; 32 of 16^3, 6 taps, 6.8 / 6.2 and 8.1 / 7.2; 200 of
+// 16 x 16 x 8, 10 taps, 8.1 / 8.2 and 9.3 / 9.5 (the worst).  2 and 14 taps, other sides (six of 12^3, 8 taps, up
+// 8.3 / 8.9) and 2-D blocks gain nothing or lose.  Squared norms keep one order of their sums at every batch size.
+constexpr int kCus = 256;
+size_t coarse_lds(const Launch& l, const TailTask* table, int grid) {
+  const TailTask& t = l.tail;
+  const bool few = (l.kind == 1 || l.kind == 2) && l.D == 3 && l.L >= 4 && l.L <= 12 && !table && grid <= kCus &&
+                   ((t.b[0] | t.b[1] | t.b[2]) & 7) == 0 && !(t.flags & kNormSq);
+  return few ? std::max(l.lds, sizeof(float) * 2 * (size_t)kFbCoarseMaxBlock) : l.lds;
+}
+
 es_status run_launch(const Launch& l, const Filter& f, hipStream_t stream, const Task* table, int count,
                      int total_wg, const TailTask* ttable, const FilterBank* bank = nullptr) {
   if (total_wg <= 0) return ES_OK;
@@ -1109,7 +1123,7 @@ es_status run_launch(const Launch& l, const Filter& f, hipStream_t stream, const
     a.total_wg = total_wg;
     a.t0 = l.tail;
     a.bank = bank;
-    ES_HIP(launch_tail(l.kind, l.D, l.L, a, grid, l.lds, f, stream), "tail kernel launch");
+    ES_HIP(launch_tail(l.kind, l.D, l.L, a, grid, coarse_lds(l, ttable, grid), f, stream), "tail kernel launch");
   }
   return ES_OK;
 }
