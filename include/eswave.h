@@ -300,7 +300,10 @@ es_status es_plan_create(const es_desc* descs, int32_t count, int op, void* stre
 
 /* Runs the plan: in[i] / out[i] (host arrays of device pointers) are instance i's input and
  * output.  When the pointers equal those of the previous call the captured graph is
- * replayed as is; otherwise the descriptor table is refreshed first. */
+ * replayed as is; otherwise the descriptor table is refreshed first.  The graph is one chain of launches, which costs
+ * the host least.  ESWAVE_PLAN_BRANCHES=3 in the environment of the call that captures it (the first) makes it three
+ * branches, faster where the pointers stay the same or every call is waited for (48 instances of 23 M voxels: 217 ->
+ * 190 us and 256 -> 191 us) and slower where they change on each (218 -> 254 us). */
 es_status es_plan_execute(es_plan* plan, const float* const* in, float* const* out, void* ws,
                           size_t ws_bytes, void* stream);
 

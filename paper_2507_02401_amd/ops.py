@@ -234,7 +234,8 @@ class RaggedPlan:
     """Many instances of different geometry in one captured launch sequence (es_plan_*).
 
     descs: list of (grid_shape, order, levels, s).  Call with lists of input and output
-    tensors (one per instance, matching the descriptors).
+    tensors (one per instance, matching the descriptors).  ESWAVE_PLAN_BRANCHES=3, set before the first call,
+    is faster for large plans whose tensors stay the same from call to call (es_plan_execute in eswave.h).
     """
 
     def __init__(self, descs, op, device=None):
